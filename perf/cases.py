@@ -223,3 +223,34 @@ def tolerance(case):
     # fp32 accumulation, then exp(logit - lse) in fp32: 4.2e-7 and 3e-6 off float64 at worst
     # over head sizes 32..256, windows 12..200, both types
     return {"rel": 2e-6, "max": 1.5e-5}
+
+
+def exact(case, seed):
+    """The scores in float64: softmax over the keys of a sequence, the largest probability over
+    the task tokens, its mean over the query heads of a group, plus the mean over KV heads.
+    What the whole pass returns are copies of cache rows and whole numbers."""
+    if case["entry"] == "compress":
+        return None
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    dtype = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    lens, window, hkv, d = _lens(case), case["window"], case["hkv"], case["head_dim"]
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    scores = torch.empty((case["layers"], hkv, cu[-1]), dtype=torch.float64, device="cuda")
+    for l in range(case["layers"]):
+        q, k, _ = _layer(case, l, lens, cu, gen, dtype)
+        for b, n in enumerate(lens):
+            if n == 0:
+                continue
+            for h in range(hkv):
+                keys = k[h, cu[b]:cu[b + 1]].double()
+                rows = q[b].view(hkv, -1, window, d)[h].double()
+                logits = (rows.reshape(-1, d) @ keys.T).view(-1, window, n) / d ** 0.5
+                if case["causal_tail"]:
+                    seen = torch.arange(n, device="cuda") <= torch.arange(n - window, n, device="cuda")[:, None]
+                    logits = logits.masked_fill(~seen, float("-inf"))
+                scores[l, h, cu[b]:cu[b + 1]] = torch.softmax(logits, dim=-1).amax(dim=1).mean(dim=0)
+        scores[l] += scores[l].mean(dim=0, keepdim=True)
+    return {"scores": scores}
