@@ -96,6 +96,15 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Wait for all of this wave's vector-memory and LDS operations.  At a loop-head barrier behind
+// wait_vmcnt the compiler has been seen to leave out the wait for LDS writes of the iteration
+// before (the generated code went from ds_write over the back edge to s_barrier without an
+// lgkmcnt wait, and another wave's read could overtake the write), so such a barrier is
+// preceded by this wait.
+__device__ __forceinline__ void wait_memory() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
 // Monotone map from float to unsigned: a < b  <=>  key(a) < key(b); -0 maps to
 // the same key as +0.
 __device__ __forceinline__ uint32_t float_to_ordered(float f) {

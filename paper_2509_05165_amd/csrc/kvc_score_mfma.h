@@ -36,15 +36,6 @@ constexpr int MF_DMA = MF_KBUF / 16 / MF_THREADS;   // direct loads per thread p
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
-// 16 bytes per lane straight from global memory into LDS: lane i of the wave
-// writes LDS bytes [lds_base + 16 i, +16).  lds_base must be wave-uniform.  The
-// load is tracked by vmcnt only; the caller orders it with wait_vmcnt + barrier.
-// K is read once per pass and a layer's K exceeds every cache, so the loads carry
-// the streaming hint (keeps the partial results of the pass in L2 instead).
-__device__ __forceinline__ void lds_dma16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_base), "v"(gptr)
-               : "memory");
-}
 // Combine the two half-waves: both halves end up with op(lower, upper).
 template <bool MAX>
 __device__ __forceinline__ float cross_half(float v) {
@@ -179,9 +170,14 @@ __device__ __forceinline__ void emit_slice(int i, const f32x16& x0, const f32x16
   }
 }
 
-// 16 bytes per lane from (scalar base + per-lane byte offset) into LDS.
+// 16 bytes per lane from (scalar base + per-lane byte offset) straight into LDS: lane i of the
+// wave writes LDS bytes [lds_base + 16 i, +16).  lds_base must be wave-uniform.  The load is
+// tracked by vmcnt only; the caller orders it with a wait and a barrier.  The s_nop is the wait
+// state that the hardware asks for between a scalar write of m0 and a load to LDS.
+// K is read once per pass and a layer's K exceeds every cache, so the loads carry
+// the streaming hint (keeps the partial results of the pass in L2 instead).
 __device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(voff), "s"(sbase)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(voff), "s"(sbase)
                : "memory");
 }
 
@@ -629,7 +625,7 @@ __device__ __forceinline__ void score_mfma_body(
   // causal mask, every tile when the wave has an odd number of key tiles.  Tile t
   // is in buffer t&1; tile t+1 is requested once every wave is done with tile t-1.
   for (int t = npipe; t < ntiles; ++t) {
-    wait_vmcnt<0>();
+    wait_memory();       // tile t, and this wave's partials of tile t-1 in LDS
     __syncthreads();
     if (EMIT && t > 0) epilogue(t - 1, MF_TILE);
     if (issued < t + 1 && t + 1 < ntiles) { issue_tile(t + 1); issued = t + 1; }
