@@ -7,9 +7,14 @@
 //   merge : lse2[row] = log2 sum_c 2^t over all chunks of the row's sequence
 //   emit  : logits again; p = 2^(t - lse2); Agg_task over m, Agg_group over g
 //   finish: combine row-chunk partials, add the mean over KV heads
-// Two implementations of stats/emit: a bf16 matrix-core (MFMA) kernel for
-// d = 128, and a plain fp32 kernel for everything else (f32 inputs, other
-// head sizes, windows that are not a multiple of 32).
+// Three implementations of stats/emit, chosen by type, shape and alignment:
+//   kvc_score_mfma.h  query-stationary matrix-core kernels: bf16, d = 128, windows of 32, 64,
+//                     128 or a multiple of 256
+//   kvc_score_tile.h  key-stationary matrix-core kernels: every other shape, both types
+//   the plain kernels below: rows that do not start at 16-byte addresses, which the
+//                     16-byte loads of the others need
+#include <algorithm>
+
 #include "kvc_internal.h"
 
 namespace kvc {
@@ -30,12 +35,14 @@ __device__ __forceinline__ float load_as_float(const uint16_t* p) {
 }  // namespace kvc
 
 #include "kvc_score_mfma.h"
+#include "kvc_score_tile.h"
 
 namespace kvc {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Plain fp32 path
+// Plain fp32 path (vector ALU, one element per load: some 200 times slower than the
+// key-stationary kernels, which take whatever it takes at 16-byte addresses)
 // ---------------------------------------------------------------------------
 constexpr int GEN_TILE = 32;     // keys per LDS tile
 constexpr int GEN_MGROUPS = 8;   // 256 threads = 32 key lanes x 8 row groups
@@ -428,7 +435,6 @@ inline int mfma_chunk(const Problem& pb, int row_chunks) {
   const int64_t wgs = big_chunks * pb.hkv * row_chunks * pb.batch * pb.layers;
   return wgs >= 2048 ? MF_CHUNK_BIG : MF_CHUNK;
 }
-constexpr int MIN_CHUNK = 256;   // workspace is sized for the smallest chunk in use
 constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact emit launch (two per compute unit)
 
 struct ScoreLayout {
@@ -440,15 +446,23 @@ struct ScoreLayout {
 ScoreLayout score_layout(const Problem& pb) {
   ScoreLayout L{};
   L.rows_layer = pb.batch * pb.hq * pb.window;
-  L.max_chunks = int((pb.max_seqlen + MIN_CHUNK - 1) / MIN_CHUNK);
-  if (L.max_chunks < 1) L.max_chunks = 1;
   const bool mfma = mfma_supported(pb);
   L.row_chunks = mfma ? (pb.group * pb.window + MF_RCHUNK - 1) / MF_RCHUNK : 1;
-  // the matrix-core path runs all layers in one launch and keeps the statistics,
-  // log-sum-exps and group partials of every layer; the generic path goes layer by layer
-  L.layers_held = mfma ? pb.layers : 1;
-  if (mfma) L.max_chunks = int((pb.max_seqlen + MF_CHUNK - 1) / MF_CHUNK) > 0
-                               ? int((pb.max_seqlen + MF_CHUNK - 1) / MF_CHUNK) : 1;
+  // The query-stationary path runs all layers in one launch and keeps the statistics,
+  // log-sum-exps and group partials of every layer.
+  if (mfma) {
+    L.layers_held = pb.layers;
+    L.max_chunks = std::max(1, int((pb.max_seqlen + MF_CHUNK - 1) / MF_CHUNK));
+  } else {
+    // The key-stationary path has a chunk per workgroup.  It takes as many layers at once as
+    // keep the statistics below what the rank stage asks of the same workspace anyway (or
+    // below 64 MB), and at least one.
+    const int keys = tile_keys(tile_ksteps(pb.dtype, pb.d * esize(pb.dtype) / 16));
+    L.max_chunks = std::max(1, int((pb.max_seqlen + keys - 1) / keys));
+    const size_t per_layer = size_t(L.rows_layer) * (8 * size_t(L.max_chunks) + 4);
+    const size_t bound = std::max(size_t(64) << 20, size_t(pb.layers) * pb.hkv * size_t(pb.total) * 16);
+    L.layers_held = int(std::min<size_t>(pb.layers, std::max<size_t>(1, bound / per_layer)));
+  }
   size_t cur = 0;
   L.off_m = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
   L.off_s = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
@@ -470,6 +484,95 @@ ScoreLayout score_layout(const Problem& pb) {
   }
   L.total = cur;
   return L;
+}
+
+// Value norms (vnorm != null) and finish of the layers [l0, l0 + layers), one launch each; `part`
+// holds the group partials of the first of them.
+kvc_status finish_scores(const Problem& pb, const FinishArgs& fa, const void* const* v, float* vnorm,
+                         const float* part, size_t part_stride, float* S_all, int l0, int layers,
+                         hipStream_t stream) {
+  const int total = int(pb.total);
+  const size_t s_stride = size_t(pb.hkv) * total;
+  float* S = S_all + size_t(l0) * s_stride;
+  if (vnorm) {
+    PtrTable vt{};
+    for (int l = 0; l < layers; ++l) vt.p[l] = v[l0 + l];
+    const size_t rows = size_t(pb.hkv) * total;
+    const dim3 vgrid(unsigned((rows + 16 * VN_ROWS - 1) / (16 * VN_ROWS)), layers);
+    if (pb.dtype == KVC_BF16)
+      KVC_LAUNCH("value_norm_kernel", stream, value_norm_kernel<uint16_t><<<vgrid, 256, 0, stream>>>(
+          vt, rows, pb.d, vnorm));
+    else
+      KVC_LAUNCH("value_norm_kernel", stream, value_norm_kernel<float><<<vgrid, 256, 0, stream>>>(
+          vt, rows, pb.d, vnorm));
+    KVC_LAUNCH("score_finish", stream, score_finish<<<dim3((total + 255) / 256, layers), 256, 0, stream>>>(
+        part, fa, pb.seq, S, part_stride, s_stride, vnorm));
+    return KVC_OK;
+  }
+  const bool plain = fa.row_chunks == 1 && pb.keep_first == 0 && pb.keep_last == 0 &&
+                     (pb.hkv == 8 || pb.hkv == 4);
+  // four tokens per thread need 16-byte aligned rows in every layer
+  const bool vec4 = total % 4 == 0 && part_stride % 4 == 0 &&
+                    (reinterpret_cast<uintptr_t>(part) | reinterpret_cast<uintptr_t>(S)) % 16 == 0;
+#define KVC_FINISH_PLAIN(HKV, VEC)                                                              \
+  KVC_LAUNCH("score_finish", stream,                                                            \
+             score_finish_plain<HKV, VEC><<<dim3((total / VEC + 255) / 256, layers), 256, 0, stream>>>( \
+                 part, S, total, fa.group_norm, pb.add_head_mean, part_stride, s_stride))
+  if (plain && pb.hkv == 8 && vec4) KVC_FINISH_PLAIN(8, 4);
+  else if (plain && pb.hkv == 8) KVC_FINISH_PLAIN(8, 1);
+  else if (plain && pb.hkv == 4 && vec4) KVC_FINISH_PLAIN(4, 4);
+  else if (plain && pb.hkv == 4) KVC_FINISH_PLAIN(4, 1);
+  else
+    KVC_LAUNCH("score_finish", stream, score_finish<<<dim3((total + 255) / 256, layers), 256, 0, stream>>>(
+        part, fa, pb.seq, S, part_stride, s_stride, nullptr));
+#undef KVC_FINISH_PLAIN
+  return KVC_OK;
+}
+
+// Statistics, merge and emit of the key-stationary path for the layers [l0, l0 + layers).
+template <typename T, int KS>
+kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* const* q,
+                       const void* const* k, int l0, int layers, float* part_m, float* part_s,
+                       float* lse2, float* out, size_t out_stride, hipStream_t stream) {
+  constexpr int KB = tile_keys(KS) / 128;
+  PtrTable qt{}, kt{};
+  for (int l = 0; l < layers; ++l) { qt.p[l] = q[l0 + l]; kt.p[l] = k[l0 + l]; }
+  constexpr int keys = tile_keys(KS);
+  int64_t flat = 0;                                   // (sequence, chunk) pairs
+  for (int b = 0; b < pb.batch; ++b) flat += (pb.seq.cu[b + 1] - pb.seq.cu[b] + keys - 1) / keys;
+  TileArgs a{};
+  a.batch = pb.batch; a.group = pb.group; a.window = pb.window; a.total = int(pb.total);
+  a.pieces = pb.d * esize(pb.dtype) / 16; a.hkv = pb.hkv;
+  a.head_rows = (pb.window + 7) / 8 * 8;
+  a.head_magic = uint32_t(((uint64_t(1) << 32) + a.head_rows - 1) / a.head_rows);
+  a.causal = pb.causal_tail; a.group_max = pb.agg_group == KVC_AGG_MAX;
+  a.c2 = pb.scale * LOG2E;
+  a.rows_all = size_t(L.rows_layer) * layers;
+  a.out_layer_stride = out_stride;
+  // the rows of a head are independent in the statistics pass: small launches deal them
+  // to several workgroups until every compute unit has its two
+  const int64_t wgs = flat * pb.hkv * layers;
+  const int tiles = (pb.group * pb.window + TL_ROWS - 1) / TL_ROWS;
+  a.row_split = int(std::max<int64_t>(1, std::min<int64_t>(tiles, 512 / wgs)));
+  KVC_LAUNCH("score_tile<stats>", stream,
+             score_tile<T, KS, KB, false, true><<<dim3(unsigned(flat), pb.hkv * a.row_split, layers), TL_THREADS, 0, stream>>>(
+                 qt, kt, pb.seq, a, part_m, part_s, nullptr, nullptr));
+  a.row_split = 1;
+  const int rows_all = int(a.rows_all), chunks = int((pb.max_seqlen + keys - 1) / keys);
+  if (chunks <= 4)
+    KVC_LAUNCH("score_merge", stream, score_merge_few<<<(rows_all + 255) / 256, 256, 0, stream>>>(
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, nullptr));
+  else
+    KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, nullptr));
+  const dim3 grid(unsigned(flat), pb.hkv, layers);
+  if (pb.agg_task == KVC_AGG_MAX)
+    KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, KB, true, true><<<grid, TL_THREADS, 0, stream>>>(
+        qt, kt, pb.seq, a, nullptr, nullptr, lse2, out));
+  else
+    KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, KB, true, false><<<grid, TL_THREADS, 0, stream>>>(
+        qt, kt, pb.seq, a, nullptr, nullptr, lse2, out));
+  return KVC_OK;
 }
 
 }  // namespace
@@ -573,39 +676,47 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
 #undef KVC_SCORE_MFMA_WQ
 #undef KVC_SCORE_MFMA_BLOCKS
 #undef KVC_SCORE_MFMA
-    if (vnorm && pb.layers > 0 && total > 0) {   // value norms and finish of all layers, one launch each
-      PtrTable vt{};
-      for (int l = 0; l < pb.layers; ++l) vt.p[l] = v[l];
-      const size_t rows = size_t(pb.hkv) * total;
-      const dim3 vgrid(unsigned((rows + 16 * VN_ROWS - 1) / (16 * VN_ROWS)), pb.layers);
-      KVC_LAUNCH("value_norm_kernel", stream, value_norm_kernel<uint16_t><<<vgrid, 256, 0, stream>>>(
-          vt, rows, pb.d, vnorm));
-      KVC_LAUNCH("score_finish", stream, score_finish<<<dim3((total + 255) / 256, pb.layers), 256, 0, stream>>>(
-          part_all, fa, pb.seq, S, out_stride, rows, vnorm));
-    } else if (pb.layers > 0 && total > 0) {
-      const bool plain = L.row_chunks == 1 && pb.keep_first == 0 && pb.keep_last == 0 &&
-                         (pb.hkv == 8 || pb.hkv == 4);
-      // four tokens per thread need 16-byte aligned rows in every layer
-      const bool vec4 = total % 4 == 0 && out_stride % 4 == 0 &&
-                        (reinterpret_cast<uintptr_t>(part_all) | reinterpret_cast<uintptr_t>(S)) % 16 == 0;
-      const size_t s_stride = size_t(pb.hkv) * total;
-#define KVC_FINISH_PLAIN(HKV, VEC)                                                              \
-  KVC_LAUNCH("score_finish", stream,                                                            \
-             score_finish_plain<HKV, VEC><<<dim3((total / VEC + 255) / 256, pb.layers), 256, 0, stream>>>( \
-                 part_all, S, total, fa.group_norm, pb.add_head_mean, out_stride, s_stride))
-      if (plain && pb.hkv == 8 && vec4) KVC_FINISH_PLAIN(8, 4);
-      else if (plain && pb.hkv == 8) KVC_FINISH_PLAIN(8, 1);
-      else if (plain && pb.hkv == 4 && vec4) KVC_FINISH_PLAIN(4, 4);
-      else if (plain && pb.hkv == 4) KVC_FINISH_PLAIN(4, 1);
-      else
-        KVC_LAUNCH("score_finish", stream, score_finish<<<dim3((total + 255) / 256, pb.layers), 256, 0, stream>>>(
-            part_all, fa, pb.seq, S, out_stride, s_stride, nullptr));
-#undef KVC_FINISH_PLAIN
+    return finish_scores(pb, fa, v, vnorm, part_all, out_stride, S, 0, pb.layers, stream);
+  }
+
+  // Everything else: the key-stationary path, as many layers at a time as the workspace holds.
+  // Its 16-byte loads need rows at 16-byte addresses; the plain kernels below take any.
+  bool aligned = true;
+  for (int l = 0; l < pb.layers; ++l)
+    aligned = aligned && (reinterpret_cast<uintptr_t>(q[l]) | reinterpret_cast<uintptr_t>(k[l])) % 16 == 0;
+  if (aligned) {
+    const size_t s_stride = size_t(pb.hkv) * total;
+    for (int l0 = 0; l0 < pb.layers; l0 += L.layers_held) {
+      const int layers = std::min(L.layers_held, pb.layers - l0);
+      float* part = separate ? reinterpret_cast<float*>(w + L.off_part) : S + size_t(l0) * s_stride;
+      kvc_status st = KVC_OK;
+#define KVC_SCORE_TILES(T, KS) \
+  st = score_tiles<T, KS>(pb, L, q, k, l0, layers, part_m, part_s, lse2, part, s_stride, stream); break
+      const int ks = tile_ksteps(pb.dtype, pb.d * esize(pb.dtype) / 16);
+      if (pb.dtype == KVC_BF16) {
+        switch (ks) {
+          case 4: KVC_SCORE_TILES(uint16_t, 4);
+          case 5: KVC_SCORE_TILES(uint16_t, 5);
+          case 6: KVC_SCORE_TILES(uint16_t, 6);
+          case 8: KVC_SCORE_TILES(uint16_t, 8);
+          default: KVC_SCORE_TILES(uint16_t, 16);
+        }
+      } else {
+        switch (ks) {
+          case 4: KVC_SCORE_TILES(float, 4);
+          case 8: KVC_SCORE_TILES(float, 8);
+          case 16: KVC_SCORE_TILES(float, 16);
+          default: KVC_SCORE_TILES(float, 32);
+        }
+      }
+#undef KVC_SCORE_TILES
+      if (st == KVC_OK) st = finish_scores(pb, fa, v, vnorm, part, s_stride, S, l0, layers, stream);
+      if (st != KVC_OK) return st;
     }
     return KVC_OK;
   }
 
-  // generic fp32 path: layer by layer
+  // plain fp32 path: layer by layer
   for (int l = 0; l < pb.layers; ++l) {
     float* S_l = S + size_t(l) * pb.hkv * total;
     float* part = separate ? reinterpret_cast<float*>(w + L.off_part) : S_l;

@@ -1,0 +1,285 @@
+// Matrix-core kernels of kvc_score for every shape the query-stationary kernels do not
+// take: bf16 and float32, any head size, any window.  Included by kvc_score.hip only.
+//
+// The roles are the reverse of the query-stationary kernels: a workgroup (4 waves) keeps
+// TILE_KEYS keys of one KV head in registers and streams the head's query rows
+// through LDS, 64 rows at a time, one tile ahead.  All query rows of a key then pass
+// through one wave, so the window and the group need not divide anything: the statistics
+// of a row over the keys of a wave, and the aggregate over the rows of a key, never leave
+// the wave (four waves' statistics of a row meet in LDS).  K is read from memory once per
+// pass, whatever the number of query rows; the query rows of a head are small and come
+// out of the cache.
+//
+// Both types use the same operand layout, 16-byte pieces: of a row's pieces, lane l of a
+// 32x32 operand holds piece 2 ks + l / 32 of row l % 32 in step ks.  For bf16 that is
+// the operand of one v_mfma_f32_32x32x16_bf16; for float32 the four elements of the piece
+// feed four v_mfma_f32_32x32x2_f32 (any order of the products is as good as another, as
+// long as both operands agree).  float32 products and sums stay float32 throughout.
+//
+// LDS tile: row r at slot r * PS (PS = 2 KS + 1 slots of 16 bytes: an odd stride, so that the
+// reads of 16 consecutive rows cover all banks).  The direct global->LDS loads write
+// consecutive slots; 64 rows of PS slots are exactly PS wave instructions.
+#pragma once
+
+namespace kvc {
+namespace {
+
+constexpr int TL_THREADS = 256;
+constexpr int TL_ROWS = 64;          // query rows per LDS tile
+
+struct TileArgs {
+  int batch, group, window, total, pieces;
+  int hkv, row_split;                // STATS: the row tiles of a head are dealt to row_split workgroups
+  int head_rows;                     // EMIT: window rounded up to 8 (rows of a head in tile order)
+  uint32_t head_magic;               // EMIT: ceil(2^32 / head_rows)
+  int causal, group_max;
+  float c2;
+  size_t rows_all;                   // query rows of the launch: layers * batch * Hq * window
+  size_t out_layer_stride;
+};
+
+// 16 bytes per lane from global memory into LDS at lds_base + 16 * lane, tracked by vmcnt only.
+__device__ __forceinline__ void tile_dma16(const void* gptr, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
+}
+
+// One k-step (16 bytes of every row of both operands) of a 32x32 tile.
+template <typename T>
+__device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
+  if constexpr (sizeof(T) == 2) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(rows), as_bf16x8(cols), acc, 0, 0, 0);
+  } else {
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rows.x), __uint_as_float(cols.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rows.y), __uint_as_float(cols.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rows.z), __uint_as_float(cols.z), acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rows.w), __uint_as_float(cols.w), acc, 0, 0, 0);
+  }
+}
+
+// KS: k-steps (pairs of 16-byte pieces) a row is padded to; KB: 32-key blocks per wave.
+// grid: ((sequence, chunk) pairs, Hkv * row_split, layers)
+//
+// STATS: keys on the rows of the matrix tile, so a lane owns one query row: maximum and
+// sum of 2^(t - max) over the wave's keys, then over the workgroup's, to part_m / part_s.
+// EMIT: queries on the rows, a lane owns one key.  In tile order every query head is
+// padded to a multiple of 8 rows, so each group of four accumulator registers (8 rows) belongs to
+// one head; the padding rows carry lse = +1e30 and contribute nothing.
+template <typename T, int KS, int KB, bool EMIT, bool TASK_MAX>
+__global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : 2) void score_tile(
+    PtrTable q_tab, PtrTable k_tab, SeqTable seq, TileArgs a, float* __restrict__ part_m,
+    float* __restrict__ part_s, const float* __restrict__ lse2, float* __restrict__ out) {
+  constexpr int PS = 2 * KS + 1;
+  constexpr int KEYS = 4 * 32 * KB;
+  constexpr int DMA = (PS + 3) / 4;             // load instructions per wave and tile, at most
+  __shared__ __attribute__((aligned(16))) uint4 qtile[2][TL_ROWS * PS];
+  __shared__ float2 stat[EMIT ? 1 : 2][4][EMIT ? 1 : TL_ROWS];
+  __shared__ __attribute__((aligned(16))) float nls[EMIT ? 2 : 1][EMIT ? TL_ROWS : 4];
+
+  const int layer = blockIdx.z;
+  int b = 0, chunk = blockIdx.x;
+  for (; b < a.batch - 1; ++b) {
+    const int nc = (seq.cu[b + 1] - seq.cu[b] + KEYS - 1) / KEYS;
+    if (chunk < nc) break;
+    chunk -= nc;
+  }
+  const int tok0 = seq.cu[b], n = seq.cu[b + 1] - tok0;
+  if (chunk * KEYS >= n) return;
+  const int h = blockIdx.y / a.row_split, split = blockIdx.y - h * a.row_split;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int col = lane & 31, half = lane >> 5;
+  const int wkey0 = chunk * KEYS + wave * 32 * KB;       // first key of the wave
+  const int P = a.pieces;
+  const uint4* q_head = static_cast<const uint4*>(q_tab.p[layer]) +
+                        ((size_t)b * a.hkv + h) * a.group * a.window * P;
+  const uint4* k_head = static_cast<const uint4*>(k_tab.p[layer]) + ((size_t)h * a.total + tok0) * P;
+  // first query row of this (layer, sequence, KV head) among the rows of the launch
+  const size_t qrow0 = (((size_t)layer * a.batch + b) * a.hkv + h) * a.group * a.window;
+  const int R = EMIT ? a.group * a.head_rows : a.group * a.window;
+  const int all_tiles = (R + TL_ROWS - 1) / TL_ROWS;
+  const int t_begin = EMIT ? 0 : (int)((int64_t)all_tiles * split / a.row_split);
+  const int t_end = EMIT ? all_tiles : (int)((int64_t)all_tiles * (split + 1) / a.row_split);
+  if (t_begin >= t_end) return;
+
+  // query row (among the head's group * window) that row `pr` in tile order stands for, and
+  // whether it is a real one
+  auto source_row = [&](int pr, bool& real) -> int {
+    if (!EMIT) { real = pr < R; return min(pr, R - 1); }
+    uint32_t g = __umulhi((uint32_t)pr, a.head_magic);   // exact or one too large
+    if (g * (uint32_t)a.head_rows > (uint32_t)pr) --g;
+    const int m = pr - (int)g * a.head_rows;
+    real = (int)g < a.group && m < a.window;
+    return min((int)g, a.group - 1) * a.window + min(m, a.window - 1);
+  };
+  const uint32_t qtile_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint4*)(&qtile[0][0]);
+  auto issue_tile = [&](int t) {
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(qtile_lds + (uint32_t)(t & 1) * (TL_ROWS * PS * 16));
+#pragma unroll
+    for (int i = 0; i < DMA; ++i) {
+      const int j = i * 4 + wave;                        // wave-uniform
+      if (j < PS) {
+        const int slot = j * 64 + lane;
+        const int r = slot / PS, piece = min(slot - r * PS, P - 1);
+        bool real;
+        tile_dma16(q_head + (size_t)source_row(t * TL_ROWS + r, real) * P + piece, dst + j * 1024);
+      }
+    }
+  };
+  // EMIT: minus the log-sum-exp of row `lane` of tile t
+  auto load_nl = [&](int t) -> float {
+    bool real;
+    const int r = source_row(t * TL_ROWS + lane, real);
+    return real ? -lse2[qrow0 + r] : NEG_BIG;
+  };
+
+  issue_tile(t_begin);
+  // ---- keys: registers for the whole kernel; pieces past the row are zero ----
+  uint4 kf[KB][KS];
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    const uint4* krow = k_head + (size_t)min(wkey0 + kb * 32 + col, n - 1) * P;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int piece = 2 * ks + half;
+      kf[kb][ks] = piece < P ? krow[piece] : make_uint4(0, 0, 0, 0);
+    }
+  }
+  float next_nl = 0.f;
+  if (EMIT && wave == 0) nls[t_begin & 1][lane] = load_nl(t_begin);
+
+  const bool active = wkey0 < n;                                  // wave-uniform, like the next two
+  const bool ragged = wkey0 + 32 * KB > n;
+  const bool masked = a.causal && wkey0 + 32 * KB - 1 > n - a.window;
+  const int subs = a.head_rows >> 3;                              // EMIT: groups of 8 rows per query head
+  int sub = 0;                                                    // EMIT: of them, done of the current head
+  float tacc[KB], gacc[KB];                                       // EMIT: current head's aggregate, group's
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) { tacc[kb] = TASK_MAX ? NEG_BIG : 0.f; gacc[kb] = 0.f; }
+  const float inv_window = 1.f / float(a.window);
+  auto finish_head = [&]() {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const float tv = cross_half<TASK_MAX>(tacc[kb]);
+      const float sv = TASK_MAX ? fast_exp2(tv) : tv * inv_window;
+      gacc[kb] = a.group_max ? fmaxf(gacc[kb], sv) : gacc[kb] + sv;
+      tacc[kb] = TASK_MAX ? NEG_BIG : 0.f;
+    }
+    sub = 0;
+  };
+  // STATS: one wave joins the four waves' statistics of tile t (a row per lane)
+  auto store_stats = [&](int t) {
+    const int row = t * TL_ROWS + lane;
+    if (wave != (t & 3) || row >= R) return;
+    float2 x[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) x[w] = stat[t & 1][w][lane];
+    const float mm = fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x));
+    float ss = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) ss += x[w].y * fast_exp2(x[w].x - mm);
+    part_m[(size_t)chunk * a.rows_all + qrow0 + row] = mm;
+    part_s[(size_t)chunk * a.rows_all + qrow0 + row] = ss;
+  };
+
+  for (int t = t_begin; t < t_end; ++t) {
+    wait_memory();
+    __syncthreads();                      // tile t is complete; every wave is done with tile t-1
+    if (!EMIT && t > t_begin) store_stats(t - 1);
+    if (t + 1 < t_end) {
+      issue_tile(t + 1);
+      if (EMIT && wave == 0) next_nl = load_nl(t + 1);
+    }
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      if (EMIT && !active) break;
+      f32x16 acc[KB];
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[kb][r] = 0.f;
+      const uint4* qrow = &qtile[t & 1][(blk * 32 + col) * PS + half];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const uint4 qf = qrow[2 * ks];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+          acc[kb] = EMIT ? tile_mma<T>(qf, kf[kb][ks], acc[kb]) : tile_mma<T>(kf[kb][ks], qf, acc[kb]);
+      }
+      if constexpr (!EMIT) {
+        if (ragged) {                     // keys past the sequence drop out
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (wkey0 + kb * 32 + acc_row(r, half) >= n) acc[kb][r] = -__builtin_inff();
+        }
+        if (masked) {                     // task token m sees keys up to n - window + m
+          const int seen = n - a.window + (t * TL_ROWS + blk * 32 + col) % a.window;
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (wkey0 + kb * 32 + acc_row(r, half) > seen) acc[kb][r] = -__builtin_inff();
+        }
+        float amax = acc[0][0];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) amax = fmaxf(amax, acc[kb][r]);
+        // (no key seen: the maximum stays finite and every 2^(-inf) below is 0)
+        const float mx = fmaxf(cross_half<true>(amax) * a.c2, NEG_BIG);
+        float s = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s += fast_exp2(fmaf(acc[kb][r], a.c2, -mx));
+        s = cross_half<false>(s);
+        if (half == 0) stat[t & 1][wave][blk * 32 + col] = make_float2(mx, s);
+      } else {
+        // registers 4 i .. 4 i + 3 hold rows 8 i + 4 half .. + 3 of the block
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 nl = *reinterpret_cast<const float4*>(&nls[t & 1][blk * 32 + 8 * i + 4 * half]);
+          const float nlv[4] = {nl.x, nl.y, nl.z, nl.w};
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) {
+            float v = TASK_MAX ? NEG_BIG : 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              float x = fmaf(acc[kb][4 * i + r], a.c2, nlv[r]);
+              if (masked && wkey0 + kb * 32 + col > n - a.window + 8 * sub + 4 * half + r) x = NEG_BIG;
+              v = TASK_MAX ? fmaxf(v, x) : v + fast_exp2(x);
+            }
+            tacc[kb] = TASK_MAX ? fmaxf(tacc[kb], v) : tacc[kb] + v;
+          }
+          if (++sub == subs) finish_head();
+        }
+      }
+    }
+    if (EMIT && wave == 0 && t + 1 < t_end) nls[(t + 1) & 1][lane] = next_nl;
+  }
+  if constexpr (!EMIT) {
+    wait_memory();
+    __syncthreads();
+    store_stats(t_end - 1);
+  } else {
+    float* out_head = out + (size_t)layer * a.out_layer_stride + (size_t)h * a.total + tok0;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const int key = wkey0 + kb * 32 + col;
+      if (half == 0 && key < n) out_head[key] = gacc[kb];
+    }
+  }
+}
+
+// k-steps a row of `pieces` 16-byte pieces is padded to: head sizes 64, 80, 96, 128 and 256 in
+// bf16 and 32, 64, 128 and 256 in float32 need no padding.
+inline int tile_ksteps(int dtype, int pieces) {
+  const int ks = (pieces + 1) / 2;
+  if (dtype == KVC_BF16) return ks <= 4 ? 4 : ks <= 5 ? 5 : ks <= 6 ? 6 : ks <= 8 ? 8 : 16;
+  return ks <= 4 ? 4 : ks <= 8 ? 8 : ks <= 16 ? 16 : 32;
+}
+// keys per workgroup: two 32-key blocks per wave; one where a row takes 128 registers
+constexpr int tile_keys(int ksteps) { return ksteps > 16 ? 128 : 256; }
+
+}  // namespace
+}  // namespace kvc
