@@ -174,9 +174,10 @@ static kvc_status check_budget(const Problem& pb, const int64_t* cu, const int64
 }
 
 // Workspace of kvc_compress: [S][idx][S_sorted][I][tau] (each only when the
-// caller gave no tap for it) followed by one region shared by the stages.
+// caller gave no tap for it), the select stage's scratch (the rank kernel clears it, so it
+// lies outside what that kernel works in) and one region shared by the stages.
 struct CompressLayout {
-  size_t off_S, off_idx, off_sorted, off_I, off_tau, off_stage, total;
+  size_t off_S, off_idx, off_sorted, off_I, off_tau, off_select, off_stage, total;
 };
 
 static CompressLayout compress_layout(const Problem& pb) {
@@ -188,12 +189,12 @@ static CompressLayout compress_layout(const Problem& pb) {
   L.off_sorted = cur; cur += align_up(lht * 4);
   L.off_I = cur;      cur += align_up(size_t(pb.layers) * size_t(pb.total) * 4);
   L.off_tau = cur;    cur += align_up(size_t(pb.batch) * 4);
+  const size_t s = select_workspace_bytes(pb);
+  L.off_select = cur; cur += align_up(s);
   L.off_stage = cur;
   size_t stage = score_workspace_bytes(pb);
   size_t r = rank_workspace_bytes(pb);
   if (r > stage) stage = r;
-  size_t s = select_workspace_bytes(pb);
-  if (s > stage) stage = s;
   size_t g = gather_workspace_bytes(pb);
   if (g > stage) stage = g;
   cur += align_up(stage);
@@ -304,7 +305,7 @@ kvc_status kvc_head_rank(const kvc_params* params, const float* S, const int64_t
   if (!S || !idx || !S_sorted) { set_error("S, idx or S_sorted is NULL"); return KVC_ERR_INVALID_ARG; }
   if ((st = check_ws(workspace, workspace_bytes, rank_workspace_bytes(pb))) != KVC_OK) return st;
   if (pb.total == 0) return KVC_OK;
-  return launch_head_rank(pb, S, idx, S_sorted, workspace, static_cast<hipStream_t>(stream));
+  return launch_head_rank(pb, S, idx, S_sorted, workspace, nullptr, 0, static_cast<hipStream_t>(stream));
 }
 
 kvc_status kvc_composite(const kvc_params* params, const float* S_sorted,
@@ -424,6 +425,7 @@ kvc_status kvc_compress(const kvc_params* params, const kvc_inputs* in, const kv
   float* sorted = out->s_sorted ? out->s_sorted : reinterpret_cast<float*>(ws + L.off_sorted);
   float* I = out->composite ? out->composite : reinterpret_cast<float*>(ws + L.off_I);
   float* tau = out->tau ? out->tau : reinterpret_cast<float*>(ws + L.off_tau);
+  void* select = ws + L.off_select;
   void* stage = ws + L.off_stage;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -431,13 +433,14 @@ kvc_status kvc_compress(const kvc_params* params, const kvc_inputs* in, const kv
     if ((st = launch_score(pb, in->q, in->k, pb.value_norm ? in->v : nullptr, S, stage, s)) !=
         KVC_OK)
       return st;
-    if ((st = launch_head_rank(pb, S, idx, sorted, stage, s)) != KVC_OK) return st;
-    if (!pb.unstructured && (st = launch_composite(pb, sorted, I, s)) != KVC_OK) return st;
+    if ((st = launch_head_rank(pb, S, idx, sorted, stage, static_cast<uint32_t*>(select),
+                               select_clear_words(pb), s)) != KVC_OK)
+      return st;
+    st = launch_composite_select(pb, sorted, I, in->budget, tau, out->lengths, out->offsets, select, s);
+  } else {
+    st = launch_global_select(pb, I, in->budget, tau, out->lengths, out->offsets, select, s);
   }
-  // unstructured: the pool is the rank-aligned per-head scores themselves
-  if ((st = launch_global_select(pb, pb.unstructured ? sorted : I, in->budget, tau, out->lengths,
-                                 out->offsets, stage, s)) != KVC_OK)
-    return st;
+  if (st != KVC_OK) return st;
   if (total_budget > 0) {
     st = launch_gather(pb, in->k, in->v, idx, out->lengths, out->offsets, total_budget,
                        out->k_out, out->v_out, stage, s);

@@ -61,8 +61,9 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
                         const void* const* v, float* S, void* ws, hipStream_t stream);
 
 size_t rank_workspace_bytes(const Problem& pb);
+// clear (may be null): words that the kernel also sets to zero (the select stage's scratch)
 kvc_status launch_head_rank(const Problem& pb, const float* S, int32_t* idx, float* S_sorted,
-                            void* ws, hipStream_t stream);
+                            void* ws, uint32_t* clear, int clear_words, hipStream_t stream);
 
 kvc_status launch_composite(const Problem& pb, const float* S_sorted, float* I,
                             hipStream_t stream);
@@ -71,6 +72,13 @@ size_t select_workspace_bytes(const Problem& pb);
 kvc_status launch_global_select(const Problem& pb, const float* I, const int64_t* budget,
                                 float* tau, int32_t* lengths, int64_t* offsets, void* ws,
                                 hipStream_t stream);
+
+// Composite and selection of kvc_compress: S_sorted must be descending in every row (the
+// composite then is, too) and the first select_clear_words words of ws zero.
+int select_clear_words(const Problem& pb);
+kvc_status launch_composite_select(const Problem& pb, const float* S_sorted, float* I,
+                                   const int64_t* budget, float* tau, int32_t* lengths,
+                                   int64_t* offsets, void* ws, hipStream_t stream);
 
 // Device address of the current GPU's file-scope scratch array of the select
 // stage (KVC_SELECT_STATIC_BYTES bytes, 256-byte aligned).

@@ -396,7 +396,8 @@ __device__ __forceinline__ void radix_sort(SH& sh, int n, int passes, uint32_t r
 template <bool SHORT, bool STREAM>
 __global__ __launch_bounds__(RK_THREADS) void head_rank_kernel(
     const float* __restrict__ S, SeqTable seq, int total, int32_t* __restrict__ idx_out,
-    float* __restrict__ sorted_out, uint2* __restrict__ pairs_a, uint2* __restrict__ pairs_b) {
+    float* __restrict__ sorted_out, uint2* __restrict__ pairs_a, uint2* __restrict__ pairs_b,
+    uint32_t* __restrict__ clear, int clear_words) {
   typedef RankShared<512, SHORT ? RK_SHORT_TILE : RK_THREADS * RK_ITEMS9> Shared9;
   typedef RankShared<1024, SHORT ? RK_SHORT_TILE : RK_THREADS * RK_ITEMS10> Shared10;
   constexpr size_t LDS_BYTES =
@@ -404,6 +405,9 @@ __global__ __launch_bounds__(RK_THREADS) void head_rank_kernel(
             : (sizeof(Shared9) > sizeof(Shared10) ? sizeof(Shared9) : sizeof(Shared10));
   static_assert(LDS_BYTES >= sizeof(RankSweepShared), "the sweep's counters fit too");
   __shared__ __align__(16) unsigned char lds[LDS_BYTES];
+  for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * RK_THREADS + threadIdx.x; i < clear_words;
+       i += gridDim.x * gridDim.y * RK_THREADS)
+    clear[i] = 0;
   const int b = blockIdx.y;
   const int n = seq.cu[b + 1] - seq.cu[b];
   if (n == 0 || (SHORT && n > RK_SHORT_TILE)) return;
@@ -540,7 +544,7 @@ size_t rank_workspace_bytes(const Problem& pb) {
 }
 
 kvc_status launch_head_rank(const Problem& pb, const float* S, int32_t* idx, float* S_sorted,
-                            void* ws, hipStream_t stream) {
+                            void* ws, uint32_t* clear, int clear_words, hipStream_t stream) {
   const size_t lht = size_t(pb.layers) * pb.hkv * size_t(pb.total);
   // (sequences are shorter than 2^29 tokens: checked with the sequence table)
   uint2* pairs_a = static_cast<uint2*>(ws);
@@ -550,13 +554,13 @@ kvc_status launch_head_rank(const Problem& pb, const float* S, int32_t* idx, flo
   const long resident = std::min<long>(long(grid.x) * grid.y, 256);
   if (pb.max_seqlen <= RK_SHORT_TILE) {
     KVC_LAUNCH("head_rank_kernel", stream, head_rank_kernel<true, false><<<grid, RK_THREADS, 0, stream>>>(S, pb.seq, int(pb.total), idx, S_sorted,
-                                                      pairs_a, pairs_b));
+                                                      pairs_a, pairs_b, clear, clear_words));
   } else if (long(pb.max_seqlen) * resident >= RK_STREAM_ITEMS) {
     KVC_LAUNCH("head_rank_kernel", stream, head_rank_kernel<false, true><<<grid, RK_THREADS, 0, stream>>>(S, pb.seq, int(pb.total), idx, S_sorted,
-                                                      pairs_a, pairs_b));
+                                                      pairs_a, pairs_b, clear, clear_words));
   } else {
     KVC_LAUNCH("head_rank_kernel", stream, head_rank_kernel<false, false><<<grid, RK_THREADS, 0, stream>>>(S, pb.seq, int(pb.total), idx, S_sorted,
-                                                      pairs_a, pairs_b));
+                                                      pairs_a, pairs_b, clear, clear_words));
   }
   return KVC_OK;
 }

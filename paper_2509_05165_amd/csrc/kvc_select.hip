@@ -15,6 +15,14 @@
 // atomic updates are complete; the one that draws the last ticket reads the totals
 // with device-scope atomic loads), so a call is five launches instead of eleven.
 //
+// Inside kvc_compress the rows of the pool are known to be sorted (the composite of sorted
+// scores is sorted, in floating point too), the scratch has been cleared by the rank kernel and
+// the scores are still to be aggregated over the heads: launch_composite_select then needs three
+// launches.  The first pass aggregates, stores and histograms, and the last workgroup of the
+// third pass finds the counts of a row by searching it instead of sweeping all rows.  Composite
+// and selection of 32 layers x 777 tokens: 34 -> 30 us; at 131072 tokens the pass as a
+// whole is within the noise of the separate launches.
+//
 // A "layer" here is a row of the pool: a layer, or a (layer, head) pair in the
 // unstructured variant.  With a per-row floor f the first f ranks of every row
 // are kept unconditionally and stay out of the histograms; the budget that is
@@ -55,18 +63,9 @@ __device__ __forceinline__ void digit_of(int pass, uint32_t key, uint32_t* digit
   else { *digit = key & 1023u; *hi = key >> 10; }
 }
 
-// budget.b[] already excludes the floor entries
-__global__ void select_init(uint32_t* hist, int count, SelState* state, BudgetTable budget,
-                            SeqTable seq, int rows, int floor_rank) {
+__global__ void select_clear(uint32_t* words, int count) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) hist[i] = 0;
-  if (i < seq.batch) {
-    const int n = seq.cu[i + 1] - seq.cu[i];
-    state[i].prefix = 0;
-    state[i].bad = 0;
-    state[i].remaining = (uint64_t)budget.b[i];
-    state[i].expect = (uint64_t)rows * (uint64_t)max(n - floor_rank, 0);   // entries that compete
-  }
+  if (i < count) words[i] = 0;
 }
 
 __device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
@@ -143,11 +142,15 @@ __device__ __forceinline__ uint64_t block_scan_incl(uint64_t v, uint64_t* total)
 // One workgroup: picks the digit whose bucket holds the wanted rank, walking from
 // the largest digit down.  Thread t owns bins [bins - (t+1)*per, bins - t*per) in
 // descending order; a prefix sum over the threads names the owner of the rank.
+// The first pass looks for rank `budget` among `pool` entries, the others go on from state[b]
+// (all zero before the first pass).  *found (LDS): the threshold bits fixed so far.
 __device__ __forceinline__ void find_digit(int pass, int b, const uint32_t* __restrict__ hist,
-                                           SelState* state) {
-  const uint64_t want = state[b].remaining;    // uniform
+                                           SelState* state, uint64_t budget, uint64_t pool,
+                                           uint32_t* found) {
+  const uint64_t want = pass == 0 ? budget : state[b].remaining;    // uniform
   if (want == 0) return;                       // budget 0: nothing to find
-  const uint64_t expect = state[b].expect;     // uniform; read before anyone updates it
+  const uint64_t expect = pass == 0 ? pool : state[b].expect;       // uniform; read before anyone updates it
+  const uint32_t prefix = state[b].prefix;
   const uint32_t* gh = hist + ((size_t)b * 3 + pass) * SEL_BINS;
   const int bins = pass == 2 ? 1024 : SEL_BINS;
   const int per = bins / SEL_THREADS;          // 8 or 4 bins per thread
@@ -177,78 +180,41 @@ __device__ __forceinline__ void find_digit(int pass, int b, const uint32_t* __re
       }
     }
     const uint32_t shift = pass == 0 ? 21u : (pass == 1 ? 10u : 0u);
-    state[b].prefix |= digit << shift;
+    state[b].prefix = prefix | digit << shift;
     state[b].remaining = want - run;           // rank inside the chosen bucket
     state[b].expect = population;              // what the next pass must count
+    *found = prefix | digit << shift;
   }
 }
 
-// grid: (token blocks, layers, batch)
-__global__ __launch_bounds__(SEL_THREADS) void select_hist(
-    const float* __restrict__ I, SeqTable seq, int total, int pass, int floor_rank, int per_block,
-    SelState* state, uint32_t* __restrict__ hist /* [batch][3][SEL_BINS] */,
-    uint32_t* __restrict__ tickets) {
-  __shared__ uint32_t lh[SEL_BINS];
-  const int b = blockIdx.z;
-  const int tok0 = seq.cu[b], n = seq.cu[b + 1] - tok0;
-  const int begin = max((int)blockIdx.x * per_block, floor_rank);   // ranks below the floor do not compete
-  const bool active = begin < n && begin < (int)(blockIdx.x + 1) * per_block;   // uniform in the workgroup
-  if (active) {
-    const int end = min(n, (int)(blockIdx.x + 1) * per_block);
-    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) lh[i] = 0;
-    __syncthreads();
-    const uint32_t want_hi = pass == 0 ? 0u : (pass == 1 ? state[b].prefix >> 21 : state[b].prefix >> 10);
-    const float* row = I + (size_t)blockIdx.y * total + tok0;
-    // Four loads in flight per thread.  Rows are usually sorted, so the 64 elements of
-    // a wave step mostly share one digit: then one lane adds the whole count instead
-    // of 64 atomics on one address.
-    const int lane = threadIdx.x & 63;
-    for (int i0 = begin; i0 < end; i0 += SEL_THREADS * 4) {
-      float x[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = i0 + e * SEL_THREADS + (int)threadIdx.x;
-        x[e] = row[i < end ? i : end - 1];              // clamped; dropped below
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = i0 + e * SEL_THREADS + (int)threadIdx.x;
-        uint32_t digit, hi;
-        digit_of(pass, float_to_ordered(x[e]), &digit, &hi);
-        const bool ok = i < end && hi == want_hi;
-        const uint64_t all = __ballot(ok);
-        if (all == 0) continue;                          // wave-uniform
-        const int leader = __ffsll((unsigned long long)all) - 1;
-        const uint32_t d0 = __builtin_amdgcn_readlane(digit, leader);
-        const uint64_t same = __ballot(ok && digit == d0);
-        if (same == all) {
-          if (lane == leader) atomicAdd(&lh[d0], (uint32_t)__popcll(all));
-        } else if (ok) {
-          atomicAdd(&lh[digit], 1u);
-        }
-      }
-    }
-    __syncthreads();
-    uint32_t* gh = hist + ((size_t)b * 3 + pass) * SEL_BINS;
-    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS)
-      if (lh[i]) atomicAdd(&gh[i], lh[i]);
+// Adds an element's digit to the workgroup's histogram.  Rows are usually sorted, so the 64
+// elements of a wave step mostly share one digit: then one lane adds the whole count instead
+// of 64 atomics on one address.
+__device__ __forceinline__ void hist_add(uint32_t* lh, bool ok, uint32_t digit) {
+  const uint64_t all = __ballot(ok);
+  if (all == 0) return;                                // wave-uniform
+  const int leader = __ffsll((unsigned long long)all) - 1;
+  const uint32_t d0 = __builtin_amdgcn_readlane(digit, leader);
+  const uint64_t same = __ballot(ok && digit == d0);
+  if (same == all) {
+    if ((int)(threadIdx.x & 63) == leader) atomicAdd(&lh[d0], (uint32_t)__popcll(all));
+  } else if (ok) {
+    atomicAdd(&lh[digit], 1u);
   }
-  // every workgroup of the sequence takes a ticket, the idle ones included
-  if (last_workgroup(tickets, pass, seq.batch, b))
-    find_digit(pass, b, hist, state);
 }
 
 // Lengths and offsets of sequence b from its per-row counts, by one workgroup.
 // The retained total of a sequence is its budget (known on the host), so the first
 // offset of every sequence comes from the table.  Ties at the threshold go to the
 // rows in ascending order until the budget is met: row l takes
-// min(eq_l, max(0, ties - sum of eq over the rows before it)).  AGENT: counts are
-// read with device-scope loads (inside the kernel that accumulated them).
-template <bool AGENT>
+// min(eq_l, max(0, ties - sum of eq over the rows before it)).  count_at(l, i): entries of row l
+// above (i = 0) and equal to (i = 1) the threshold, whose key is tau_key.
+template <typename COUNT>
 __device__ __forceinline__ void finalize_sequence(int b, const SeqTable& seq, int layers,
                                                   int floor_rank, const BudgetTable& budget,
-                                                  const SelState* state, const uint32_t* counts,
-                                                  float* tau, int32_t* lengths, int64_t* offsets) {
+                                                  uint32_t tau_key, const SelState* state,
+                                                  const COUNT& count_at, float* tau,
+                                                  int32_t* lengths, int64_t* offsets) {
   int64_t off = 0;       // rows retained by the sequences before mine
   for (int p = 0; p < b; ++p) {
     const int n_p = seq.cu[p + 1] - seq.cu[p];
@@ -261,13 +227,12 @@ __device__ __forceinline__ void finalize_sequence(int b, const SeqTable& seq, in
   if (tau && t == 0) {
     // stored through the integer image: the library is compiled under the assumption
     // that no NaN occurs, which a floating-point select of a NaN need not survive
-    const uint32_t bits = want > 0 ? __float_as_uint(ordered_to_float(state[b].prefix)) : 0x7f800000u;
+    const uint32_t bits = want > 0 ? __float_as_uint(ordered_to_float(tau_key)) : 0x7f800000u;
     reinterpret_cast<uint32_t*>(tau)[b] = state[b].bad ? 0x7fc00000u : bits;
   }
-  auto count_at = [&](size_t i) -> uint64_t { return AGENT ? load_agent(&counts[i]) : counts[i]; };
   uint64_t above_mine = 0;
   if (want > 0)
-    for (int l = t; l < layers; l += SEL_THREADS) above_mine += count_at(((size_t)b * layers + l) * 2);
+    for (int l = t; l < layers; l += SEL_THREADS) above_mine += count_at(l, 0);
   uint64_t above;
   block_scan_incl(above_mine, &above);
   const int64_t ties = want - (int64_t)above;
@@ -277,8 +242,8 @@ __device__ __forceinline__ void finalize_sequence(int b, const SeqTable& seq, in
     const bool live = l < layers;
     uint64_t gt = 0, eq = 0;
     if (live && want > 0) {
-      gt = count_at(((size_t)b * layers + l) * 2);
-      eq = count_at(((size_t)b * layers + l) * 2 + 1);
+      gt = count_at(l, 0);
+      eq = count_at(l, 1);
     }
     uint64_t eq_chunk, len_chunk;
     const uint64_t eq_excl = eq_before + block_scan_incl(eq, &eq_chunk) - eq;
@@ -294,6 +259,165 @@ __device__ __forceinline__ void finalize_sequence(int b, const SeqTable& seq, in
     len_before += len_chunk;
   }
   if (b == seq.batch - 1 && t == 0) offsets[seq.batch * layers] = off + (int64_t)len_before;
+}
+
+// Entries [first, n) of a descending row that lie above (x) and at (y) the threshold: both
+// borders are searched by the `lanes` (a power of two) adjacent lanes of a group together, each
+// step cutting the stretch by lanes + 1.  Every lane of the group gets the result.
+__device__ __forceinline__ uint2 count_sorted(const float* row, int first, int n, uint32_t tau_key,
+                                              int lanes, bool live) {
+  const int lane = threadIdx.x & 63, j = lane & (lanes - 1);
+  const uint64_t group = (lanes == 64 ? ~0ull : (1ull << lanes) - 1) << (lane - j);
+  int lo[2], hi[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) { lo[s] = live ? first : 0; hi[s] = live ? n : 0; }
+  while (__any(lo[0] < hi[0] || lo[1] < hi[1])) {
+    int probe[2];
+    float x[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      // (inside [lo, hi) for every lane while the stretch is not empty)
+      probe[s] = lo[s] + (int)((uint64_t)(uint32_t)(hi[s] - lo[s]) * (j + 1) / (lanes + 1));
+      x[s] = lo[s] < hi[s] ? row[probe[s]] : 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const uint32_t key = float_to_ordered(x[s]);
+      const bool before = lo[s] < hi[s] && (s == 0 ? key > tau_key : key >= tau_key);
+      const int c = __popcll(__ballot(before) & group);    // probes before the border
+      const int below = __shfl(probe[s], (lane - j) + max(c - 1, 0));
+      const int above = __shfl(probe[s], (lane - j) + min(c, lanes - 1));
+      if (lo[s] < hi[s]) {
+        if (c < lanes) hi[s] = above;
+        if (c > 0) lo[s] = below + 1;
+      }
+    }
+  }
+  return make_uint2(lo[0] - first, lo[1] - lo[0]);
+}
+
+// grid: (token blocks, rows, batch).  SORTED (last pass, at most SEL_THREADS rows): every row is
+// descending, and the last workgroup of a sequence finds its counts, lengths and offsets.
+template <bool SORTED>
+__global__ __launch_bounds__(SEL_THREADS) void select_hist(
+    const float* __restrict__ I, SeqTable seq, int total, int rows, int pass, int floor_rank,
+    int per_block, BudgetTable budget, SelState* state,
+    uint32_t* __restrict__ hist /* [batch][3][SEL_BINS] */, uint32_t* __restrict__ tickets,
+    float* tau, int32_t* lengths, int64_t* offsets) {
+  __shared__ __attribute__((aligned(8))) uint32_t lh[SEL_BINS];
+  __shared__ uint32_t found;
+  const int b = blockIdx.z;
+  const int tok0 = seq.cu[b], n = seq.cu[b + 1] - tok0;
+  const int begin = max((int)blockIdx.x * per_block, floor_rank);   // ranks below the floor do not compete
+  const bool active = begin < n && begin < (int)(blockIdx.x + 1) * per_block;   // uniform in the workgroup
+  if (active) {
+    const int end = min(n, (int)(blockIdx.x + 1) * per_block);
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) lh[i] = 0;
+    __syncthreads();
+    const uint32_t want_hi = pass == 0 ? 0u : (pass == 1 ? state[b].prefix >> 21 : state[b].prefix >> 10);
+    const float* row = I + (size_t)blockIdx.y * total + tok0;
+    for (int i0 = begin; i0 < end; i0 += SEL_THREADS * 4) {   // four loads in flight per thread
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + e * SEL_THREADS + (int)threadIdx.x;
+        x[e] = row[i < end ? i : end - 1];              // clamped; dropped below
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + e * SEL_THREADS + (int)threadIdx.x;
+        uint32_t digit, hi;
+        digit_of(pass, float_to_ordered(x[e]), &digit, &hi);
+        hist_add(lh, i < end && hi == want_hi, digit);
+      }
+    }
+    __syncthreads();
+    uint32_t* gh = hist + ((size_t)b * 3 + pass) * SEL_BINS;
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS)
+      if (lh[i]) atomicAdd(&gh[i], lh[i]);
+  }
+  // every workgroup of the sequence takes a ticket, the idle ones included
+  if (!last_workgroup(tickets, pass, seq.batch, b)) return;
+  find_digit(pass, b, hist, state, (uint64_t)budget.b[b], (uint64_t)rows * (uint64_t)max(n - floor_rank, 0), &found);
+  if (!SORTED) return;
+  __syncthreads();                                       // found
+  const uint32_t tau_key = budget.b[b] > 0 ? found : 0u;
+  uint2* rc = reinterpret_cast<uint2*>(lh);              // counts of a row (the histogram is flushed)
+  int lanes = 64;
+  while (lanes * rows > SEL_THREADS) lanes /= 2;         // at least 1: rows <= SEL_THREADS
+  const int r = (int)threadIdx.x / lanes;
+  if (budget.b[b] > 0) {                                 // uniform
+    const uint2 c = count_sorted(I + (size_t)min(r, rows - 1) * total + tok0, min(floor_rank, n), n,
+                                 tau_key, lanes, r < rows);
+    if (r < rows && ((int)threadIdx.x & (lanes - 1)) == 0) rc[r] = c;
+  }
+  __syncthreads();
+  finalize_sequence(b, seq, rows, floor_rank, budget, tau_key, state,
+                    [&](int l, int i) -> uint64_t { return i ? rc[l].y : rc[l].x; }, tau, lengths, offsets);
+}
+
+// The composite (mean or maximum over the heads of the rank-aligned scores) and the first
+// histogram pass over it.  grid: (rank blocks, layers, batch); HKV heads (0: not known at compile
+// time), VEC consecutive ranks per thread, all loads of a thread in flight together; the
+// heads are joined in ascending order as in kvc_composite.
+template <int HKV, int VEC>
+__global__ __launch_bounds__(SEL_THREADS) void composite_hist(
+    const float* __restrict__ sorted, SeqTable seq, int hkv_arg, int total, int head_max,
+    int floor_rank, int per_block, BudgetTable budget, float* __restrict__ I, SelState* state,
+    uint32_t* __restrict__ hist, uint32_t* __restrict__ tickets) {
+  typedef float vec_t __attribute__((ext_vector_type(VEC)));
+  __shared__ uint32_t lh[SEL_BINS];
+  __shared__ uint32_t found;
+  const int hkv = HKV ? HKV : hkv_arg;
+  const int b = blockIdx.z, l = blockIdx.y;
+  const int tok0 = seq.cu[b], n = seq.cu[b + 1] - tok0;
+  const int begin = (int)blockIdx.x * per_block;
+  if (begin < n) {                                       // uniform in the workgroup
+    const int end = min(n, begin + per_block);
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) lh[i] = 0;
+    __syncthreads();
+    const float* p0 = sorted + (size_t)l * hkv * total + tok0;
+    float* out = I + (size_t)l * total + tok0;
+    for (int i0 = begin; i0 < end; i0 += SEL_THREADS * VEC) {
+      const int i = i0 + (int)threadIdx.x * VEC;
+      const bool live = i < end;                         // VEC > 1: n is a multiple of VEC (host-checked)
+      const float* p = p0 + (live ? i : begin);
+      vec_t acc;
+      if constexpr (HKV > 0) {
+        vec_t x[HKV];
+#pragma unroll
+        for (int h = 0; h < HKV; ++h) x[h] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(p + (size_t)h * total));
+        acc = x[0];
+#pragma unroll
+        for (int h = 1; h < HKV; ++h) {
+          if (head_max) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[j] = fmaxf(acc[j], x[h][j]);
+          } else {
+            acc += x[h];
+          }
+        }
+      } else {
+        static_assert(HKV > 0 || VEC == 1, "the general form takes one rank per thread");
+        acc[0] = p[0];
+        for (int h = 1; h < hkv; ++h) {
+          const float x = p[(size_t)h * total];
+          acc[0] = head_max ? fmaxf(acc[0], x) : acc[0] + x;
+        }
+      }
+      if (!head_max) acc = acc / float(hkv);
+      if (live) *reinterpret_cast<vec_t*>(out + i) = acc;
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) hist_add(lh, live && i + j >= floor_rank, float_to_ordered(acc[j]) >> 21);
+    }
+    __syncthreads();
+    uint32_t* gh = hist + (size_t)b * 3 * SEL_BINS;
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS)
+      if (lh[i]) atomicAdd(&gh[i], lh[i]);
+  }
+  if (last_workgroup(tickets, 0, seq.batch, b))
+    find_digit(0, b, hist, state, (uint64_t)budget.b[b],
+               (uint64_t)gridDim.y * (uint64_t)max(n - floor_rank, 0), &found);
 }
 
 // grid: (token blocks, layers, batch): counts[b][l] = {#(I > tau), #(I == tau)}; the
@@ -326,7 +450,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_count(
       atomicAdd(&counts[((size_t)b * layers + blockIdx.y) * 2 + threadIdx.x], sh[threadIdx.x]);
   }
   if (last_workgroup(tickets, 3, seq.batch, b))
-    finalize_sequence<true>(b, seq, layers, floor_rank, budget, state, counts, tau, lengths, offsets);
+    finalize_sequence(b, seq, layers, floor_rank, budget, state[b].prefix, state,
+                      [&](int l, int i) -> uint64_t { return load_agent(&counts[((size_t)b * layers + l) * 2 + i]); },
+                      tau, lengths, offsets);
 }
 
 // Batches whose sequences are all empty launch nothing else.  grid: (batch)
@@ -334,7 +460,10 @@ __global__ __launch_bounds__(SEL_THREADS) void select_finalize(
     SeqTable seq, int layers, int floor_rank, BudgetTable budget,
     const SelState* __restrict__ state, const uint32_t* __restrict__ counts, float* tau,
     int32_t* lengths, int64_t* offsets) {
-  finalize_sequence<false>(blockIdx.x, seq, layers, floor_rank, budget, state, counts, tau, lengths, offsets);
+  const int b = blockIdx.x;
+  finalize_sequence(b, seq, layers, floor_rank, budget, state[b].prefix, state,
+                    [&](int l, int i) -> uint64_t { return counts[((size_t)b * layers + l) * 2 + i]; },
+                    tau, lengths, offsets);
 }
 
 // Elements of a row per workgroup: every workgroup clears and flushes a 2048-bin
@@ -361,8 +490,8 @@ SelectLayout select_layout(const Problem& pb) {
   const size_t sel_blocks = size_t((pb.max_seqlen + SEL_PER_BLOCK - 1) / SEL_PER_BLOCK) * pb.sel_rows;
   const size_t sel_groups = (sel_blocks + SEL_GROUP - 1) / SEL_GROUP;
   L.off_tickets = cur; cur += align_up(4 * size_t(pb.batch) * (sel_groups + 1) * SEL_TICKET_WORDS * 4);
-  L.words = int((cur) / 4);                   // hist, counts and tickets are zeroed together
   L.off_state = cur;  cur += align_up(size_t(pb.batch) * sizeof(SelState));
+  L.words = int(cur / 4);                     // all of it starts from zero
   L.total = cur;
   return L;
 }
@@ -370,6 +499,7 @@ SelectLayout select_layout(const Problem& pb) {
 }  // namespace
 
 size_t select_workspace_bytes(const Problem& pb) { return select_layout(pb).total; }
+int select_clear_words(const Problem& pb) { return select_layout(pb).words; }
 
 // Device address of this GPU's copy of `scratch` (looked up on the first call on
 // each device, with that device current).
@@ -396,36 +526,86 @@ kvc_status select_static_scratch(void** ptr) {
   return KVC_OK;
 }
 
+// What is left to compete for after the floor entries.
+static BudgetTable open_budgets(const Problem& pb, const int64_t* budget) {
+  BudgetTable bt{};
+  for (int b = 0; b < pb.batch; ++b) {
+    const int64_t n_b = pb.seq.cu[b + 1] - pb.seq.cu[b];
+    bt.b[b] = budget[b] - int64_t(pb.sel_rows) * (pb.min_per_layer < n_b ? pb.min_per_layer : n_b);
+  }
+  return bt;
+}
+
+// Passes [first_pass, 3) and the counts, on cleared scratch.
+static kvc_status select_passes(const Problem& pb, const float* I, const BudgetTable& bt, int first_pass,
+                                bool sorted, float* tau, int32_t* lengths, int64_t* offsets, char* w,
+                                hipStream_t stream) {
+  const SelectLayout L = select_layout(pb);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(w + L.off_hist);
+  uint32_t* counts = reinterpret_cast<uint32_t*>(w + L.off_counts);
+  uint32_t* tickets = reinterpret_cast<uint32_t*>(w + L.off_tickets);
+  SelState* state = reinterpret_cast<SelState*>(w + L.off_state);
+  const int total = int(pb.total), rows = pb.sel_rows, floor_rank = pb.min_per_layer;
+  const int per_block = select_per_block(pb);
+  dim3 grid((unsigned)((pb.max_seqlen + per_block - 1) / per_block), rows, pb.batch);
+  // more rows than threads (unstructured pools) keep the counting sweep: one workgroup
+  // searching them one row per thread and round would take longer than the sweep's launch
+  const bool search = sorted && rows <= SEL_THREADS;
+  for (int pass = first_pass; pass < 3; ++pass) {
+    if (pass == 2 && search)
+      KVC_LAUNCH("select_hist", stream, select_hist<true><<<grid, SEL_THREADS, 0, stream>>>(
+          I, pb.seq, total, rows, pass, floor_rank, per_block, bt, state, hist, tickets, tau, lengths, offsets));
+    else
+      KVC_LAUNCH("select_hist", stream, select_hist<false><<<grid, SEL_THREADS, 0, stream>>>(
+          I, pb.seq, total, rows, pass, floor_rank, per_block, bt, state, hist, tickets, tau, lengths, offsets));
+  }
+  if (!search)
+    KVC_LAUNCH("select_count", stream, select_count<<<grid, SEL_THREADS, 0, stream>>>(
+        I, pb.seq, total, rows, floor_rank, per_block, bt, state, counts, tickets, tau, lengths, offsets));
+  return KVC_OK;
+}
+
 kvc_status launch_global_select(const Problem& pb, const float* I, const int64_t* budget,
                                 float* tau, int32_t* lengths, int64_t* offsets, void* ws,
                                 hipStream_t stream) {
   const SelectLayout L = select_layout(pb);
   char* w = static_cast<char*>(ws);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(w + L.off_hist);
-  uint32_t* counts = reinterpret_cast<uint32_t*>(w + L.off_counts);
-  uint32_t* tickets = reinterpret_cast<uint32_t*>(w + L.off_tickets);
-  SelState* state = reinterpret_cast<SelState*>(w + L.off_state);
-  const int rows = pb.sel_rows, floor_rank = pb.min_per_layer;
-  BudgetTable bt{};   // what is left to compete for after the floor entries
-  for (int b = 0; b < pb.batch; ++b) {
-    const int64_t n_b = pb.seq.cu[b + 1] - pb.seq.cu[b];
-    bt.b[b] = budget[b] - int64_t(rows) * (floor_rank < n_b ? floor_rank : n_b);
-  }
-  const int total = int(pb.total);
-
-  KVC_LAUNCH("select_init", stream, select_init<<<(L.words + 255) / 256, 256, 0, stream>>>(hist, L.words, state, bt, pb.seq, rows, floor_rank));
-  if (pb.max_seqlen > 0) {
-    const int per_block = select_per_block(pb);
-    dim3 grid((unsigned)((pb.max_seqlen + per_block - 1) / per_block), rows, pb.batch);
-    for (int pass = 0; pass < 3; ++pass)
-      KVC_LAUNCH("select_hist", stream, select_hist<<<grid, SEL_THREADS, 0, stream>>>(I, pb.seq, total, pass, floor_rank, per_block, state, hist, tickets));
-    KVC_LAUNCH("select_count", stream, select_count<<<grid, SEL_THREADS, 0, stream>>>(I, pb.seq, total, rows, floor_rank, per_block, bt, state, counts,
-                                                                                     tickets, tau, lengths, offsets));
-  } else {
-    KVC_LAUNCH("select_finalize", stream, select_finalize<<<pb.batch, SEL_THREADS, 0, stream>>>(pb.seq, rows, floor_rank, bt, state, counts, tau,
-                                          lengths, offsets));
-  }
+  const BudgetTable bt = open_budgets(pb, budget);
+  KVC_LAUNCH("select_clear", stream, select_clear<<<(L.words + 255) / 256, 256, 0, stream>>>(
+      reinterpret_cast<uint32_t*>(w), L.words));
+  if (pb.max_seqlen > 0) return select_passes(pb, I, bt, 0, false, tau, lengths, offsets, w, stream);
+  KVC_LAUNCH("select_finalize", stream, select_finalize<<<pb.batch, SEL_THREADS, 0, stream>>>(
+      pb.seq, pb.sel_rows, pb.min_per_layer, bt, reinterpret_cast<SelState*>(w + L.off_state),
+      reinterpret_cast<uint32_t*>(w + L.off_counts), tau, lengths, offsets));
   return KVC_OK;
+}
+
+kvc_status launch_composite_select(const Problem& pb, const float* S_sorted, float* I,
+                                   const int64_t* budget, float* tau, int32_t* lengths,
+                                   int64_t* offsets, void* ws, hipStream_t stream) {
+  const SelectLayout L = select_layout(pb);
+  char* w = static_cast<char*>(ws);
+  const BudgetTable bt = open_budgets(pb, budget);
+  if (pb.unstructured)   // the pool is the rank-aligned per-head scores themselves
+    return select_passes(pb, S_sorted, bt, 0, true, tau, lengths, offsets, w, stream);
+  const int total = int(pb.total), head_max = pb.agg_head == KVC_AGG_MAX;
+  const int per_block = select_per_block(pb);
+  dim3 grid((unsigned)((pb.max_seqlen + per_block - 1) / per_block), pb.layers, pb.batch);
+  // four ranks per thread need 16-byte aligned sequences in every layer
+  bool vec4 = (reinterpret_cast<uintptr_t>(S_sorted) | reinterpret_cast<uintptr_t>(I)) % 16 == 0;
+  for (int b = 0; b <= pb.batch; ++b) vec4 = vec4 && pb.seq.cu[b] % 4 == 0;
+#define KVC_COMPOSITE_HIST(HKV, VEC)                                                              \
+  KVC_LAUNCH("composite_hist", stream, composite_hist<HKV, VEC><<<grid, SEL_THREADS, 0, stream>>>( \
+      S_sorted, pb.seq, pb.hkv, total, head_max, pb.min_per_layer, per_block, bt, I,               \
+      reinterpret_cast<SelState*>(w + L.off_state), reinterpret_cast<uint32_t*>(w + L.off_hist),   \
+      reinterpret_cast<uint32_t*>(w + L.off_tickets)))
+  if (pb.hkv == 8 && vec4) KVC_COMPOSITE_HIST(8, 4);
+  else if (pb.hkv == 8) KVC_COMPOSITE_HIST(8, 1);
+  else if (pb.hkv == 4 && vec4) KVC_COMPOSITE_HIST(4, 4);
+  else if (pb.hkv == 4) KVC_COMPOSITE_HIST(4, 1);
+  else KVC_COMPOSITE_HIST(0, 1);
+#undef KVC_COMPOSITE_HIST
+  return select_passes(pb, I, bt, 1, true, tau, lengths, offsets, w, stream);
 }
 
 }  // namespace kvc
