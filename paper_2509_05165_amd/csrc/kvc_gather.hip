@@ -22,7 +22,12 @@ namespace kvc {
 namespace {
 
 constexpr int GA_THREADS = 256;
-constexpr int GA_BATCH = 2;   // row groups in flight per lane (measured: 2 beats 1, 3, 4 and 8)
+// Large pools: 64 rows per wave, two wave instructions of loads in flight per lane (measured: 2
+// beats 1, 3, 4 and 8).  A pool that would leave the chip with few waves is a chain of
+// latencies instead: it gets fewer rows per wave and all of them in flight.
+// (99k rows of 256 bytes, 102 MB moved: 33 us with 64 rows per wave, 27 with 32, 24 with 16, 26
+// with 8; 524k rows: 105 us with 64 and 32, 108 with 16.)
+constexpr int GA_WAVES = 4096;   // waves that a launch should have (16 per compute unit)
 
 // Every byte the gather moves is touched once, so loads and stores carry the
 // streaming (non-temporal) hint: measured 0.70 -> 0.63 ms at the 128k shape,
@@ -31,17 +36,35 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x4 load_stream(const u32x4* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void store_stream(u32x4* p, u32x4 v) { __builtin_nontemporal_store(v, p); }
 
-// Each wave takes 64 consecutive rows of the output pool.  Lane i first resolves
-// pool row (group*64 + i): which (sequence, layer) block it lies in (binary
-// search in `offsets`), its head and rank inside the block, and from `idx` the
-// address of the source row.  Then the wave copies the rows a few at a time:
-// `pieces` adjacent lanes move one row as 16-byte pieces, the source address
-// comes from the owning lane by a cross-lane read.
+// Block of the pool that `row` lies in: lo with start(lo) <= row < start(lo + 1), where
+// start(i) = offsets[i] * hpb.  `row` is the same in all lanes; the wave probes 64 borders at a
+// time, so up to 64 blocks take one load and up to 4096 two.
+__device__ __forceinline__ int find_block(const int64_t* __restrict__ offsets, int hpb, int nblk, int64_t row) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = nblk;                            // invariant: start(lo) <= row < start(hi)
+  while (hi - lo > 1) {                             // wave-uniform
+    const int span = hi - lo, step = (span + 63) / 64;
+    const int mid = lo + lane * step;               // lane 0 probes lo itself: true
+    const bool at_or_before = mid < hi && offsets[mid] * hpb <= row;
+    const int last = 63 - __clzll((long long)(__ballot(at_or_before) | 1ull));
+    lo += last * step;
+    hi = min(lo + step, hi);
+  }
+  return lo;
+}
+
+// Each wave takes wave_rows (a power of two, at most 64) consecutive rows of the output pool.
+// Lane i first resolves pool row (group*wave_rows + i): which (sequence, layer) block it lies in
+// (a search of `offsets` for the first and the last row, and between these two if they
+// differ), its head and rank inside the block, and from `idx` the address of the source row.
+// Then the wave copies the rows a few at a time: `pieces` adjacent lanes move one row as 16-byte
+// pieces, the source address comes from the owning lane by a cross-lane read.
 // heads_per_block = Hkv (block = layer) or 1 (block = one head of a layer)
+template <int GA_BATCH>
 __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
     PtrTable k_tab, PtrTable v_tab, int has_v, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ lengths, const int64_t* __restrict__ offsets, SeqTable seq,
-    int layers, int hkv, int heads_per_block, int total, int pieces, int64_t pool_rows,
+    int layers, int hkv, int heads_per_block, int total, int pieces, int wave_rows, int64_t pool_rows,
     uint4* __restrict__ k_out, uint4* __restrict__ v_out) {
   const int lane = threadIdx.x & 63;
   const int64_t wave_id = (int64_t)blockIdx.x * (GA_THREADS / 64) + (threadIdx.x >> 6);
@@ -52,14 +75,18 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
   const int rows_per_step = 64 / pieces;            // rows copied by one wave instruction
   const int sub = lane / pieces, piece = lane - sub * pieces;
   const bool mover = sub < rows_per_step;
-  const int steps = (64 + rows_per_step - 1) / rows_per_step;
+  const int steps = (wave_rows + rows_per_step - 1) / rows_per_step;
 
-  for (int64_t group = wave_id; group * 64 < pool_rows; group += wave_count) {
+  for (int64_t group = wave_id; group * wave_rows < pool_rows; group += wave_count) {
     // ---- resolve my row ----
-    const int64_t row = group * 64 + lane;
+    const int64_t row = group * wave_rows + lane;
     uint64_t ksrc = 0, vsrc = 0;                    // 0 = nothing to copy
-    if (row < pool_rows) {
-      int lo = 0, hi = nblk;   // invariant: offsets[lo]*hpb <= row < offsets[hi]*hpb
+    const int64_t last_row = min(group * wave_rows + wave_rows, pool_rows) - 1;
+    const int first_blk = find_block(offsets, hpb, nblk, group * wave_rows);
+    const int end_blk = offsets[first_blk + 1] * hpb > last_row ? first_blk + 1
+                                                                : find_block(offsets, hpb, nblk, last_row) + 1;
+    if (lane < wave_rows && row < pool_rows) {
+      int lo = first_blk, hi = end_blk;   // invariant: offsets[lo]*hpb <= row < offsets[hi]*hpb
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (offsets[mid] * hpb <= row) lo = mid; else hi = mid;
@@ -82,16 +109,16 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
         }
       }
     }
-    // ---- copy the 64 rows, GA_BATCH wave instructions of loads in flight ----
+    // ---- copy the rows, GA_BATCH wave instructions of loads in flight ----
     for (int s0 = 0; s0 < steps; s0 += GA_BATCH) {
       u32x4 kd[GA_BATCH], vd[GA_BATCH];
       uint64_t kp[GA_BATCH], vp[GA_BATCH];
 #pragma unroll
       for (int j = 0; j < GA_BATCH; ++j) {
-        const int r = min((s0 + j) * rows_per_step + sub, 63);   // owning lane
+        const int r = min((s0 + j) * rows_per_step + sub, wave_rows - 1);   // owning lane
         const uint32_t klo = __shfl((uint32_t)ksrc, r), khi = __shfl((uint32_t)(ksrc >> 32), r);
         kp[j] = ((uint64_t)khi << 32) | klo;
-        if (!mover || (s0 + j) * rows_per_step + sub > 63) kp[j] = 0;
+        if (!mover || (s0 + j) * rows_per_step + sub >= wave_rows) kp[j] = 0;
         if (has_v) {
           const uint32_t vlo = __shfl((uint32_t)vsrc, r), vhi = __shfl((uint32_t)(vsrc >> 32), r);
           vp[j] = kp[j] ? (((uint64_t)vhi << 32) | vlo) : 0;
@@ -106,7 +133,7 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
       }
 #pragma unroll
       for (int j = 0; j < GA_BATCH; ++j) {
-        const int64_t orow = group * 64 + (s0 + j) * rows_per_step + sub;
+        const int64_t orow = group * wave_rows + (s0 + j) * rows_per_step + sub;
         if (kp[j]) store_stream(reinterpret_cast<u32x4*>(k_out) + ((size_t)orow * pieces + piece), kd[j]);
         if (vp[j]) store_stream(reinterpret_cast<u32x4*>(v_out) + ((size_t)orow * pieces + piece), vd[j]);
       }
@@ -248,13 +275,19 @@ kvc_status launch_gather(const Problem& pb, const void* const* k, const void* co
     }
     idx = sel;
   }
-  const int64_t groups = (pool_rows + 63) / 64;                  // one wave per 64 pool rows
+  int wave_rows = 64;
+  while (wave_rows > 16 && pool_rows < int64_t(GA_WAVES) * wave_rows) wave_rows /= 2;
+  const int64_t groups = (pool_rows + wave_rows - 1) / wave_rows;
   int64_t blocks = (groups + GA_THREADS / 64 - 1) / (GA_THREADS / 64);
   const int64_t cap = 256 * 32;
   if (blocks > cap) blocks = cap;
-  KVC_LAUNCH("gather_kernel", stream, gather_kernel<<<(unsigned)blocks, GA_THREADS, 0, stream>>>(
-      kt, vt, v != nullptr, idx, lengths, offsets, pb.seq, pb.layers, pb.hkv, hpb, int(pb.total),
-      pieces, pool_rows, static_cast<uint4*>(k_out), static_cast<uint4*>(v_out)));
+#define KVC_GATHER(BATCH)                                                                            \
+  KVC_LAUNCH("gather_kernel", stream, gather_kernel<BATCH><<<(unsigned)blocks, GA_THREADS, 0, stream>>>( \
+      kt, vt, v != nullptr, idx, lengths, offsets, pb.seq, pb.layers, pb.hkv, hpb, int(pb.total),    \
+      pieces, wave_rows, pool_rows, static_cast<uint4*>(k_out), static_cast<uint4*>(v_out)))
+  if (wave_rows < 64) KVC_GATHER(4);
+  else KVC_GATHER(2);
+#undef KVC_GATHER
   return KVC_OK;
 }
 
