@@ -64,8 +64,15 @@ __device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
 // EMIT: queries on the rows, a lane owns one key.  In tile order every query head is
 // padded to a multiple of 8 rows, so each group of four accumulator registers (8 rows) belongs to
 // one head; the padding rows carry lse = +1e30 and contribute nothing.
+//
+// What bounds it is latency inside a wave (fragment reads, products, the vector work on their
+// result, one after the other), so the waves per SIMD decide: registers are held to what four
+// waves (rows of up to 160 bytes), three (256) or two (512) leave.  At 200 task tokens, 32
+// heads of 128 and 8192 tokens x 32 layers the emit pass took 722 us with two waves and 650 with
+// three.  A form with two accumulator sets and prefetched fragments, one wave less, was 5 %
+// faster there than this one with two waves, and 27 % slower at heads of 64.
 template <typename T, int KS, int KB, bool EMIT, bool TASK_MAX>
-__global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : 2) void score_tile(
+__global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 : 4) void score_tile(
     PtrTable q_tab, PtrTable k_tab, SeqTable seq, TileArgs a, float* __restrict__ part_m,
     float* __restrict__ part_s, const float* __restrict__ lse2, float* __restrict__ out) {
   constexpr int PS = 2 * KS + 1;
