@@ -435,6 +435,14 @@ inline int mfma_chunk(const Problem& pb, int row_chunks) {
   const int64_t wgs = big_chunks * pb.hkv * row_chunks * pb.batch * pb.layers;
   return wgs >= 2048 ? MF_CHUNK_BIG : MF_CHUNK;
 }
+// The K loads carry the streaming hint (which keeps a pass's partial results in L2 instead) where a
+// launch reads each key once and its K is far beyond the 256 MB memory-side cache.  Where the
+// row chunks of a head share the reads, or the emit pass can still find what the
+// statistics pass read, plain loads are better.  Whole passes in us, plain / hint: row chunks
+// shared: 80 layers x 64k (four) 21250 / 22250, 16k per head (four) 4792 / 4856, ragged 4k (two)
+// 1684 / 1708; one row chunk: 51 MB of K 108 / 111, 268 MB 294 / 304; 4.7 GB 7424 / 7353, 8.6 GB
+// 5514 / 5470; 10.7 GB with the rest of the rows in a launch of its own 13834 / 13550.
+constexpr int64_t MF_STREAM_BYTES = int64_t(1) << 30;
 constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact emit launch (two per compute unit)
 
 struct ScoreLayout {
@@ -627,6 +635,8 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const bool split = L.row_chunks > 1 && rem_blocks > 0 && rem_blocks <= 4;
     const int main_chunks = split ? L.row_chunks - 1 : L.row_chunks;
     const unsigned gx = flat_chunks > 0 ? flat_chunks : 1;
+    const int64_t k_bytes = int64_t(pb.layers) * pb.hkv * total * MF_D * 2;
+    const bool stream_k = k_bytes > MF_STREAM_BYTES;
     // Max-pooling emit pass: a workgroup whose log-sum-exps are too far apart for the cheap
     // form puts itself on a list (one for the main launch, one for the remainder launch)
     // and a small list-driven launch right behind redoes the listed ones in the exact form.
@@ -639,7 +649,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
 #define KVC_SCORE_MFMA(NAME, EMIT, TMAX, WQ, RCS, RC0, PM, PS, LSE, OUT)                         \
   do {                                                                                           \
     const DeferList dl_ = (EMIT && TMAX) ? ((RC0) == 0 ? defer_main : defer_rem) : defer_none;   \
-    KVC_LAUNCH(NAME, stream, score_mfma<EMIT, TMAX, WQ><<<dim3(gx, pb.hkv * (RCS), pb.layers), MF_THREADS, 0, stream>>>( \
+    KVC_LAUNCH(NAME, stream, (stream_k && (RCS) == 1 ? score_mfma<EMIT, TMAX, WQ, true> : score_mfma<EMIT, TMAX, WQ, false>)<<<dim3(gx, pb.hkv * (RCS), pb.layers), MF_THREADS, 0, stream>>>( \
         qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,      \
         RCS, RC0, PM, PS, LSE, group_max, pb.causal_tail, OUT, dl_));                            \
     if (EMIT && TMAX)                                                                            \

@@ -174,11 +174,15 @@ __device__ __forceinline__ void emit_slice(int i, const f32x16& x0, const f32x16
 // wave writes LDS bytes [lds_base + 16 i, +16).  lds_base must be wave-uniform.  The load is
 // tracked by vmcnt only; the caller orders it with a wait and a barrier.  The s_nop is the wait
 // state that the hardware asks for between a scalar write of m0 and a load to LDS.
-// K is read once per pass and a layer's K exceeds every cache, so the loads carry
-// the streaming hint (keeps the partial results of the pass in L2 instead).
+// STREAM: with the streaming hint (the launcher says when).
+template <bool STREAM>
 __device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(voff), "s"(sbase)
-               : "memory");
+  if (STREAM)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(voff), "s"(sbase)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
+                 : "memory");
 }
 
 // grid: ((sequence, chunk) pairs, Hkv * row_chunks, Lyr), 256 threads.  WQ = waves along the query
@@ -212,7 +216,7 @@ struct DeferList {
   uint64_t* entries;      // device: bx | by << 32 | bz << 56
   uint32_t capacity;
 };
-template <bool EMIT, bool TASK_MAX, int WQ, int MODE>
+template <bool EMIT, bool TASK_MAX, int WQ, int MODE, bool STREAM>
 __device__ __forceinline__ void score_mfma_body(
     const PtrTable& q_tab, const PtrTable& k_tab, int batch, size_t out_layer_stride,
     const SeqTable& seq, int hq, int group, int window, int total, float c2, int chunk_keys,
@@ -288,11 +292,11 @@ __device__ __forceinline__ void score_mfma_body(
     if (t < nfull) {
 #pragma unroll
       for (int j = 0; j < MF_DMA; ++j)
-        lds_dma16_s(reinterpret_cast<const void*>(tile + j * 4096), dvoff, dst + j * 4096);
+        lds_dma16_s<STREAM>(reinterpret_cast<const void*>(tile + j * 4096), dvoff, dst + j * 4096);
     } else {   // ragged: rows past the sequence re-read the last valid row (masked later)
 #pragma unroll
       for (int j = 0; j < MF_DMA; ++j)
-        lds_dma16_s(reinterpret_cast<const void*>(tile),
+        lds_dma16_s<STREAM>(reinterpret_cast<const void*>(tile),
                     (uint32_t)(min(16 * j + drow, tail - 1) * MF_D + dpiece * 8) * 2u, dst + j * 4096);
     }
   };
@@ -683,13 +687,13 @@ __device__ __forceinline__ void score_mfma_body(
 }
 
 // The grid-indexed kernel: workgroup (blockIdx) = ((sequence, chunk) pair, KV head x row chunk, layer).
-template <bool EMIT, bool TASK_MAX, int WQ>
+template <bool EMIT, bool TASK_MAX, int WQ, bool STREAM>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
     int rc_offset, float* __restrict__ part_m, float* __restrict__ part_s, const float* __restrict__ lse2,
     int group_max, int causal, float* __restrict__ out, DeferList defer) {
-  score_mfma_body<EMIT, TASK_MAX, WQ, (EMIT && TASK_MAX) ? 1 : 0>(
+  score_mfma_body<EMIT, TASK_MAX, WQ, (EMIT && TASK_MAX) ? 1 : 0, STREAM>(
       q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
       row_chunks, rc_offset, part_m, part_s, lse2, group_max, causal, out, defer,
       (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, (int)gridDim.z);
@@ -709,7 +713,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
     const uint64_t e = defer.entries[i];
     const int bx = (int)(uint32_t)(e & 0xffffffffu), by = (int)((e >> 32) & 0xffffffu), bz = (int)(e >> 56);
     if (bx < gx && by < gy && bz < gz)     // entries are this library's own block indices; checked all the same
-      score_mfma_body<true, true, WQ, 2>(q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window,
+      score_mfma_body<true, true, WQ, 2, false>(q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window,
                                          total, c2, chunk_keys, row_chunks, rc_offset, nullptr, nullptr,
                                          lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
     __syncthreads();   // the next entry reuses the LDS
