@@ -38,11 +38,6 @@ struct TileArgs {
   size_t out_layer_stride;
 };
 
-// 16 bytes per lane from global memory into LDS at lds_base + 16 * lane, tracked by vmcnt only.
-__device__ __forceinline__ void tile_dma16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
-}
-
 // One k-step (16 bytes of every row of both operands) of a 32x32 tile.
 template <typename T>
 __device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
@@ -66,11 +61,13 @@ __device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
 // one head; the padding rows carry lse = +1e30 and contribute nothing.
 //
 // What bounds it is latency inside a wave (fragment reads, products, the vector work on their
-// result, one after the other), so the waves per SIMD decide: registers are held to what four
-// waves (rows of up to 160 bytes), three (256) or two (512) leave.  At 200 task tokens, 32
-// heads of 128 and 8192 tokens x 32 layers the emit pass took 722 us with two waves and 650 with
-// three.  A form with two accumulator sets and prefetched fragments, one wave less, was 5 %
-// faster there than this one with two waves, and 27 % slower at heads of 64.
+// result, one after the other) and the vector port, so registers are held to what four waves per
+// SIMD (rows of up to 160 bytes), three (256) or two (512) leave, masks stay out of the common
+// path and the tile loads take 32-bit offsets from a scalar base.  200 task tokens, 32 heads
+// of 128 and 8192 tokens x 32 layers, both passes: 1126 us with two waves and the mask
+// looked at per element, 1062 with three, 989 now (0.87 PFLOP/s); heads of 64 in a ragged batch of
+// 14k tokens 206, 202, 187.  A form with two accumulator sets and prefetched fragments, one
+// wave less, took 1075 and 262.
 template <typename T, int KS, int KB, bool EMIT, bool TASK_MAX>
 __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 : 4) void score_tile(
     PtrTable q_tab, PtrTable k_tab, SeqTable seq, TileArgs a, float* __restrict__ part_m,
@@ -108,26 +105,32 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   if (t_begin >= t_end) return;
 
   // query row (among the head's group * window) that row `pr` in tile order stands for, and
-  // whether it is a real one
+  // whether it is a real one; never falling with pr
   auto source_row = [&](int pr, bool& real) -> int {
     if (!EMIT) { real = pr < R; return min(pr, R - 1); }
     uint32_t g = __umulhi((uint32_t)pr, a.head_magic);   // exact or one too large
     if (g * (uint32_t)a.head_rows > (uint32_t)pr) --g;
     const int m = pr - (int)g * a.head_rows;
     real = (int)g < a.group && m < a.window;
-    return min((int)g, a.group - 1) * a.window + min(m, a.window - 1);
+    return (int)g < a.group ? (int)g * a.window + min(m, a.window - 1) : a.group * a.window - 1;
   };
   const uint32_t qtile_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint4*)(&qtile[0][0]);
   auto issue_tile = [&](int t) {
     const uint32_t dst = __builtin_amdgcn_readfirstlane(qtile_lds + (uint32_t)(t & 1) * (TL_ROWS * PS * 16));
+    // scalar base: the first row of the tile; the others follow within 64 rows of it
+    bool real;
+    const int first = __builtin_amdgcn_readfirstlane(source_row(t * TL_ROWS, real));
+    const uint64_t addr = reinterpret_cast<uint64_t>(q_head) + (uint64_t)(uint32_t)first * (uint32_t)(P * 16);
+    const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(addr >> 32)) << 32) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)addr);
 #pragma unroll
     for (int i = 0; i < DMA; ++i) {
       const int j = i * 4 + wave;                        // wave-uniform
       if (j < PS) {
         const int slot = j * 64 + lane;
         const int r = slot / PS, piece = min(slot - r * PS, P - 1);
-        bool real;
-        tile_dma16(q_head + (size_t)source_row(t * TL_ROWS + r, real) * P + piece, dst + j * 1024);
+        const uint32_t off = (uint32_t)((source_row(t * TL_ROWS + r, real) - first) * P + piece) * 16u;
+        lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, dst + j * 1024);
       }
     }
   };
@@ -203,6 +206,13 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[kb][r] = 0.f;
+      // EMIT: -lse2 of the lane's rows, asked for before the products so that it is there after them
+      float4 nl[4];
+      if (EMIT) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          nl[i] = *reinterpret_cast<const float4*>(&nls[t & 1][blk * 32 + 8 * i + 4 * half]);
+      }
       const uint4* qrow = &qtile[t & 1][(blk * 32 + col) * PS + half];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -243,20 +253,31 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
         if (half == 0) stat[t & 1][wave][blk * 32 + col] = make_float2(mx, s);
       } else {
         // registers 4 i .. 4 i + 3 hold rows 8 i + 4 half .. + 3 of the block
+        if (masked) {                     // on its own, so that the common case has no mask to look at
+          int m8 = sub;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int seen = n - a.window + 8 * m8 + 4 * half;     // last key that the first of the four sees
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if (wkey0 + kb * 32 + col > seen + r) acc[kb][4 * i + r] = -__builtin_inff();
+            if (++m8 == subs) m8 = 0;
+          }
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float4 nl = *reinterpret_cast<const float4*>(&nls[t & 1][blk * 32 + 8 * i + 4 * half]);
-          const float nlv[4] = {nl.x, nl.y, nl.z, nl.w};
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb) {
-            float v = TASK_MAX ? NEG_BIG : 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              float x = fmaf(acc[kb][4 * i + r], a.c2, nlv[r]);
-              if (masked && wkey0 + kb * 32 + col > n - a.window + 8 * sub + 4 * half + r) x = NEG_BIG;
-              v = TASK_MAX ? fmaxf(v, x) : v + fast_exp2(x);
+            const float x0 = fmaf(acc[kb][4 * i], a.c2, nl[i].x), x1 = fmaf(acc[kb][4 * i + 1], a.c2, nl[i].y);
+            const float x2 = fmaf(acc[kb][4 * i + 2], a.c2, nl[i].z), x3 = fmaf(acc[kb][4 * i + 3], a.c2, nl[i].w);
+            if (TASK_MAX) {
+              tacc[kb] = fmaxf(fmaxf(tacc[kb], x0), x1);
+              tacc[kb] = fmaxf(fmaxf(tacc[kb], x2), x3);
+            } else {
+              tacc[kb] += (fast_exp2(x0) + fast_exp2(x1)) + (fast_exp2(x2) + fast_exp2(x3));
             }
-            tacc[kb] = TASK_MAX ? fmaxf(tacc[kb], v) : tacc[kb] + v;
           }
           if (++sub == subs) finish_head();
         }
