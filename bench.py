@@ -46,6 +46,7 @@ PEAK_HBM_GBPS = 8000.0
 # instructions off, so its plain-ALU kernels can reach half of it at most; the
 # roofline object of such a kernel carries both.
 PEAK_FP32_VALU_TFLOPS = 157.3
+PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP32_VALU_TFLOPS_UNPACKED = PEAK_FP32_VALU_TFLOPS / 2
 # Counter-derived HBM bytes per launch live in a tracked data file together with a
 # digest of the kernel sources they were measured on (see load_traffic).
@@ -113,8 +114,8 @@ def record_traffic(d: str, layers: int, commit: str) -> None:
     cal_w = means("cal_write", "WRITE_SIZE")["copy_probe_kernel"][0]
     fs, ws = known_kib / cal_f, known_kib / cal_w
     fetch, write = means("fetch", "FETCH_SIZE"), means("write", "WRITE_SIZE")
-    label = {"score_mfma<false, true, 4, true>": "score_mfma<stats>",
-             "score_mfma<true, true, 4, true>": "score_mfma<emit>",
+    label = {"score_mfma<false, true, 4, true, 0>": "score_mfma<stats>",
+             "score_mfma<true, true, 4, true, 0>": "score_mfma<emit>",
              "head_rank_kernel<false, false>": "head_rank_kernel",
              "head_rank_kernel<false, true>": "head_rank_kernel",
              "head_rank_kernel<true, false>": "head_rank_kernel", "gather_kernel<2>": "gather_kernel"}
@@ -477,8 +478,18 @@ def main():
         roofline = {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": PEAK_HBM_GBPS,
                     "unit": "GB/s", "frac": achieved / PEAK_HBM_GBPS, "traffic": None,
                     "avg_launch_us": avg_s * 1e6, "launches_per_step": c}
+    elif dom.startswith("score_tile"):
+        # key-stationary matrix-core kernels (shapes and types outside score_mfma's)
+        c, ms = per_step[dom]
+        flops_per_launch = 2.0 * cfg.hq * cfg.window * cfg.head_dim * total * cfg.layers / c
+        avg_s = ms / c * 1e-3
+        achieved = flops_per_launch / avg_s / 1e12
+        peak = PEAK_BF16_MFMA_TFLOPS if cfg.dtype == "bf16" else PEAK_FP32_MFMA_TFLOPS
+        roofline = {"bound": "mfma", "kernel": dom, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                    "frac": achieved / peak, "traffic": None, "avg_launch_us": avg_s * 1e6,
+                    "launches_per_step": c}
     elif dom.startswith("score_"):
-        # generic fp32 kernels (vector ALU, no matrix cores): 2*d flops per logit
+        # plain fp32 kernels (vector ALU, no matrix cores): 2*d flops per logit
         c, ms = per_step[dom]
         flops_per_launch = 2.0 * cfg.hq * cfg.window * cfg.head_dim * total * cfg.layers / c
         avg_s = ms / c * 1e-3

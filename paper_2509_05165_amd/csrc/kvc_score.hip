@@ -189,17 +189,14 @@ __global__ __launch_bounds__(256) void score_emit_generic(
 // ---------------------------------------------------------------------------
 constexpr int MERGE_ROWS = 16;
 
-// (Both merge kernels also clear the two counters of the emit pass's defer lists, which
-// sit DEFER_COUNTER_STRIDE words apart: the merge always runs between stats and emit.)
+// Words between the counters of the emit pass's two defer lists.
 constexpr int DEFER_COUNTER_STRIDE = 64;
 __global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_seq, int layers,
                                                    int chunk_keys,
                                                    const float* __restrict__ part_m,
                                                    const float* __restrict__ part_s,
-                                                   float* __restrict__ lse2,
-                                                   uint32_t* __restrict__ defer_counters) {
+                                                   float* __restrict__ lse2) {
   __shared__ float sm[16][MERGE_ROWS], ss[16][MERGE_ROWS];
-  if (defer_counters && blockIdx.x == 0 && threadIdx.x < 2) defer_counters[threadIdx.x * DEFER_COUNTER_STRIDE] = 0;
   const int r = threadIdx.x & (MERGE_ROWS - 1), cg = threadIdx.x >> 4;
   // rows of every layer of the launch: row = (layer * batch + sequence) * rows_per_seq + ...
   const int rows = rows_per_seq * seq.batch * layers;
@@ -237,9 +234,7 @@ __global__ __launch_bounds__(256) void score_merge_few(SeqTable seq, int rows_pe
                                                        int chunk_keys,
                                                        const float* __restrict__ part_m,
                                                        const float* __restrict__ part_s,
-                                                       float* __restrict__ lse2,
-                                                       uint32_t* __restrict__ defer_counters) {
-  if (defer_counters && blockIdx.x == 0 && threadIdx.x < 2) defer_counters[threadIdx.x * DEFER_COUNTER_STRIDE] = 0;
+                                                       float* __restrict__ lse2) {
   const int rows = rows_per_seq * seq.batch * layers;
   const int row = blockIdx.x * 256 + threadIdx.x;
   if (row >= rows) return;
@@ -247,14 +242,7 @@ __global__ __launch_bounds__(256) void score_merge_few(SeqTable seq, int rows_pe
   const int n = seq.cu[b + 1] - seq.cu[b];
   const int chunks = (n + chunk_keys - 1) / chunk_keys;
   if (chunks == 0) return;
-  float mm = NEG_BIG, acc = 0.f;
-  for (int c = 0; c < chunks; ++c) {
-    const float m2 = part_m[(size_t)c * rows + row], s2 = part_s[(size_t)c * rows + row];
-    const float mn = fmaxf(mm, m2);
-    acc = acc * fast_exp2(mm - mn) + s2 * fast_exp2(m2 - mn);
-    mm = mn;
-  }
-  lse2[row] = mm + __log2f(acc);
+  lse2[row] = merge_few(part_m, part_s, row, rows, chunks);
 }
 
 // ---------------------------------------------------------------------------
@@ -569,10 +557,10 @@ kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* cons
   const int rows_all = int(a.rows_all), chunks = int((pb.max_seqlen + keys - 1) / keys);
   if (chunks <= 4)
     KVC_LAUNCH("score_merge", stream, score_merge_few<<<(rows_all + 255) / 256, 256, 0, stream>>>(
-        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, nullptr));
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2));
   else
     KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, nullptr));
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2));
   const dim3 grid(unsigned(flat), pb.hkv, layers);
   if (pb.agg_task == KVC_AGG_MAX)
     KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, KB, true, true><<<grid, TL_THREADS, 0, stream>>>(
@@ -645,17 +633,18 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const uint32_t defer_cap = (uint32_t)(L.defer_capacity < 0xffffffffu ? L.defer_capacity : 0xffffffffu);
     const DeferList defer_main{defer_counters, defer_entries, defer_cap};
     const DeferList defer_rem{defer_counters + DEFER_COUNTER_STRIDE, defer_entries + L.defer_capacity, defer_cap};
-    const DeferList defer_none{nullptr, nullptr, 0};
 #define KVC_SCORE_MFMA(NAME, EMIT, TMAX, WQ, RCS, RC0, PM, PS, LSE, OUT)                         \
   do {                                                                                           \
-    const DeferList dl_ = (EMIT && TMAX) ? ((RC0) == 0 ? defer_main : defer_rem) : defer_none;   \
-    KVC_LAUNCH(NAME, stream, (stream_k && (RCS) == 1 ? score_mfma<EMIT, TMAX, WQ, true> : score_mfma<EMIT, TMAX, WQ, false>)<<<dim3(gx, pb.hkv * (RCS), pb.layers), MF_THREADS, 0, stream>>>( \
+    const DeferList dl_ = (RC0) == 0 ? defer_main : defer_rem;   \
+    KVC_LAUNCH(NAME, stream, \
+        (EMIT && !merge ? (stream_k && (RCS) == 1 ? score_mfma<EMIT, TMAX, WQ, true, EMIT ? LSE_PARTIAL : LSE_MERGED> : score_mfma<EMIT, TMAX, WQ, false, EMIT ? LSE_PARTIAL : LSE_MERGED>) \
+                        : (stream_k && (RCS) == 1 ? score_mfma<EMIT, TMAX, WQ, true, LSE_MERGED> : score_mfma<EMIT, TMAX, WQ, false, LSE_MERGED>))<<<dim3(gx, pb.hkv * (RCS), pb.layers), MF_THREADS, 0, stream>>>( \
         qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,      \
         RCS, RC0, PM, PS, LSE, group_max, pb.causal_tail, OUT, dl_));                            \
     if (EMIT && TMAX)                                                                            \
       KVC_LAUNCH(NAME ",exact", stream, score_mfma_listed<WQ><<<MF_LISTED_BLOCKS, MF_THREADS, 0, stream>>>( \
           qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,    \
-          RCS, RC0, LSE, group_max, pb.causal_tail, OUT, dl_, (int)gx, pb.hkv * (RCS), pb.layers)); \
+          RCS, RC0, PM, PS, LSE, group_max, pb.causal_tail, OUT, dl_, (int)gx, pb.hkv * (RCS), pb.layers)); \
   } while (0)
 #define KVC_SCORE_MFMA_BLOCKS(NAME, EMIT, TMAX, BLOCKS, RCS, RC0, PM, PS, LSE, OUT)                  \
   do {                                                                                             \
@@ -668,19 +657,20 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     KVC_SCORE_MFMA_BLOCKS(NAME, EMIT, TMAX, nqb0, main_chunks, 0, PM, PS, LSE, OUT);                            \
     if (split) KVC_SCORE_MFMA_BLOCKS(NAME ",rem", EMIT, TMAX, rem_blocks, 1, main_chunks, PM, PS, LSE, OUT);    \
   } while (0)
+    // up to four chunks a sequence: the emit workgroups merge their rows' partials
+    // themselves (two loads a chunk and row), which is a launch of 5 us less (one prompt of 777
+    // tokens 107.0 -> 103.5 us, one of 4096 301 -> 294)
+    const bool merge = chunks > 4;
     if (chunks > 0) {
       KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);
-      if (chunks <= 4) {
-        KVC_LAUNCH("score_merge", stream, score_merge_few<<<(rows_all + 255) / 256, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, defer_counters));
-      } else {
+      if (merge)
         KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, defer_counters));
-      }
+            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2));
+      float *few_m = merge ? nullptr : part_m, *few_s = merge ? nullptr : part_s;
       if (task_max) {
-        KVC_SCORE_MFMA_WQ("score_mfma<emit>", true, true, nullptr, nullptr, lse2, part_all);
+        KVC_SCORE_MFMA_WQ("score_mfma<emit>", true, true, few_m, few_s, lse2, part_all);
       } else {
-        KVC_SCORE_MFMA_WQ("score_mfma<emit>", true, false, nullptr, nullptr, lse2, part_all);
+        KVC_SCORE_MFMA_WQ("score_mfma<emit>", true, false, few_m, few_s, lse2, part_all);
       }
     }
 #undef KVC_SCORE_MFMA_WQ
@@ -742,7 +732,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, L.max_chunks,
             pb.causal_tail, part_m, part_s));
         KVC_LAUNCH("score_merge", stream, score_merge<<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, nullptr));
+            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2));
         KVC_LAUNCH("score_emit_generic", stream, score_emit_generic<uint16_t><<<ge, 256, lds_e, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, lse2, task_max,
             group_max, pb.causal_tail, part));
@@ -753,7 +743,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, L.max_chunks,
             pb.causal_tail, part_m, part_s));
         KVC_LAUNCH("score_merge", stream, score_merge<<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, nullptr));
+            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2));
         KVC_LAUNCH("score_emit_generic", stream, score_emit_generic<float><<<ge, 256, lds_e, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, lse2, task_max,
             group_max, pb.causal_tail, part));

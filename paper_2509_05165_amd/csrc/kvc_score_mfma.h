@@ -185,6 +185,19 @@ __device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, ui
                  : "memory");
 }
 
+// log2 sum 2^t of a row from its partial statistics (stored chunk by chunk, `stride` rows each).
+__device__ __forceinline__ float merge_few(const float* __restrict__ part_m, const float* __restrict__ part_s,
+                                           size_t row, size_t stride, int chunks) {
+  float mm = NEG_BIG, acc = 0.f;
+  for (int c = 0; c < chunks; ++c) {
+    const float m2 = part_m[c * stride + row], s2 = part_s[c * stride + row];
+    const float mn = fmaxf(mm, m2);
+    acc = acc * fast_exp2(mm - mn) + s2 * fast_exp2(m2 - mn);
+    mm = mn;
+  }
+  return mm + __log2f(acc);
+}
+
 // grid: ((sequence, chunk) pairs, Hkv * row_chunks, Lyr), 256 threads.  WQ = waves along the query
 // rows (each owns 2 blocks of 32 rows); the other 4/WQ waves split the key tiles.
 // A launch covers the row chunks [rc_offset, rc_offset + row_chunks) of every KV head
@@ -211,12 +224,17 @@ __device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, ui
 // putting its block index (bx, by, bz) on the `defer` list instead of working; 2 = the
 // exact form, which the list-driven kernel below runs for the listed workgroups.
 // (bx, by, bz) and (gy, gz) stand for blockIdx and gridDim.y/z of the grid launch.
+//
+// LSE: where the emit pass has the log-sum-exps of its rows from.  LSE_MERGED: lse2, written by
+// score_merge.  LSE_PARTIAL: part_m / part_s, merged by each workgroup for its own rows.
+// (Two kernels, not a branch: that cost the long launches 0.5 %.)
+enum { LSE_MERGED = 0, LSE_PARTIAL = 1, LSE_EITHER = 2 };   // (by part_m being null or not)
 struct DeferList {
   uint32_t* count;        // device: number of entries appended so far
   uint64_t* entries;      // device: bx | by << 32 | bz << 56
   uint32_t capacity;
 };
-template <bool EMIT, bool TASK_MAX, int WQ, int MODE, bool STREAM>
+template <bool EMIT, bool TASK_MAX, int WQ, int MODE, bool STREAM, int LSE>
 __device__ __forceinline__ void score_mfma_body(
     const PtrTable& q_tab, const PtrTable& k_tab, int batch, size_t out_layer_stride,
     const SeqTable& seq, int hq, int group, int window, int total, float c2, int chunk_keys,
@@ -242,6 +260,8 @@ __device__ __forceinline__ void score_mfma_body(
   // mix of sequence lengths (a chunk-major grid gave XCD j the j-th chunk of every
   // sequence: twice the time on a batch of 5k..29k-token sequences).
   const int layer = bz;
+  // the list of the emit pass starts empty
+  if (!EMIT && bx == 0 && by == 0 && bz == 0 && threadIdx.x == 0) *defer.count = 0;
   const int chunk_shift = __builtin_ctz(chunk_keys);   // chunk_keys is a power of two (host-checked)
   int b = 0, chunk = bx;
   for (; b < batch - 1; ++b) {
@@ -322,8 +342,15 @@ __device__ __forceinline__ void score_mfma_body(
 
   // EMIT: minus lse2 of this row chunk goes through LDS (one coalesced load)
   float my_nl = 0.f;
-  if (EMIT && (int)threadIdx.x < nqb * 32)
-    my_nl = -lse2[((size_t)zid * hq + h * group) * window + row0 + threadIdx.x];
+  if (EMIT && (int)threadIdx.x < nqb * 32) {
+    const size_t row = ((size_t)zid * hq + h * group) * window + row0 + threadIdx.x;
+    if (LSE == LSE_MERGED || (LSE == LSE_EITHER && part_m == nullptr)) {
+      my_nl = -lse2[row];
+    } else {
+      const size_t rows_all = (size_t)gz * batch * hq * window;
+      my_nl = -merge_few(part_m, part_s, row, rows_all, (n + chunk_keys - 1) >> chunk_shift);
+    }
+  }
   float nl[2][16];   // EMIT: minus lse2 of the lane's accumulator rows, filled after the first barrier
   float nbase[2] = {0.f, 0.f};   // RECENTRE: minus lse2 of the first row of each q block
 
@@ -687,13 +714,13 @@ __device__ __forceinline__ void score_mfma_body(
 }
 
 // The grid-indexed kernel: workgroup (blockIdx) = ((sequence, chunk) pair, KV head x row chunk, layer).
-template <bool EMIT, bool TASK_MAX, int WQ, bool STREAM>
+template <bool EMIT, bool TASK_MAX, int WQ, bool STREAM, int LSE>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
     int rc_offset, float* __restrict__ part_m, float* __restrict__ part_s, const float* __restrict__ lse2,
     int group_max, int causal, float* __restrict__ out, DeferList defer) {
-  score_mfma_body<EMIT, TASK_MAX, WQ, (EMIT && TASK_MAX) ? 1 : 0, STREAM>(
+  score_mfma_body<EMIT, TASK_MAX, WQ, (EMIT && TASK_MAX) ? 1 : 0, STREAM, LSE>(
       q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
       row_chunks, rc_offset, part_m, part_s, lse2, group_max, causal, out, defer,
       (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, (int)gridDim.z);
@@ -706,15 +733,16 @@ template <int WQ>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
-    int rc_offset, const float* __restrict__ lse2, int group_max, int causal,
+    int rc_offset, float* __restrict__ part_m, float* __restrict__ part_s,
+    const float* __restrict__ lse2, int group_max, int causal,
     float* __restrict__ out, DeferList defer, int gx, int gy, int gz) {
   const uint32_t listed = min(*defer.count, defer.capacity);     // appended by the launch before this one
   for (uint32_t i = blockIdx.x; i < listed; i += gridDim.x) {
     const uint64_t e = defer.entries[i];
     const int bx = (int)(uint32_t)(e & 0xffffffffu), by = (int)((e >> 32) & 0xffffffu), bz = (int)(e >> 56);
     if (bx < gx && by < gy && bz < gz)     // entries are this library's own block indices; checked all the same
-      score_mfma_body<true, true, WQ, 2, false>(q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window,
-                                         total, c2, chunk_keys, row_chunks, rc_offset, nullptr, nullptr,
+      score_mfma_body<true, true, WQ, 2, false, LSE_EITHER>(q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window,
+                                         total, c2, chunk_keys, row_chunks, rc_offset, part_m, part_s,
                                          lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
     __syncthreads();   // the next entry reuses the LDS
   }
