@@ -188,6 +188,8 @@ __global__ __launch_bounds__(256) void score_emit_generic(
 // key chunks (partials are stored [chunk][row], so reads are coalesced).
 // ---------------------------------------------------------------------------
 constexpr int MERGE_ROWS = 16;
+// with_rest: lse2 holds a second array behind the first, what rounding took from each entry
+// (float32 callers: at a log-sum-exp of 50 the rounding is 2e-6, more than the rest of the path).
 
 // Words between the counters of the emit pass's two defer lists.
 constexpr int DEFER_COUNTER_STRIDE = 64;
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_se
                                                    int chunk_keys,
                                                    const float* __restrict__ part_m,
                                                    const float* __restrict__ part_s,
-                                                   float* __restrict__ lse2) {
+                                                   float* __restrict__ lse2, int with_rest) {
   __shared__ float sm[16][MERGE_ROWS], ss[16][MERGE_ROWS];
   const int r = threadIdx.x & (MERGE_ROWS - 1), cg = threadIdx.x >> 4;
   // rows of every layer of the launch: row = (layer * batch + sequence) * rows_per_seq + ...
@@ -224,7 +226,9 @@ __global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_se
     float tot = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) tot += ss[i][r] * fast_exp2(sm[i][r] - top);
-    lse2[row] = top + __log2f(tot);
+    const float lg = __log2f(tot), lse = top + lg;
+    lse2[row] = lse;
+    if (with_rest) lse2[rows + row] = (top - lse) + lg;
   }
 }
 
@@ -234,7 +238,7 @@ __global__ __launch_bounds__(256) void score_merge_few(SeqTable seq, int rows_pe
                                                        int chunk_keys,
                                                        const float* __restrict__ part_m,
                                                        const float* __restrict__ part_s,
-                                                       float* __restrict__ lse2) {
+                                                       float* __restrict__ lse2, int with_rest) {
   const int rows = rows_per_seq * seq.batch * layers;
   const int row = blockIdx.x * 256 + threadIdx.x;
   if (row >= rows) return;
@@ -242,7 +246,9 @@ __global__ __launch_bounds__(256) void score_merge_few(SeqTable seq, int rows_pe
   const int n = seq.cu[b + 1] - seq.cu[b];
   const int chunks = (n + chunk_keys - 1) / chunk_keys;
   if (chunks == 0) return;
-  lse2[row] = merge_few(part_m, part_s, row, rows, chunks);
+  float rest;
+  lse2[row] = merge_few(part_m, part_s, row, rows, chunks, rest);
+  if (with_rest) lse2[rows + row] = rest;
 }
 
 // ---------------------------------------------------------------------------
@@ -455,14 +461,14 @@ ScoreLayout score_layout(const Problem& pb) {
     // below 64 MB), and at least one.
     const int keys = tile_keys(tile_ksteps(pb.dtype, pb.d * esize(pb.dtype) / 16));
     L.max_chunks = std::max(1, int((pb.max_seqlen + keys - 1) / keys));
-    const size_t per_layer = size_t(L.rows_layer) * (8 * size_t(L.max_chunks) + 4);
+    const size_t per_layer = size_t(L.rows_layer) * (8 * size_t(L.max_chunks) + 8);
     const size_t bound = std::max(size_t(64) << 20, size_t(pb.layers) * pb.hkv * size_t(pb.total) * 16);
     L.layers_held = int(std::min<size_t>(pb.layers, std::max<size_t>(1, bound / per_layer)));
   }
   size_t cur = 0;
   L.off_m = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
   L.off_s = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
-  L.off_lse = cur;  cur += align_up(size_t(L.rows_layer) * L.layers_held * 4);
+  L.off_lse = cur;  cur += align_up(size_t(L.rows_layer) * L.layers_held * (pb.dtype == KVC_F32 ? 8 : 4));
   L.off_part = cur;
   // partials are needed when row chunks must be combined, or when more than 8
   // KV heads make the in-place finish impossible
@@ -557,10 +563,10 @@ kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* cons
   const int rows_all = int(a.rows_all), chunks = int((pb.max_seqlen + keys - 1) / keys);
   if (chunks <= 4)
     KVC_LAUNCH("score_merge", stream, score_merge_few<<<(rows_all + 255) / 256, 256, 0, stream>>>(
-        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2));
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4)));
   else
     KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2));
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4)));
   const dim3 grid(unsigned(flat), pb.hkv, layers);
   if (pb.agg_task == KVC_AGG_MAX)
     KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, KB, true, true><<<grid, TL_THREADS, 0, stream>>>(
@@ -665,7 +671,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
       KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);
       if (merge)
         KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2));
+            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0));
       float *few_m = merge ? nullptr : part_m, *few_s = merge ? nullptr : part_s;
       if (task_max) {
         KVC_SCORE_MFMA_WQ("score_mfma<emit>", true, true, few_m, few_s, lse2, part_all);
@@ -732,7 +738,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, L.max_chunks,
             pb.causal_tail, part_m, part_s));
         KVC_LAUNCH("score_merge", stream, score_merge<<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2));
+            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, 0));
         KVC_LAUNCH("score_emit_generic", stream, score_emit_generic<uint16_t><<<ge, 256, lds_e, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, lse2, task_max,
             group_max, pb.causal_tail, part));
@@ -743,7 +749,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, L.max_chunks,
             pb.causal_tail, part_m, part_s));
         KVC_LAUNCH("score_merge", stream, score_merge<<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2));
+            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, 0));
         KVC_LAUNCH("score_emit_generic", stream, score_emit_generic<float><<<ge, 256, lds_e, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, lse2, task_max,
             group_max, pb.causal_tail, part));

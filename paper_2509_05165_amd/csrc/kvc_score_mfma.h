@@ -185,9 +185,10 @@ __device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, ui
                  : "memory");
 }
 
-// log2 sum 2^t of a row from its partial statistics (stored chunk by chunk, `stride` rows each).
+// log2 sum 2^t of a row from its partial statistics (stored chunk by chunk, `stride` rows each);
+// rest: what its rounding took away.
 __device__ __forceinline__ float merge_few(const float* __restrict__ part_m, const float* __restrict__ part_s,
-                                           size_t row, size_t stride, int chunks) {
+                                           size_t row, size_t stride, int chunks, float& rest) {
   float mm = NEG_BIG, acc = 0.f;
   for (int c = 0; c < chunks; ++c) {
     const float m2 = part_m[c * stride + row], s2 = part_s[c * stride + row];
@@ -195,7 +196,9 @@ __device__ __forceinline__ float merge_few(const float* __restrict__ part_m, con
     acc = acc * fast_exp2(mm - mn) + s2 * fast_exp2(m2 - mn);
     mm = mn;
   }
-  return mm + __log2f(acc);
+  const float lg = __log2f(acc), lse = mm + lg;
+  rest = (mm - lse) + lg;
+  return lse;
 }
 
 // grid: ((sequence, chunk) pairs, Hkv * row_chunks, Lyr), 256 threads.  WQ = waves along the query
@@ -348,7 +351,8 @@ __device__ __forceinline__ void score_mfma_body(
       my_nl = -lse2[row];
     } else {
       const size_t rows_all = (size_t)gz * batch * hq * window;
-      my_nl = -merge_few(part_m, part_s, row, rows_all, (n + chunk_keys - 1) >> chunk_shift);
+      float rest;
+      my_nl = -merge_few(part_m, part_s, row, rows_all, (n + chunk_keys - 1) >> chunk_shift, rest);
     }
   }
   float nl[2][16];   // EMIT: minus lse2 of the lane's accumulator rows, filled after the first barrier

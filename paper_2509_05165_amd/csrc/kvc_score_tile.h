@@ -77,7 +77,10 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   constexpr int DMA = (PS + 3) / 4;             // load instructions per wave and tile, at most
   __shared__ __attribute__((aligned(16))) uint4 qtile[2][TL_ROWS * PS];
   __shared__ float2 stat[EMIT ? 1 : 2][4][EMIT ? 1 : TL_ROWS];
+  // EMIT: minus the log-sum-exps of a tile's rows; float32 keeps what rounding took from them, too
+  constexpr bool REST = EMIT && sizeof(T) == 4;
   __shared__ __attribute__((aligned(16))) float nls[EMIT ? 2 : 1][EMIT ? TL_ROWS : 4];
+  __shared__ __attribute__((aligned(16))) float rests[REST ? 2 : 1][REST ? TL_ROWS : 4];
 
   const int layer = blockIdx.z;
   int b = 0, chunk = blockIdx.x;
@@ -134,10 +137,11 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
       }
     }
   };
-  // EMIT: minus the log-sum-exp of row `lane` of tile t
-  auto load_nl = [&](int t) -> float {
+  // EMIT: minus the log-sum-exp of row `lane` of tile t (and minus the rest of it)
+  auto load_nl = [&](int t, float& rest) -> float {
     bool real;
     const int r = source_row(t * TL_ROWS + lane, real);
+    rest = REST ? -lse2[a.rows_all + qrow0 + r] : 0.f;
     return real ? -lse2[qrow0 + r] : NEG_BIG;
   };
 
@@ -153,8 +157,11 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
       kf[kb][ks] = piece < P ? krow[piece] : make_uint4(0, 0, 0, 0);
     }
   }
-  float next_nl = 0.f;
-  if (EMIT && wave == 0) nls[t_begin & 1][lane] = load_nl(t_begin);
+  float next_nl = 0.f, next_rest = 0.f;
+  if (EMIT && wave == 0) {
+    nls[t_begin & 1][lane] = load_nl(t_begin, next_rest);
+    if (REST) rests[t_begin & 1][lane] = next_rest;
+  }
 
   const bool active = wkey0 < n;                                  // wave-uniform, like the next two
   const bool ragged = wkey0 + 32 * KB > n;
@@ -196,7 +203,7 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
     if (!EMIT && t > t_begin) store_stats(t - 1);
     if (t + 1 < t_end) {
       issue_tile(t + 1);
-      if (EMIT && wave == 0) next_nl = load_nl(t + 1);
+      if (EMIT && wave == 0) next_nl = load_nl(t + 1, next_rest);
     }
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
@@ -268,10 +275,13 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+          float4 rest = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (REST) rest = *reinterpret_cast<const float4*>(&rests[t & 1][blk * 32 + 8 * i + 4 * half]);
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb) {
-            const float x0 = fmaf(acc[kb][4 * i], a.c2, nl[i].x), x1 = fmaf(acc[kb][4 * i + 1], a.c2, nl[i].y);
-            const float x2 = fmaf(acc[kb][4 * i + 2], a.c2, nl[i].z), x3 = fmaf(acc[kb][4 * i + 3], a.c2, nl[i].w);
+            float x0 = fmaf(acc[kb][4 * i], a.c2, nl[i].x), x1 = fmaf(acc[kb][4 * i + 1], a.c2, nl[i].y);
+            float x2 = fmaf(acc[kb][4 * i + 2], a.c2, nl[i].z), x3 = fmaf(acc[kb][4 * i + 3], a.c2, nl[i].w);
+            if (REST) { x0 += rest.x; x1 += rest.y; x2 += rest.z; x3 += rest.w; }
             if (TASK_MAX) {
               tacc[kb] = fmaxf(fmaxf(tacc[kb], x0), x1);
               tacc[kb] = fmaxf(fmaxf(tacc[kb], x2), x3);
@@ -283,7 +293,10 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
         }
       }
     }
-    if (EMIT && wave == 0 && t + 1 < t_end) nls[(t + 1) & 1][lane] = next_nl;
+    if (EMIT && wave == 0 && t + 1 < t_end) {
+      nls[(t + 1) & 1][lane] = next_nl;
+      if (REST) rests[(t + 1) & 1][lane] = next_rest;
+    }
   }
   if constexpr (!EMIT) {
     wait_memory();
