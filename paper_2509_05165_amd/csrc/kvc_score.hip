@@ -630,7 +630,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const int main_chunks = split ? L.row_chunks - 1 : L.row_chunks;
     const unsigned gx = flat_chunks > 0 ? flat_chunks : 1;
     const int64_t k_bytes = int64_t(pb.layers) * pb.hkv * total * MF_D * 2;
-    const bool stream_k = k_bytes > MF_STREAM_BYTES;
+    const bool stream_k = k_bytes >= MF_STREAM_BYTES;
     // Max-pooling emit pass: a workgroup whose log-sum-exps are too far apart for the cheap
     // form puts itself on a list (one for the main launch, one for the remainder launch)
     // and a small list-driven launch right behind redoes the listed ones in the exact form.
