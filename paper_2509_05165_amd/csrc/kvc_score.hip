@@ -452,30 +452,37 @@ ScoreLayout score_layout(const Problem& pb) {
   L.row_chunks = mfma ? (pb.group * pb.window + MF_RCHUNK - 1) / MF_RCHUNK : 1;
   // The query-stationary path runs all layers in one launch and keeps the statistics,
   // log-sum-exps and group partials of every layer.
+  const size_t lse_bytes = pb.dtype == KVC_F32 ? 8 : 4;   // float32 keeps the rest of its log-sum-exps, too
+  size_t reserved = 0;
   if (mfma) {
     L.layers_held = pb.layers;
     L.max_chunks = std::max(1, int((pb.max_seqlen + MF_CHUNK - 1) / MF_CHUNK));
   } else {
     // The key-stationary path has a chunk per workgroup.  It takes as many layers at once as
     // keep the statistics below what the rank stage asks of the same workspace anyway (or
-    // below 64 MB), and at least one.
+    // below 64 MB), and at least one.  The space is reserved by that bound and not by the layers
+    // that fit it, so that it never shrinks when max_seqlen grows.
     const int keys = tile_keys(tile_ksteps(pb.dtype, pb.d * esize(pb.dtype) / 16));
     L.max_chunks = std::max(1, int((pb.max_seqlen + keys - 1) / keys));
-    const size_t per_layer = size_t(L.rows_layer) * (8 * size_t(L.max_chunks) + 8);
+    const size_t per_layer = size_t(L.rows_layer) * (8 * size_t(L.max_chunks) + lse_bytes);
     const size_t bound = std::max(size_t(64) << 20, size_t(pb.layers) * pb.hkv * size_t(pb.total) * 16);
-    L.layers_held = int(std::min<size_t>(pb.layers, std::max<size_t>(1, bound / per_layer)));
+    const size_t stats = std::max(per_layer, std::min(bound, pb.layers * per_layer));
+    // (the merge kernels count the rows of a launch in 32 bits)
+    L.layers_held = int(std::min<size_t>(stats / per_layer, std::max<size_t>(1, (size_t(1) << 30) / L.rows_layer)));
+    reserved = align_up(stats) + 3 * align_up(1);         // each of the three arrays is rounded up
   }
   size_t cur = 0;
   L.off_m = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
   L.off_s = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
-  L.off_lse = cur;  cur += align_up(size_t(L.rows_layer) * L.layers_held * (pb.dtype == KVC_F32 ? 8 : 4));
+  L.off_lse = cur;  cur += align_up(size_t(L.rows_layer) * L.layers_held * lse_bytes);
+  cur = std::max(cur, reserved);
   L.off_part = cur;
   // partials are needed when row chunks must be combined, or when more than 8
   // KV heads make the in-place finish impossible
   L.part_layer = size_t(L.row_chunks) * pb.hkv * size_t(pb.total);
-  if (L.row_chunks > 1 || pb.hkv > 8) cur += align_up(L.part_layer * L.layers_held * 4);
+  if (L.row_chunks > 1 || pb.hkv > 8) cur += align_up(L.part_layer * pb.layers * 4);
   L.off_vnorm = cur;
-  if (pb.value_norm) cur += align_up(size_t(L.layers_held) * pb.hkv * size_t(pb.total) * 4);
+  if (pb.value_norm) cur += align_up(size_t(pb.layers) * pb.hkv * size_t(pb.total) * 4);
   // defer lists of the emit pass (matrix-core path): two counters, then two lists of block
   // indices; a launch has at most (total/chunk + batch) x hkv x row_chunks x layers workgroups
   L.off_defer = cur;
