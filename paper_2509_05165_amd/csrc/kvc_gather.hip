@@ -147,7 +147,7 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
 // launches over a bit map in memory, 256 lists of 6000 out of 30011 positions took 45 us of
 // global atomics, 7 to clear and 12 to compact.)  grid: (layers*hkv, batch), 1024 threads, a bit per
 // token of dynamic LDS; sel: int32 [layers, hkv, total] like idx.
-constexpr int64_t ORDER_LDS_TOKENS = 65536 * 8;   // 64 KB of bits: two workgroups share a compute unit
+constexpr int64_t ORDER_LDS_TOKENS = 61440 * 8;   // 60 KB of bits: two workgroups share a compute unit
 __global__ __launch_bounds__(1024) void order_list(const int32_t* __restrict__ idx,
                                                    const int32_t* __restrict__ lengths, SeqTable seq,
                                                    int layers, int hkv, int heads_per_block, int total,

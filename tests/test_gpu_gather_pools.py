@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (60, 8, [70, 700], 700),              # 262144 rows and more: 64 a wave
     (2, 3, [32767, 1], 32767),
     (1, 2, [32769, 31, 33], 32769),       # two stretches of words
+    (1, 1, [491520], 491520),             # the longest list that is ordered in LDS
+    (1, 1, [491521, 40], 491521),         # and the shortest that is not
 ])
 def test_gather_of_many_blocks(order, lyr, hkv, lens, most):
     print(f"[case] gather pools order={order} lyr={lyr} hkv={hkv} {lens}", flush=True)
