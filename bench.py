@@ -114,8 +114,8 @@ def record_traffic(d: str, layers: int, commit: str) -> None:
     cal_w = means("cal_write", "WRITE_SIZE")["copy_probe_kernel"][0]
     fs, ws = known_kib / cal_f, known_kib / cal_w
     fetch, write = means("fetch", "FETCH_SIZE"), means("write", "WRITE_SIZE")
-    label = {"score_mfma<false, true, 4, true, 0>": "score_mfma<stats>",
-             "score_mfma<true, true, 4, true, 0>": "score_mfma<emit>",
+    label = {"score_mfma<false, true, 4, 0, true, 0>": "score_mfma<stats>",
+             "score_mfma<true, true, 4, 0, true, 0>": "score_mfma<emit>",
              "head_rank_kernel<false, false>": "head_rank_kernel",
              "head_rank_kernel<false, true>": "head_rank_kernel",
              "head_rank_kernel<true, false>": "head_rank_kernel", "gather_kernel<2>": "gather_kernel"}

@@ -191,8 +191,6 @@ constexpr int MERGE_ROWS = 16;
 // with_rest: lse2 holds a second array behind the first, what rounding took from each entry
 // (float32 callers: at a log-sum-exp of 50 the rounding is 2e-6, more than the rest of the path).
 
-// Words between the counters of the emit pass's two defer lists.
-constexpr int DEFER_COUNTER_STRIDE = 64;
 __global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_seq, int layers,
                                                    int chunk_keys,
                                                    const float* __restrict__ part_m,
@@ -483,13 +481,12 @@ ScoreLayout score_layout(const Problem& pb) {
   if (L.row_chunks > 1 || pb.hkv > 8) cur += align_up(L.part_layer * pb.layers * 4);
   L.off_vnorm = cur;
   if (pb.value_norm) cur += align_up(size_t(pb.layers) * pb.hkv * size_t(pb.total) * 4);
-  // defer lists of the emit pass (matrix-core path): two counters, then two lists of block
-  // indices; a launch has at most (total/chunk + batch) x hkv x row_chunks x layers workgroups
+  // defer list of the emit pass (query-stationary path): a counter, then block indices; a launch has at most (total/chunk + batch) x hkv x row_chunks x layers workgroups
   L.off_defer = cur;
   L.defer_capacity = 0;
   if (mfma) {
     L.defer_capacity = (size_t(pb.total) / MF_CHUNK + size_t(pb.batch)) * pb.hkv * L.row_chunks * pb.layers;
-    cur += align_up(2 * DEFER_COUNTER_STRIDE * 4) + align_up(2 * L.defer_capacity * 8);
+    cur += align_up(4) + align_up(L.defer_capacity * 8);
   }
   L.total = cur;
   return L;
@@ -629,46 +626,45 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const int rows_head = pb.group * pb.window;                  // query rows per KV head
     const int nqb0 = (rows_head < MF_RCHUNK ? rows_head : MF_RCHUNK) / 32;
     const int rows_all = L.rows_layer * pb.layers;
-    // The last row chunk of a head may hold few rows (G = 5 at M = 64: 256 + 64).  With
-    // four waves along the rows it would cost a full 256-row pass, so when it has at most
-    // four 32-row blocks it gets a launch of its own in which the waves split the keys.
+    // The last row chunk of a head may hold few rows (G = 5 at M = 64: 256 + 64).  With four
+    // waves along the rows it would cost a full 256-row pass, so when it has at most four
+    // 32-row blocks the waves of its workgroups split the keys instead, in the same launch and
+    // without the streaming hint, so that K comes from memory once for all row chunks.  40/8
+    // heads, M = 64, 32 sequences of 4096: 13475 us a pass as two launches, 12530 as one; 28/4 heads, M = 128
+    // 4543 / 4469.
     const int rem_blocks = (rows_head % MF_RCHUNK) / 32;         // 0: every chunk is full
     const bool split = L.row_chunks > 1 && rem_blocks > 0 && rem_blocks <= 4;
-    const int main_chunks = split ? L.row_chunks - 1 : L.row_chunks;
     const unsigned gx = flat_chunks > 0 ? flat_chunks : 1;
     const int64_t k_bytes = int64_t(pb.layers) * pb.hkv * total * MF_D * 2;
     const bool stream_k = k_bytes >= MF_STREAM_BYTES;
     // Max-pooling emit pass: a workgroup whose log-sum-exps are too far apart for the cheap
-    // form puts itself on a list (one for the main launch, one for the remainder launch)
-    // and a small list-driven launch right behind redoes the listed ones in the exact form.
-    uint32_t* defer_counters = reinterpret_cast<uint32_t*>(w + L.off_defer);
-    uint64_t* defer_entries = reinterpret_cast<uint64_t*>(w + L.off_defer + align_up(2 * DEFER_COUNTER_STRIDE * 4));
-    const uint32_t defer_cap = (uint32_t)(L.defer_capacity < 0xffffffffu ? L.defer_capacity : 0xffffffffu);
-    const DeferList defer_main{defer_counters, defer_entries, defer_cap};
-    const DeferList defer_rem{defer_counters + DEFER_COUNTER_STRIDE, defer_entries + L.defer_capacity, defer_cap};
-#define KVC_SCORE_MFMA(NAME, EMIT, TMAX, WQ, RCS, RC0, PM, PS, LSE, OUT)                         \
+    // form puts itself on a list, and a small list-driven launch right behind redoes the
+    // listed ones in the exact form.
+    const DeferList defer{reinterpret_cast<uint32_t*>(w + L.off_defer),
+                          reinterpret_cast<uint64_t*>(w + L.off_defer + align_up(4)),
+                          uint32_t(std::min<size_t>(L.defer_capacity, 0xffffffffu))};
+#define KVC_SCORE_MFMA(NAME, EMIT, TMAX, WQ, REM, PM, PS, LSE, OUT)                               \
   do {                                                                                           \
-    const DeferList dl_ = (RC0) == 0 ? defer_main : defer_rem;   \
-    KVC_LAUNCH(NAME, stream, \
-        (EMIT && !merge ? (stream_k && (RCS) == 1 ? score_mfma<EMIT, TMAX, WQ, true, EMIT ? LSE_PARTIAL : LSE_MERGED> : score_mfma<EMIT, TMAX, WQ, false, EMIT ? LSE_PARTIAL : LSE_MERGED>) \
-                        : (stream_k && (RCS) == 1 ? score_mfma<EMIT, TMAX, WQ, true, LSE_MERGED> : score_mfma<EMIT, TMAX, WQ, false, LSE_MERGED>))<<<dim3(gx, pb.hkv * (RCS), pb.layers), MF_THREADS, 0, stream>>>( \
+    constexpr int few_ = EMIT ? LSE_PARTIAL : LSE_MERGED;                                        \
+    const bool hint_ = (REM) == 0 && stream_k && L.row_chunks == 1;                              \
+    KVC_LAUNCH(NAME, stream,                                                                     \
+        (merge ? (hint_ ? score_mfma<EMIT, TMAX, WQ, REM, (REM) == 0, LSE_MERGED> : score_mfma<EMIT, TMAX, WQ, REM, false, LSE_MERGED>) \
+               : (hint_ ? score_mfma<EMIT, TMAX, WQ, REM, (REM) == 0, few_> : score_mfma<EMIT, TMAX, WQ, REM, false, few_>)) \
+        <<<dim3(gx, pb.hkv * L.row_chunks, pb.layers), MF_THREADS, 0, stream>>>(                 \
         qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,      \
-        RCS, RC0, PM, PS, LSE, group_max, pb.causal_tail, OUT, dl_));                            \
+        L.row_chunks, PM, PS, LSE, group_max, pb.causal_tail, OUT, defer));                      \
     if (EMIT && TMAX)                                                                            \
-      KVC_LAUNCH(NAME ",exact", stream, score_mfma_listed<WQ><<<MF_LISTED_BLOCKS, MF_THREADS, 0, stream>>>( \
+      KVC_LAUNCH(NAME ",exact", stream, score_mfma_listed<WQ, REM><<<MF_LISTED_BLOCKS, MF_THREADS, 0, stream>>>( \
           qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,    \
-          RCS, RC0, PM, PS, LSE, group_max, pb.causal_tail, OUT, dl_, (int)gx, pb.hkv * (RCS), pb.layers)); \
+          L.row_chunks, PM, PS, LSE, group_max, pb.causal_tail, OUT, defer, (int)gx, pb.hkv * L.row_chunks, pb.layers)); \
   } while (0)
-#define KVC_SCORE_MFMA_BLOCKS(NAME, EMIT, TMAX, BLOCKS, RCS, RC0, PM, PS, LSE, OUT)                  \
+#define KVC_SCORE_MFMA_WQ(NAME, EMIT, TMAX, PM, PS, LSE, OUT)                                        \
   do {                                                                                             \
-    if ((BLOCKS) <= 2) { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 1, RCS, RC0, PM, PS, LSE, OUT); }          \
-    else if ((BLOCKS) <= 4) { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 2, RCS, RC0, PM, PS, LSE, OUT); }     \
-    else { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 4, RCS, RC0, PM, PS, LSE, OUT); }                        \
-  } while (0)
-#define KVC_SCORE_MFMA_WQ(NAME, EMIT, TMAX, PM, PS, LSE, OUT)                                                   \
-  do {                                                                                                          \
-    KVC_SCORE_MFMA_BLOCKS(NAME, EMIT, TMAX, nqb0, main_chunks, 0, PM, PS, LSE, OUT);                            \
-    if (split) KVC_SCORE_MFMA_BLOCKS(NAME ",rem", EMIT, TMAX, rem_blocks, 1, main_chunks, PM, PS, LSE, OUT);    \
+    if (split && rem_blocks <= 2) { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 4, 1, PM, PS, LSE, OUT); }      \
+    else if (split) { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 4, 2, PM, PS, LSE, OUT); }                    \
+    else if (nqb0 <= 2) { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 1, 0, PM, PS, LSE, OUT); }                \
+    else if (nqb0 <= 4) { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 2, 0, PM, PS, LSE, OUT); }                \
+    else { KVC_SCORE_MFMA(NAME, EMIT, TMAX, 4, 0, PM, PS, LSE, OUT); }                               \
   } while (0)
     // up to four chunks a sequence: the emit workgroups merge their rows' partials
     // themselves (two loads a chunk and row), which is a launch of 5 us less (one prompt of 777
@@ -687,7 +683,6 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
       }
     }
 #undef KVC_SCORE_MFMA_WQ
-#undef KVC_SCORE_MFMA_BLOCKS
 #undef KVC_SCORE_MFMA
     return finish_scores(pb, fa, v, vnorm, part_all, out_stride, S, 0, pb.layers, stream);
   }

@@ -203,9 +203,8 @@ __device__ __forceinline__ float merge_few(const float* __restrict__ part_m, con
 
 // grid: ((sequence, chunk) pairs, Hkv * row_chunks, Lyr), 256 threads.  WQ = waves along the query
 // rows (each owns 2 blocks of 32 rows); the other 4/WQ waves split the key tiles.
-// A launch covers the row chunks [rc_offset, rc_offset + row_chunks) of every KV head
-// (the last, partly filled row chunk of a head may get a launch of its own with fewer
-// waves along the rows).
+// A launch covers all row chunks of every KV head; the last, partly filled one may be worked
+// with fewer waves along the rows (see the kernels below).
 //
 // Schedule of one workgroup over its macro tiles (two K buffers, tile t in
 // buffer t&1), for an even number NT of 32-key tiles per wave:
@@ -237,11 +236,25 @@ struct DeferList {
   uint64_t* entries;      // device: bx | by << 32 | bz << 56
   uint32_t capacity;
 };
+// A workgroup's LDS: declared in the kernels, so that two forms of the body can share it.
+template <bool EMIT>
+struct MfmaShared {
+  unsigned char (&kbuf)[MF_NBUF][MF_KBUF];
+  float (&red)[EMIT ? 3 : 1][8][EMIT ? MF_TILE : 1];   // EMIT: per (q block | wave, key)
+  float (&stat)[EMIT ? 1 : 4][2][32][2];               // STATS: per wave (max, sum)
+  float (&lse_s)[EMIT ? MF_RCHUNK : 4];                // EMIT: -lse2 of the row chunk
+};
+#define KVC_MFMA_SHARED(EMIT)                                                                    \
+  __shared__ __attribute__((aligned(1024))) unsigned char kbuf[MF_NBUF][MF_KBUF];                \
+  __shared__ float red[EMIT ? 3 : 1][8][EMIT ? MF_TILE : 1];                                     \
+  __shared__ float stat[EMIT ? 1 : 4][2][32][2];                                                 \
+  __shared__ __attribute__((aligned(16))) float lse_s[EMIT ? MF_RCHUNK : 4];                     \
+  const MfmaShared<EMIT> sh{kbuf, red, stat, lse_s}
 template <bool EMIT, bool TASK_MAX, int WQ, int MODE, bool STREAM, int LSE>
 __device__ __forceinline__ void score_mfma_body(
-    const PtrTable& q_tab, const PtrTable& k_tab, int batch, size_t out_layer_stride,
+    const MfmaShared<EMIT>& sh, const PtrTable& q_tab, const PtrTable& k_tab, int batch, size_t out_layer_stride,
     const SeqTable& seq, int hq, int group, int window, int total, float c2, int chunk_keys,
-    int row_chunks, int rc_offset, float* __restrict__ part_m, float* __restrict__ part_s,
+    int row_chunks, float* __restrict__ part_m, float* __restrict__ part_s,
     const float* __restrict__ lse2, int group_max, int causal, float* __restrict__ out,
     const DeferList& defer, const int bx, const int by, const int bz, const int gy, const int gz) {
   static_assert(MODE == 0 || (EMIT && TASK_MAX), "modes 1 and 2 are forms of the max-pooling emit pass");
@@ -249,10 +262,10 @@ __device__ __forceinline__ void score_mfma_body(
   constexpr int WK = 4 / WQ;        // waves along the keys
   constexpr int NT = 4 / WK;        // 32-key tiles per wave per macro tile
   constexpr bool PIPE = NT % 2 == 0;
-  __shared__ __attribute__((aligned(1024))) unsigned char kbuf[MF_NBUF][MF_KBUF];
-  __shared__ float red[EMIT ? 3 : 1][8][EMIT ? MF_TILE : 1];   // EMIT: per (q block | wave, key)
-  __shared__ float stat[EMIT ? 1 : 4][2][32][2];               // STATS: per wave (max, sum)
-  __shared__ __attribute__((aligned(16))) float lse_s[EMIT ? MF_RCHUNK : 4];   // EMIT: -lse2 of the row chunk
+  auto& kbuf = sh.kbuf;
+  auto& red = sh.red;
+  auto& stat = sh.stat;
+  auto& lse_s = sh.lse_s;
 
   // blockIdx.z = layer: one launch covers every layer, so that workgroups of the
   // next layer start as those of this one finish and only the very first ones wait
@@ -281,7 +294,7 @@ __device__ __forceinline__ void score_mfma_body(
   if (key_begin >= n) return;
   const int key_end = min(n, key_begin + chunk_keys);
   const int hkv = gy / row_chunks;
-  const int h = by / row_chunks, rc = by - h * row_chunks + rc_offset;
+  const int h = by / row_chunks, rc = by - h * row_chunks;
   const int R = group * window;
   const int row0 = rc * MF_RCHUNK;
   const int nqb = (min(R, row0 + MF_RCHUNK) - row0) / 32;   // q blocks in this row chunk
@@ -718,36 +731,63 @@ __device__ __forceinline__ void score_mfma_body(
 }
 
 // The grid-indexed kernel: workgroup (blockIdx) = ((sequence, chunk) pair, KV head x row chunk, layer).
-template <bool EMIT, bool TASK_MAX, int WQ, bool STREAM, int LSE>
+//
+// REM > 0: the last row chunk of a head has at most four blocks (G = 5 at M = 64: 8 + 2) and is
+// worked with REM waves along the rows and the others along the keys.  Such a workgroup is
+// bound by the K stream where the others are bound by the vector port, and all read the same
+// keys, so they share a launch (the launcher has the figures).
+template <bool EMIT, bool TASK_MAX, int WQ, int REM, bool STREAM, int LSE>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
-    int rc_offset, float* __restrict__ part_m, float* __restrict__ part_s, const float* __restrict__ lse2,
+    float* __restrict__ part_m, float* __restrict__ part_s, const float* __restrict__ lse2,
     int group_max, int causal, float* __restrict__ out, DeferList defer) {
-  score_mfma_body<EMIT, TASK_MAX, WQ, (EMIT && TASK_MAX) ? 1 : 0, STREAM, LSE>(
-      q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-      row_chunks, rc_offset, part_m, part_s, lse2, group_max, causal, out, defer,
+  KVC_MFMA_SHARED(EMIT);
+  constexpr int MODE = (EMIT && TASK_MAX) ? 1 : 0;
+  if constexpr (REM > 0) {
+    if ((int)blockIdx.y % row_chunks == row_chunks - 1) {
+      score_mfma_body<EMIT, TASK_MAX, REM, MODE, STREAM, LSE>(
+          sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
+          row_chunks, part_m, part_s, lse2, group_max, causal, out, defer,
+          (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, (int)gridDim.z);
+      return;
+    }
+  }
+  score_mfma_body<EMIT, TASK_MAX, WQ, MODE, STREAM, LSE>(
+      sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
+      row_chunks, part_m, part_s, lse2, group_max, causal, out, defer,
       (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, (int)gridDim.z);
 }
 
 // The list-driven kernel: redoes, in the exact form, the workgroups of the max-pooling
 // emit launch with grid (gx, gy, gz) that put themselves on the list.  Workgroup i takes
 // entries i, i + gridDim.x, ...; an empty list costs one load per workgroup.
-template <int WQ>
+template <int WQ, int REM>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
-    int rc_offset, float* __restrict__ part_m, float* __restrict__ part_s,
+    float* __restrict__ part_m, float* __restrict__ part_s,
     const float* __restrict__ lse2, int group_max, int causal,
     float* __restrict__ out, DeferList defer, int gx, int gy, int gz) {
+  KVC_MFMA_SHARED(true);
   const uint32_t listed = min(*defer.count, defer.capacity);     // appended by the launch before this one
   for (uint32_t i = blockIdx.x; i < listed; i += gridDim.x) {
     const uint64_t e = defer.entries[i];
     const int bx = (int)(uint32_t)(e & 0xffffffffu), by = (int)((e >> 32) & 0xffffffu), bz = (int)(e >> 56);
-    if (bx < gx && by < gy && bz < gz)     // entries are this library's own block indices; checked all the same
-      score_mfma_body<true, true, WQ, 2, false, LSE_EITHER>(q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window,
-                                         total, c2, chunk_keys, row_chunks, rc_offset, part_m, part_s,
-                                         lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
+    if (bx < gx && by < gy && bz < gz) {   // entries are this library's own block indices; checked all the same
+      bool rem = false;
+      if constexpr (REM > 0) {
+        rem = by % row_chunks == row_chunks - 1;
+        if (rem)
+          score_mfma_body<true, true, REM, 2, false, LSE_EITHER>(
+              sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
+              row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
+      }
+      if (!rem)
+        score_mfma_body<true, true, WQ, 2, false, LSE_EITHER>(
+            sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
+            row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
+    }
     __syncthreads();   // the next entry reuses the LDS
   }
 }
