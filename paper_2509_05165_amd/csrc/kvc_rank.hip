@@ -22,6 +22,7 @@
 // A segment that fits one tile (n <= 12288) never leaves the chip between the
 // passes: the digit-ordered staging area of one pass is the input of the next,
 // global memory sees the sweep, one read of the scores and one write of the result.
+#include "kvc_grid.h"
 #include "kvc_internal.h"
 
 namespace kvc {
@@ -405,8 +406,8 @@ __global__ __launch_bounds__(RK_THREADS) void head_rank_kernel(
             : (sizeof(Shared9) > sizeof(Shared10) ? sizeof(Shared9) : sizeof(Shared10));
   static_assert(LDS_BYTES >= sizeof(RankSweepShared), "the sweep's counters fit too");
   __shared__ __align__(16) unsigned char lds[LDS_BYTES];
-  for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * RK_THREADS + threadIdx.x; i < clear_words;
-       i += gridDim.x * gridDim.y * RK_THREADS)
+  for (int64_t i = flat_thread(blockIdx.x, blockIdx.y, gridDim.x, RK_THREADS, threadIdx.x); i < clear_words;
+       i += grid_threads(gridDim.x, gridDim.y, RK_THREADS))
     clear[i] = 0;
   const int b = blockIdx.y;
   const int n = seq.cu[b + 1] - seq.cu[b];
