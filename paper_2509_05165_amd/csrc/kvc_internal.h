@@ -113,6 +113,11 @@ __device__ __forceinline__ void wait_memory() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
+// The LDS half of it, where loads to LDS stay in flight over the barrier.
+__device__ __forceinline__ void wait_lds() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
 // Monotone map from float to unsigned: a < b  <=>  key(a) < key(b); -0 maps to
 // the same key as +0.
 __device__ __forceinline__ uint32_t float_to_ordered(float f) {

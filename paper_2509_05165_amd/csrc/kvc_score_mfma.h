@@ -541,6 +541,7 @@ __device__ __forceinline__ void score_mfma_body(
   if (EMIT) lse_s[threadIdx.x] = my_nl;
   if (ntiles > 1) issue_tile(1);
   int issued = ntiles > 1 ? 1 : 0;            // highest tile requested so far
+  wait_lds();                                 // lse_s; tile 1 stays in flight
   __syncthreads();
 
   // MODE 1: the re-centred form needs the rows of each block close to its first row;
@@ -610,8 +611,9 @@ __device__ __forceinline__ void score_mfma_body(
         if (j + 1 < NT) {
           nkb = kb + (kt + WK) * 8192;
         } else {
-          // all fragments of tile `it` are in registers: hand its buffer over
-          if (it + 1 < ntiles) wait_vmcnt<0>();
+          // tile it + 1 has landed, the fragments of tile `it` are in registers and this wave's
+          // partials of tile it - 1 in LDS: hand the buffer over
+          wait_memory();
           __syncthreads();
           if (EMIT && it > 0) epilogue(it - 1, MF_TILE);
           if (it + 2 < ntiles) { issue_tile(it + 2); issued = it + 2; }
@@ -679,6 +681,7 @@ __device__ __forceinline__ void score_mfma_body(
     if (issued < t + 1 && t + 1 < ntiles) { issue_tile(t + 1); issued = t + 1; }
     serial_tile(t, t < nfull ? MF_TILE : tail);
   }
+  wait_lds();
   __syncthreads();
   if (EMIT && ntiles > 0) epilogue(ntiles - 1, tail > 0 ? tail : MF_TILE);
   if (EMIT || track_all) break;
