@@ -629,11 +629,17 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     // The last row chunk of a head may hold few rows (G = 5 at M = 64: 256 + 64).  With four
     // waves along the rows it would cost a full 256-row pass, so when it has at most four
     // 32-row blocks the waves of its workgroups split the keys instead, in the same launch and
-    // without the streaming hint, so that K comes from memory once for all row chunks.  40/8
-    // heads, M = 64, 32 sequences of 4096: 13475 us a pass as two launches, 12530 as one; 28/4 heads, M = 128
-    // 4543 / 4469.
+    // without the streaming hint, so that K comes from memory once for all row chunks.  The
+    // order of the workgroups decides whether that pays (row_chunk_block).  Score stage in us,
+    // 32 layers, 40/8 heads, M = 64, as two launches / as one in grid order / in groups of 256 slices:
+    // 1024 tokens 86 / 78 / 62, 4096 241 / 264 / 210, 16384 905 / 1009 / 822, 65536 3546 / 3520 /
+    // 3106, 32 sequences of 4096 7172 / 6507 / 6301; 28/4 heads, M = 128, 4096 tokens 275 / 265 / 241;
+    // mean pooling, 40/8 heads, 4096 tokens 247 / 280 / 218.  (Groups of 8 / 32 / 128 / 256 / 512
+    // slices at 16384 tokens: 912 / 853 / 839 / 824 / 953.)
     const int rem_blocks = (rows_head % MF_RCHUNK) / 32;         // 0: every chunk is full
-    const bool split = L.row_chunks > 1 && rem_blocks > 0 && rem_blocks <= 4;
+    // (row_chunk_block counts the workgroups in 32 bits)
+    const int64_t workgroups = int64_t(flat_chunks) * pb.hkv * L.row_chunks * pb.layers;
+    const bool split = L.row_chunks > 1 && rem_blocks > 0 && rem_blocks <= 4 && workgroups < (int64_t(1) << 31);
     const unsigned gx = flat_chunks > 0 ? flat_chunks : 1;
     const int64_t k_bytes = int64_t(pb.layers) * pb.hkv * total * MF_D * 2;
     const bool stream_k = k_bytes >= MF_STREAM_BYTES;

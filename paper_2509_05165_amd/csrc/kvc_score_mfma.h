@@ -19,6 +19,8 @@
 // 16 different slots (all banks) although rows are exactly one bank-stride apart.
 #pragma once
 
+#include "kvc_grid.h"
+
 namespace kvc {
 namespace {
 
@@ -738,7 +740,7 @@ __device__ __forceinline__ void score_mfma_body(
 // REM > 0: the last row chunk of a head has at most four blocks (G = 5 at M = 64: 8 + 2) and is
 // worked with REM waves along the rows and the others along the keys.  Such a workgroup is
 // bound by the K stream where the others are bound by the vector port, and all read the same
-// keys, so they share a launch (the launcher has the figures).
+// keys, so they share a launch, in the order of row_chunk_block (the launcher has the figures).
 template <bool EMIT, bool TASK_MAX, int WQ, int REM, bool STREAM, int LSE>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
@@ -747,19 +749,23 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     int group_max, int causal, float* __restrict__ out, DeferList defer) {
   KVC_MFMA_SHARED(EMIT);
   constexpr int MODE = (EMIT && TASK_MAX) ? 1 : 0;
+  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
   if constexpr (REM > 0) {
-    if ((int)blockIdx.y % row_chunks == row_chunks - 1) {
+    const GridBlock at = row_chunk_block(bx + gridDim.x * (by + gridDim.y * bz), gridDim.x,
+                                         gridDim.y / row_chunks, row_chunks, gridDim.z);
+    bx = at.bx; by = at.by; bz = at.bz;
+    if (by % row_chunks == row_chunks - 1) {
       score_mfma_body<EMIT, TASK_MAX, REM, MODE, STREAM, LSE>(
           sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
           row_chunks, part_m, part_s, lse2, group_max, causal, out, defer,
-          (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, (int)gridDim.z);
+          bx, by, bz, (int)gridDim.y, (int)gridDim.z);
       return;
     }
   }
   score_mfma_body<EMIT, TASK_MAX, WQ, MODE, STREAM, LSE>(
       sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
       row_chunks, part_m, part_s, lse2, group_max, causal, out, defer,
-      (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, (int)gridDim.z);
+      bx, by, bz, (int)gridDim.y, (int)gridDim.z);
 }
 
 // The list-driven kernel: redoes, in the exact form, the workgroups of the max-pooling
