@@ -148,6 +148,10 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
 // global atomics, 7 to clear and 12 to compact.)  grid: (layers*hkv, batch), 1024 threads, a bit per
 // token of dynamic LDS; sel: int32 [layers, hkv, total] like idx.
 constexpr int64_t ORDER_LDS_TOKENS = 61440 * 8;   // 60 KB of bits: two workgroups share a compute unit
+// List entries in flight per thread: one at a time made a chain of a single long list (one head,
+// 480000 of 480000 tokens: 509 us with one, 391 with 8, 386 with 16; three launches over a map in
+// memory 373; 8 heads 1126 / 989 / 1008, the three launches 1125).
+constexpr int ORDER_LOADS = 16;
 __global__ __launch_bounds__(1024) void order_list(const int32_t* __restrict__ idx,
                                                    const int32_t* __restrict__ lengths, SeqTable seq,
                                                    int layers, int hkv, int heads_per_block, int total,
@@ -163,9 +167,13 @@ __global__ __launch_bounds__(1024) void order_list(const int32_t* __restrict__ i
   for (int w = tid; w < words; w += 1024) bits[w] = 0;
   __syncthreads();
   const int32_t* src = idx + (size_t)lh * total + tok0;
-  for (int k = tid; k < len; k += 1024) {
-    const int p = src[k];
-    if (p >= 0 && p < n) atomicOr(&bits[p >> 5], 1u << (p & 31));   // never mark outside the sequence
+  for (int k0 = tid; k0 < len; k0 += 1024 * ORDER_LOADS) {
+    int p[ORDER_LOADS];
+#pragma unroll
+    for (int j = 0; j < ORDER_LOADS; ++j) p[j] = k0 + j * 1024 < len ? src[k0 + j * 1024] : -1;
+#pragma unroll
+    for (int j = 0; j < ORDER_LOADS; ++j)
+      if (p[j] >= 0 && p[j] < n) atomicOr(&bits[p[j] >> 5], 1u << (p[j] & 31));   // never mark outside the sequence
   }
   __syncthreads();
   int32_t* out = sel + (size_t)lh * total + tok0;

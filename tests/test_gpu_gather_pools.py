@@ -21,6 +21,7 @@ pytestmark = pytest.mark.gpu
     (60, 8, [70, 700], 700),              # 262144 rows and more: 64 a wave
     (2, 3, [32767, 1], 32767),
     (1, 2, [32769, 31, 33], 32769),       # two stretches of words
+    (3, 2, [16384, 16385, 16383], 16385), # a list is marked in steps of 16384 entries
     (1, 1, [491520], 491520),             # the longest list that is ordered in LDS
     (1, 1, [491521, 40], 491521),         # and the shortest that is not
 ])
