@@ -187,9 +187,12 @@ const char* kvc_last_error(void);
 int64_t kvc_budget(int32_t keep_percent, int32_t layers, int64_t n);
 
 /* Bytes of device workspace that suffice for kvc_compress and for every stage
- * entry point on this problem.  max_seqlen = max_b N_b.  The workspace must be
- * 256-byte aligned; its contents on entry are irrelevant and on exit
- * unspecified. */
+ * entry point on this problem, on their fastest routes.  max_seqlen = max_b N_b.
+ * The workspace must be 256-byte aligned; its contents on entry are irrelevant
+ * and on exit unspecified.  The size never falls as max_seqlen or total_tokens
+ * grows.  Calls take a smaller workspace as long as each stage finds the least it
+ * runs in: kvc_score then takes fewer layers at a time (shapes outside bf16, d = 128,
+ * M = 32, 64, 128 or 256 k), and in the end kernels that need less and are slow. */
 kvc_status kvc_workspace_size(const kvc_params* params, int64_t total_tokens,
                               int64_t max_seqlen, size_t* bytes);
 

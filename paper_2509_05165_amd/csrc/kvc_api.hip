@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument validation, workspace carving and the
 // stream-ordered sequence of stage launches.  All checks run before the first
 // HIP call so every error path can be exercised without a GPU.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -174,10 +175,12 @@ static kvc_status check_budget(const Problem& pb, const int64_t* cu, const int64
 }
 
 // Workspace of kvc_compress: [S][idx][S_sorted][I][tau] (each only when the
-// caller gave no tap for it), the select stage's scratch (the rank kernel clears it, so it
-// lies outside what that kernel works in) and one region shared by the stages.
+// caller gave no tap for it) and one region shared by the stages.  The select stage's scratch lies
+// in that region behind what the rank kernel works in, which then clears it on the way; where
+// the region is too small for that (`least` is what the stages need one by one), it lies in
+// front and takes a launch of its own to clear.
 struct CompressLayout {
-  size_t off_S, off_idx, off_sorted, off_I, off_tau, off_select, off_stage, total;
+  size_t off_S, off_idx, off_sorted, off_I, off_tau, off_stage, total, least;
 };
 
 static CompressLayout compress_layout(const Problem& pb) {
@@ -189,16 +192,11 @@ static CompressLayout compress_layout(const Problem& pb) {
   L.off_sorted = cur; cur += align_up(lht * 4);
   L.off_I = cur;      cur += align_up(size_t(pb.layers) * size_t(pb.total) * 4);
   L.off_tau = cur;    cur += align_up(size_t(pb.batch) * 4);
-  const size_t s = select_workspace_bytes(pb);
-  L.off_select = cur; cur += align_up(s);
   L.off_stage = cur;
-  size_t stage = score_workspace_bytes(pb);
-  size_t r = rank_workspace_bytes(pb);
-  if (r > stage) stage = r;
-  size_t g = gather_workspace_bytes(pb);
-  if (g > stage) stage = g;
-  cur += align_up(stage);
-  L.total = cur;
+  const size_t select = select_workspace_bytes(pb);
+  const size_t others = std::max(rank_workspace_bytes(pb), gather_workspace_bytes(pb));
+  L.least = cur + align_up(std::max({others, score_workspace_least(pb), select}));
+  L.total = cur + align_up(std::max({others, score_workspace_bytes(pb), rank_workspace_used(pb) + select}));
   return L;
 }
 
@@ -290,9 +288,9 @@ kvc_status kvc_score(const kvc_params* params, const void* const* q, const void*
   if ((st = check_ptr_table(k, pb.layers, "k")) != KVC_OK) return st;
   if (pb.value_norm && (st = check_ptr_table(v, pb.layers, "v")) != KVC_OK) return st;
   if (!S) { set_error("S is NULL"); return KVC_ERR_INVALID_ARG; }
-  if ((st = check_ws(workspace, workspace_bytes, score_workspace_bytes(pb))) != KVC_OK) return st;
+  if ((st = check_ws(workspace, workspace_bytes, score_workspace_least(pb))) != KVC_OK) return st;
   if (pb.total == 0) return KVC_OK;
-  return launch_score(pb, q, k, pb.value_norm ? v : nullptr, S, workspace,
+  return launch_score(pb, q, k, pb.value_norm ? v : nullptr, S, workspace, workspace_bytes,
                       static_cast<hipStream_t>(stream));
 }
 
@@ -417,7 +415,7 @@ kvc_status kvc_compress(const kvc_params* params, const kvc_inputs* in, const kv
   }
   if (total_budget > 0 && !out->k_out) { set_error("k_out is NULL"); return KVC_ERR_INVALID_ARG; }
   CompressLayout L = compress_layout(pb);
-  if ((st = check_ws(workspace, workspace_bytes, L.total)) != KVC_OK) return st;
+  if ((st = check_ws(workspace, workspace_bytes, L.least)) != KVC_OK) return st;
 
   char* ws = static_cast<char*>(workspace);
   float* S = out->scores ? out->scores : reinterpret_cast<float*>(ws + L.off_S);
@@ -425,20 +423,24 @@ kvc_status kvc_compress(const kvc_params* params, const kvc_inputs* in, const kv
   float* sorted = out->s_sorted ? out->s_sorted : reinterpret_cast<float*>(ws + L.off_sorted);
   float* I = out->composite ? out->composite : reinterpret_cast<float*>(ws + L.off_I);
   float* tau = out->tau ? out->tau : reinterpret_cast<float*>(ws + L.off_tau);
-  void* select = ws + L.off_select;
-  void* stage = ws + L.off_stage;
+  char* stage = ws + L.off_stage;
+  const size_t room = workspace_bytes - L.off_stage;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   if (pb.total > 0) {
-    if ((st = launch_score(pb, in->q, in->k, pb.value_norm ? in->v : nullptr, S, stage, s)) !=
+    if ((st = launch_score(pb, in->q, in->k, pb.value_norm ? in->v : nullptr, S, stage, room, s)) !=
         KVC_OK)
       return st;
-    if ((st = launch_head_rank(pb, S, idx, sorted, stage, static_cast<uint32_t*>(select),
-                               select_clear_words(pb), s)) != KVC_OK)
+    const size_t behind = rank_workspace_used(pb);
+    const bool by_rank = behind + select_workspace_bytes(pb) <= room;
+    char* select = by_rank ? stage + behind : stage;
+    if ((st = launch_head_rank(pb, S, idx, sorted, stage, by_rank ? reinterpret_cast<uint32_t*>(select) : nullptr,
+                               by_rank ? select_clear_words(pb) : 0, s)) != KVC_OK)
       return st;
+    if (!by_rank && (st = launch_select_clear(pb, select, s)) != KVC_OK) return st;
     st = launch_composite_select(pb, sorted, I, in->budget, tau, out->lengths, out->offsets, select, s);
   } else {
-    st = launch_global_select(pb, I, in->budget, tau, out->lengths, out->offsets, select, s);
+    st = launch_global_select(pb, I, in->budget, tau, out->lengths, out->offsets, stage, s);
   }
   if (st != KVC_OK) return st;
   if (total_budget > 0) {

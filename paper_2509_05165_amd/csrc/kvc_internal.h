@@ -56,11 +56,15 @@ void prof_end(hipStream_t stream);
 // ---------------------------------------------------------------------------
 // Stage launchers (each enqueues on `stream`, validates nothing).
 // ---------------------------------------------------------------------------
+// what is reserved for the stage, and the least it runs in (slower)
 size_t score_workspace_bytes(const Problem& pb);
+size_t score_workspace_least(const Problem& pb);
+// room: bytes at ws, at least score_workspace_least
 kvc_status launch_score(const Problem& pb, const void* const* q, const void* const* k,
-                        const void* const* v, float* S, void* ws, hipStream_t stream);
+                        const void* const* v, float* S, void* ws, size_t room, hipStream_t stream);
 
 size_t rank_workspace_bytes(const Problem& pb);
+size_t rank_workspace_used(const Problem& pb);   // of it, what the kernel touches at these lengths
 // clear (may be null): words that the kernel also sets to zero (the select stage's scratch)
 kvc_status launch_head_rank(const Problem& pb, const float* S, int32_t* idx, float* S_sorted,
                             void* ws, uint32_t* clear, int clear_words, hipStream_t stream);
@@ -76,6 +80,7 @@ kvc_status launch_global_select(const Problem& pb, const float* I, const int64_t
 // Composite and selection of kvc_compress: S_sorted must be descending in every row (the
 // composite then is, too) and the first select_clear_words words of ws zero.
 int select_clear_words(const Problem& pb);
+kvc_status launch_select_clear(const Problem& pb, void* ws, hipStream_t stream);
 kvc_status launch_composite_select(const Problem& pb, const float* S_sorted, float* I,
                                    const int64_t* budget, float* tau, int32_t* lengths,
                                    int64_t* offsets, void* ws, hipStream_t stream);

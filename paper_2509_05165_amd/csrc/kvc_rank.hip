@@ -544,6 +544,9 @@ size_t rank_workspace_bytes(const Problem& pb) {
   return align_up(lht * 8) * 2;
 }
 
+// segments of one tile stay in LDS
+size_t rank_workspace_used(const Problem& pb) { return pb.max_seqlen > RK_TILE ? rank_workspace_bytes(pb) : 0; }
+
 kvc_status launch_head_rank(const Problem& pb, const float* S, int32_t* idx, float* S_sorted,
                             void* ws, uint32_t* clear, int clear_words, hipStream_t stream) {
   const size_t lht = size_t(pb.layers) * pb.hkv * size_t(pb.total);

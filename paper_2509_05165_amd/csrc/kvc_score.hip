@@ -437,59 +437,85 @@ inline int mfma_chunk(const Problem& pb, int row_chunks) {
 constexpr int64_t MF_STREAM_BYTES = int64_t(1) << 30;
 constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact emit launch (two per compute unit)
 
+// The ways through the stage (see the top of the file).
+enum ScoreRoute { SCORE_QUERY_STATIONARY, SCORE_KEY_STATIONARY, SCORE_PLAIN };
+
 struct ScoreLayout {
+  ScoreRoute route;
   size_t off_m, off_s, off_lse, off_part, off_vnorm, off_defer, total, part_layer;
   size_t defer_capacity;   // entries per defer list: an upper bound of the workgroups of one emit launch
   int max_chunks, rows_layer, row_chunks, layers_held;
 };
 
-ScoreLayout score_layout(const Problem& pb) {
+// Workspace of a route that holds the statistics, log-sum-exps, group partials and value norms of
+// `layers` layers at once and has at least `chunk` keys in a chunk.
+ScoreLayout score_layout(const Problem& pb, ScoreRoute route, int layers, int chunk) {
   ScoreLayout L{};
+  L.route = route;
+  L.layers_held = layers;
   L.rows_layer = pb.batch * pb.hq * pb.window;
-  const bool mfma = mfma_supported(pb);
-  L.row_chunks = mfma ? (pb.group * pb.window + MF_RCHUNK - 1) / MF_RCHUNK : 1;
-  // The query-stationary path runs all layers in one launch and keeps the statistics,
-  // log-sum-exps and group partials of every layer.
-  const size_t lse_bytes = pb.dtype == KVC_F32 ? 8 : 4;   // float32 keeps the rest of its log-sum-exps, too
-  size_t reserved = 0;
-  if (mfma) {
-    L.layers_held = pb.layers;
-    L.max_chunks = std::max(1, int((pb.max_seqlen + MF_CHUNK - 1) / MF_CHUNK));
-  } else {
-    // The key-stationary path has a chunk per workgroup.  It takes as many layers at once as
-    // keep the statistics below what the rank stage asks of the same workspace anyway (or
-    // below 64 MB), and at least one.  The space is reserved by that bound and not by the layers
-    // that fit it, so that it never shrinks when max_seqlen grows.
-    const int keys = tile_keys(tile_ksteps(pb.dtype, pb.d * esize(pb.dtype) / 16));
-    L.max_chunks = std::max(1, int((pb.max_seqlen + keys - 1) / keys));
-    const size_t per_layer = size_t(L.rows_layer) * (8 * size_t(L.max_chunks) + lse_bytes);
-    const size_t bound = std::max(size_t(64) << 20, size_t(pb.layers) * pb.hkv * size_t(pb.total) * 16);
-    const size_t stats = std::max(per_layer, std::min(bound, pb.layers * per_layer));
-    // (the merge kernels count the rows of a launch in 32 bits)
-    L.layers_held = int(std::min<size_t>(stats / per_layer, std::max<size_t>(1, (size_t(1) << 30) / L.rows_layer)));
-    reserved = align_up(stats) + 3 * align_up(1);         // each of the three arrays is rounded up
-  }
+  L.row_chunks = route == SCORE_QUERY_STATIONARY ? (pb.group * pb.window + MF_RCHUNK - 1) / MF_RCHUNK : 1;
+  L.max_chunks = std::max(1, int((pb.max_seqlen + chunk - 1) / chunk));
+  const size_t rows = size_t(L.rows_layer) * layers;
   size_t cur = 0;
-  L.off_m = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
-  L.off_s = cur;    cur += align_up(size_t(L.rows_layer) * L.layers_held * L.max_chunks * 4);
-  L.off_lse = cur;  cur += align_up(size_t(L.rows_layer) * L.layers_held * lse_bytes);
-  cur = std::max(cur, reserved);
+  L.off_m = cur;    cur += align_up(rows * L.max_chunks * 4);
+  L.off_s = cur;    cur += align_up(rows * L.max_chunks * 4);
+  // the key-stationary path keeps the rest of its float32 log-sum-exps, too
+  L.off_lse = cur;  cur += align_up(rows * (route == SCORE_KEY_STATIONARY && pb.dtype == KVC_F32 ? 8 : 4));
   L.off_part = cur;
   // partials are needed when row chunks must be combined, or when more than 8
   // KV heads make the in-place finish impossible
   L.part_layer = size_t(L.row_chunks) * pb.hkv * size_t(pb.total);
-  if (L.row_chunks > 1 || pb.hkv > 8) cur += align_up(L.part_layer * pb.layers * 4);
+  if (L.row_chunks > 1 || pb.hkv > 8) cur += align_up(L.part_layer * layers * 4);
   L.off_vnorm = cur;
-  if (pb.value_norm) cur += align_up(size_t(pb.layers) * pb.hkv * size_t(pb.total) * 4);
-  // defer list of the emit pass (query-stationary path): a counter, then block indices; a launch has at most (total/chunk + batch) x hkv x row_chunks x layers workgroups
+  if (pb.value_norm) cur += align_up(size_t(layers) * pb.hkv * size_t(pb.total) * 4);
+  // defer list of the emit pass (query-stationary path): a counter, then block indices; a launch has
+  // at most (total/chunk + batch) x hkv x row_chunks x layers workgroups
   L.off_defer = cur;
-  L.defer_capacity = 0;
-  if (mfma) {
-    L.defer_capacity = (size_t(pb.total) / MF_CHUNK + size_t(pb.batch)) * pb.hkv * L.row_chunks * pb.layers;
+  if (route == SCORE_QUERY_STATIONARY) {
+    L.defer_capacity = (size_t(pb.total) / MF_CHUNK + size_t(pb.batch)) * pb.hkv * L.row_chunks * layers;
     cur += align_up(4) + align_up(L.defer_capacity * 8);
   }
   L.total = cur;
   return L;
+}
+
+// The query-stationary path runs all layers in one launch.
+ScoreLayout query_layout(const Problem& pb) {
+  return score_layout(pb, SCORE_QUERY_STATIONARY, pb.layers, MF_CHUNK);
+}
+
+// The key-stationary path has a chunk per workgroup.  It takes as many layers at once as keep the
+// statistics below what the rank stage asks of the same workspace anyway (or below 64 MB), and at
+// least one.
+inline int tile_chunk(const Problem& pb) { return tile_keys(tile_ksteps(pb.dtype, pb.d * esize(pb.dtype) / 16)); }
+inline size_t tile_stats_layer(const Problem& pb) {
+  const size_t chunks = std::max<int64_t>(1, (pb.max_seqlen + tile_chunk(pb) - 1) / tile_chunk(pb));
+  return size_t(pb.batch) * pb.hq * pb.window * (8 * chunks + (pb.dtype == KVC_F32 ? 8 : 4));
+}
+inline size_t tile_stats(const Problem& pb) {
+  const size_t bound = std::max(size_t(64) << 20, size_t(pb.layers) * pb.hkv * size_t(pb.total) * 16);
+  return std::max(tile_stats_layer(pb), std::min(bound, pb.layers * tile_stats_layer(pb)));
+}
+
+// The route that a call with `room` bytes (at least score_workspace_least) takes.
+ScoreLayout choose_layout(const Problem& pb, const void* const* q, const void* const* k, size_t room) {
+  if (mfma_supported(pb)) return query_layout(pb);
+  // the 16-byte loads of the key-stationary kernels need rows at 16-byte addresses
+  bool aligned = true;
+  for (int l = 0; l < pb.layers; ++l)
+    aligned = aligned && (reinterpret_cast<uintptr_t>(q[l]) | reinterpret_cast<uintptr_t>(k[l])) % 16 == 0;
+  if (aligned) {
+    // (the merge kernels count the rows of a launch in 32 bits)
+    const size_t rows_layer = size_t(pb.batch) * pb.hq * pb.window;
+    int layers = int(std::min<size_t>(tile_stats(pb) / tile_stats_layer(pb),
+                                      std::max<size_t>(1, (size_t(1) << 30) / rows_layer)));
+    for (; layers > 0; --layers) {
+      const ScoreLayout L = score_layout(pb, SCORE_KEY_STATIONARY, layers, tile_chunk(pb));
+      if (L.total <= room) return L;
+    }
+  }
+  return score_layout(pb, SCORE_PLAIN, 1, GEN_CHUNK);
 }
 
 // Value norms (vnorm != null) and finish of the layers [l0, l0 + layers), one launch each; `part`
@@ -583,11 +609,23 @@ kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* cons
 
 }  // namespace
 
-size_t score_workspace_bytes(const Problem& pb) { return score_layout(pb).total; }
+size_t score_workspace_least(const Problem& pb) {
+  return mfma_supported(pb) ? query_layout(pb).total : score_layout(pb, SCORE_PLAIN, 1, GEN_CHUNK).total;
+}
+
+// Space for the key-stationary path is reserved by the bound on the statistics and for the
+// partials and norms of every layer, not by the layers that fit it, so that it never shrinks when
+// max_seqlen grows.
+size_t score_workspace_bytes(const Problem& pb) {
+  if (mfma_supported(pb)) return query_layout(pb).total;
+  const size_t per_token = size_t(pb.layers) * pb.hkv * size_t(pb.total) * 4;
+  return align_up(tile_stats(pb)) + 3 * align_up(1) +    // each of the three arrays is rounded up
+         (pb.hkv > 8 ? align_up(per_token) : 0) + (pb.value_norm ? align_up(per_token) : 0);
+}
 
 kvc_status launch_score(const Problem& pb, const void* const* q, const void* const* k,
-                        const void* const* v, float* S, void* ws, hipStream_t stream) {
-  const ScoreLayout L = score_layout(pb);
+                        const void* const* v, float* S, void* ws, size_t room, hipStream_t stream) {
+  const ScoreLayout L = choose_layout(pb, q, k, room);
   char* w = static_cast<char*>(ws);
   float* part_m = reinterpret_cast<float*>(w + L.off_m);
   float* part_s = reinterpret_cast<float*>(w + L.off_s);
@@ -600,14 +638,14 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
   fa.group_max = pb.agg_group == KVC_AGG_MAX; fa.add_head_mean = pb.add_head_mean;
   fa.task_max = pb.agg_task == KVC_AGG_MAX;
   // a window above 256 task tokens spreads every query head over window/256 row chunks
-  fa.chunks_per_head = (mfma_supported(pb) && pb.window > MF_RCHUNK) ? pb.window / MF_RCHUNK : 1;
+  const bool mfma = L.route == SCORE_QUERY_STATIONARY;
+  fa.chunks_per_head = (mfma && pb.window > MF_RCHUNK) ? pb.window / MF_RCHUNK : 1;
   fa.group_norm = fa.group_max ? 1.f : 1.f / float(pb.group);
   fa.inv_window = 1.f / float(pb.window);
   fa.keep_first = pb.keep_first; fa.keep_last = pb.keep_last;
   const float c2 = pb.scale * LOG2E;
   const int total = int(pb.total);
   const int task_max = pb.agg_task == KVC_AGG_MAX, group_max = pb.agg_group == KVC_AGG_MAX;
-  const bool mfma = mfma_supported(pb);
   const int chunk = mfma ? mfma_chunk(pb, L.row_chunks) : GEN_CHUNK;
   const int chunks = int((pb.max_seqlen + chunk - 1) / chunk);
   const int rows_per_seq = pb.hq * pb.window;
@@ -694,11 +732,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
   }
 
   // Everything else: the key-stationary path, as many layers at a time as the workspace holds.
-  // Its 16-byte loads need rows at 16-byte addresses; the plain kernels below take any.
-  bool aligned = true;
-  for (int l = 0; l < pb.layers; ++l)
-    aligned = aligned && (reinterpret_cast<uintptr_t>(q[l]) | reinterpret_cast<uintptr_t>(k[l])) % 16 == 0;
-  if (aligned) {
+  if (L.route == SCORE_KEY_STATIONARY) {
     const size_t s_stride = size_t(pb.hkv) * total;
     for (int l0 = 0; l0 < pb.layers; l0 += L.layers_held) {
       const int layers = std::min(L.layers_held, pb.layers - l0);

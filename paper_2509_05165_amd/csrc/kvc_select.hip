@@ -565,14 +565,21 @@ static kvc_status select_passes(const Problem& pb, const float* I, const BudgetT
   return KVC_OK;
 }
 
+kvc_status launch_select_clear(const Problem& pb, void* ws, hipStream_t stream) {
+  const int words = select_clear_words(pb);
+  KVC_LAUNCH("select_clear", stream, select_clear<<<(words + 255) / 256, 256, 0, stream>>>(
+      static_cast<uint32_t*>(ws), words));
+  return KVC_OK;
+}
+
 kvc_status launch_global_select(const Problem& pb, const float* I, const int64_t* budget,
                                 float* tau, int32_t* lengths, int64_t* offsets, void* ws,
                                 hipStream_t stream) {
   const SelectLayout L = select_layout(pb);
   char* w = static_cast<char*>(ws);
   const BudgetTable bt = open_budgets(pb, budget);
-  KVC_LAUNCH("select_clear", stream, select_clear<<<(L.words + 255) / 256, 256, 0, stream>>>(
-      reinterpret_cast<uint32_t*>(w), L.words));
+  const kvc_status st = launch_select_clear(pb, ws, stream);
+  if (st != KVC_OK) return st;
   if (pb.max_seqlen > 0) return select_passes(pb, I, bt, 0, false, tau, lengths, offsets, w, stream);
   KVC_LAUNCH("select_finalize", stream, select_finalize<<<pb.batch, SEL_THREADS, 0, stream>>>(
       pb.seq, pb.sel_rows, pb.min_per_layer, bt, reinterpret_cast<SelState*>(w + L.off_state),
