@@ -33,6 +33,8 @@
  * pointer after return and never synchronises the stream: all work is
  * enqueued on `stream` (a hipStream_t passed as void*, NULL = default stream).
  * Results are valid once the stream has been synchronised by the caller.
+ * Device pointers need the alignment of their elements (the workspace 256 bytes).
+ * kvc_score is some 200 times slower where a q[l] or k[l] is not 16-byte aligned.
  *
  * Layouts (row-major, innermost last):
  *   q[l]   device, [Bt, Hq, M, d]       task queries of layer l (already

@@ -32,7 +32,9 @@ constexpr int GA_WAVES = 4096;   // waves that a launch should have (16 per comp
 // Every byte the gather moves is touched once, so loads and stores carry the
 // streaming (non-temporal) hint: measured 0.70 -> 0.63 ms at the 128k shape,
 // most of it from the stores.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// (Aligned to 2: caches and pools start at any address that suits their elements; the instructions
+// are the same 16-byte ones.)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(2)));
 __device__ __forceinline__ u32x4 load_stream(const u32x4* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void store_stream(u32x4* p, u32x4 v) { __builtin_nontemporal_store(v, p); }
 
@@ -65,7 +67,7 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
     PtrTable k_tab, PtrTable v_tab, int has_v, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ lengths, const int64_t* __restrict__ offsets, SeqTable seq,
     int layers, int hkv, int heads_per_block, int total, int pieces, int wave_rows, int64_t pool_rows,
-    uint4* __restrict__ k_out, uint4* __restrict__ v_out) {
+    u32x4* __restrict__ k_out, u32x4* __restrict__ v_out) {
   const int lane = threadIdx.x & 63;
   const int64_t wave_id = (int64_t)blockIdx.x * (GA_THREADS / 64) + (threadIdx.x >> 6);
   const int64_t wave_count = (int64_t)gridDim.x * (GA_THREADS / 64);
@@ -103,8 +105,8 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
           const int p = idx[((size_t)l * hkv + h) * total + seq.cu[b] + kk];
           if (p >= 0 && p < n_b) {                   // never read outside the cache
             const size_t src = ((size_t)h * total + seq.cu[b] + p) * pieces;
-            ksrc = reinterpret_cast<uint64_t>(static_cast<const uint4*>(k_tab.p[l]) + src);
-            if (has_v) vsrc = reinterpret_cast<uint64_t>(static_cast<const uint4*>(v_tab.p[l]) + src);
+            ksrc = reinterpret_cast<uint64_t>(static_cast<const u32x4*>(k_tab.p[l]) + src);
+            if (has_v) vsrc = reinterpret_cast<uint64_t>(static_cast<const u32x4*>(v_tab.p[l]) + src);
           }
         }
       }
@@ -134,8 +136,8 @@ __global__ __launch_bounds__(GA_THREADS) void gather_kernel(
 #pragma unroll
       for (int j = 0; j < GA_BATCH; ++j) {
         const int64_t orow = group * wave_rows + (s0 + j) * rows_per_step + sub;
-        if (kp[j]) store_stream(reinterpret_cast<u32x4*>(k_out) + ((size_t)orow * pieces + piece), kd[j]);
-        if (vp[j]) store_stream(reinterpret_cast<u32x4*>(v_out) + ((size_t)orow * pieces + piece), vd[j]);
+        if (kp[j]) store_stream(k_out + ((size_t)orow * pieces + piece), kd[j]);
+        if (vp[j]) store_stream(v_out + ((size_t)orow * pieces + piece), vd[j]);
       }
     }
   }
@@ -353,7 +355,7 @@ kvc_status launch_gather(const Problem& pb, const void* const* k, const void* co
 #define KVC_GATHER(BATCH)                                                                            \
   KVC_LAUNCH("gather_kernel", stream, gather_kernel<BATCH><<<(unsigned)blocks, GA_THREADS, 0, stream>>>( \
       kt, vt, v != nullptr, idx, lengths, offsets, pb.seq, pb.layers, pb.hkv, hpb, int(pb.total),    \
-      pieces, wave_rows, pool_rows, static_cast<uint4*>(k_out), static_cast<uint4*>(v_out)))
+      pieces, wave_rows, pool_rows, static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out)))
   if (wave_rows < 64) KVC_GATHER(4);
   else KVC_GATHER(2);
 #undef KVC_GATHER

@@ -11,8 +11,9 @@
 //   kvc_score_mfma.h  query-stationary matrix-core kernels: bf16, d = 128, windows of 32, 64,
 //                     128 or a multiple of 256
 //   kvc_score_tile.h  key-stationary matrix-core kernels: every other shape, both types
-//   the plain kernels below: rows that do not start at 16-byte addresses, which the
-//                     16-byte loads of the others need
+//   the plain kernels below: q or k that do not start at 16-byte addresses, which the 16-byte loads
+//                     of the others need (K goes straight into LDS), and workspaces too small for
+//                     a layer of the key-stationary kernels
 #include <algorithm>
 
 #include "kvc_internal.h"
@@ -376,7 +377,8 @@ template <typename T>
 __global__ __launch_bounds__(256) void value_norm_kernel(PtrTable v_tab, size_t rows, int d,
                                                          float* __restrict__ w) {
   constexpr int PER = 16 / sizeof(T);          // elements per 16-byte piece
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  // (2: rows start at any address that suits their elements; the load is the same 16-byte one)
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(2)));
   // blockIdx.y = entry of the pointer table (a layer); its weights follow those of the one before
   const T* __restrict__ v = static_cast<const T*>(v_tab.p[blockIdx.y]);
   w += (size_t)blockIdx.y * rows;
@@ -444,7 +446,7 @@ struct ScoreLayout {
   ScoreRoute route;
   size_t off_m, off_s, off_lse, off_part, off_vnorm, off_defer, total, part_layer;
   size_t defer_capacity;   // entries per defer list: an upper bound of the workgroups of one emit launch
-  int max_chunks, rows_layer, row_chunks, layers_held;
+  int chunk, max_chunks, rows_layer, row_chunks, layers_held;
 };
 
 // Workspace of a route that holds the statistics, log-sum-exps, group partials and value norms of
@@ -452,6 +454,7 @@ struct ScoreLayout {
 ScoreLayout score_layout(const Problem& pb, ScoreRoute route, int layers, int chunk) {
   ScoreLayout L{};
   L.route = route;
+  L.chunk = chunk;
   L.layers_held = layers;
   L.rows_layer = pb.batch * pb.hq * pb.window;
   L.row_chunks = route == SCORE_QUERY_STATIONARY ? (pb.group * pb.window + MF_RCHUNK - 1) / MF_RCHUNK : 1;
@@ -500,11 +503,11 @@ inline size_t tile_stats(const Problem& pb) {
 
 // The route that a call with `room` bytes (at least score_workspace_least) takes.
 ScoreLayout choose_layout(const Problem& pb, const void* const* q, const void* const* k, size_t room) {
-  if (mfma_supported(pb)) return query_layout(pb);
-  // the 16-byte loads of the key-stationary kernels need rows at 16-byte addresses
+  // the matrix-core kernels load 16 bytes at a time, K straight into LDS: rows at 16-byte addresses
   bool aligned = true;
   for (int l = 0; l < pb.layers; ++l)
     aligned = aligned && (reinterpret_cast<uintptr_t>(q[l]) | reinterpret_cast<uintptr_t>(k[l])) % 16 == 0;
+  if (aligned && mfma_supported(pb)) return query_layout(pb);
   if (aligned) {
     // (the merge kernels count the rows of a launch in 32 bits)
     const size_t rows_layer = size_t(pb.batch) * pb.hq * pb.window;
@@ -515,7 +518,11 @@ ScoreLayout choose_layout(const Problem& pb, const void* const* q, const void* c
       if (L.total <= room) return L;
     }
   }
-  return score_layout(pb, SCORE_PLAIN, 1, GEN_CHUNK);
+  // (what is reserved for the query-stationary path holds one layer in its chunks, and often in
+  // shorter ones; for the other shapes the least is one layer in the shortest)
+  int chunk = GEN_CHUNK;
+  while (chunk < MF_CHUNK && score_layout(pb, SCORE_PLAIN, 1, chunk).total > room) chunk *= 2;
+  return score_layout(pb, SCORE_PLAIN, 1, chunk);
 }
 
 // Value norms (vnorm != null) and finish of the layers [l0, l0 + layers), one launch each; `part`
@@ -646,7 +653,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
   const float c2 = pb.scale * LOG2E;
   const int total = int(pb.total);
   const int task_max = pb.agg_task == KVC_AGG_MAX, group_max = pb.agg_group == KVC_AGG_MAX;
-  const int chunk = mfma ? mfma_chunk(pb, L.row_chunks) : GEN_CHUNK;
+  const int chunk = mfma ? mfma_chunk(pb, L.row_chunks) : L.chunk;
   const int chunks = int((pb.max_seqlen + chunk - 1) / chunk);
   const int rows_per_seq = pb.hq * pb.window;
 
