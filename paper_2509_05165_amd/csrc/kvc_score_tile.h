@@ -63,11 +63,14 @@ __device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
 // What bounds it is latency inside a wave (fragment reads, products, the vector work on their
 // result, one after the other) and the vector port, so registers are held to what four waves per
 // SIMD (rows of up to 160 bytes), three (256) or two (512) leave, masks stay out of the common
-// path and the tile loads take 32-bit offsets from a scalar base.  200 task tokens, 32 heads
-// of 128 and 8192 tokens x 32 layers, both passes: 1126 us with two waves and the mask
-// looked at per element, 1062 with three, 989 now (0.87 PFLOP/s); heads of 64 in a ragged batch of
-// 14k tokens 206, 202, 187.  A form with two accumulator sets and prefetched fragments, one
-// wave less, took 1075 and 262.
+// path and the tile loads take 32-bit offsets from a scalar base.  The emit pass also waits for
+// what it has only just asked for: the compiler cannot see that wait_memory covers the key
+// fragments and puts its own vmcnt(0) in front of the first product of every tile, behind the loads
+// of the next one, and load_nl negates what it loads at once; the tile loads run ahead in the
+// statistics pass only.  200 task tokens, 32 heads of 128 and 8192 tokens x 32 layers, both passes:
+// 1126 us with two waves and the mask looked at per element, 1062 with three, 989 without the
+// mask, 972 now (0.88 PFLOP/s); heads of 64 in a ragged batch of 14k tokens 206, 202, 187, 186.  A
+// form with two accumulator sets and prefetched fragments, one wave less, took 1075 and 262.
 template <typename T, int KS, int KB, bool EMIT, bool TASK_MAX>
 __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 : 4) void score_tile(
     PtrTable q_tab, PtrTable k_tab, SeqTable seq, TileArgs a, float* __restrict__ part_m,
@@ -79,6 +82,13 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   __shared__ float2 stat[EMIT ? 1 : 2][4][EMIT ? 1 : TL_ROWS];
   // EMIT: minus the log-sum-exps of a tile's rows; float32 keeps what rounding took from them, too
   constexpr bool REST = EMIT && sizeof(T) == 4;
+  // An opaque copy of the lane keeps what a tile load's offsets are made of out of the live set:
+  // otherwise the emit forms whose registers are used up spill it (2 to 15 registers), and every
+  // reload waits for the loads before it between two loads of a tile.  Score stage, 16 layers of
+  // 4096 tokens, 32/8 heads, in us without / with: bf16 d = 80 79 / 71, 128 (M = 200) 252 / 245,
+  // 256 207 / 189, float32 d = 64 327 / 298, 128 613 / 577.  The two forms with registers to
+  // spare gain nothing (bf16 d = 64 54.0 / 54.2) or lose (float32 d = 256 1344 / 1369).
+  constexpr bool OPAQUE = EMIT && KS < 32 && (KS > 4 || sizeof(T) == 4);
   __shared__ __attribute__((aligned(16))) float nls[EMIT ? 2 : 1][EMIT ? TL_ROWS : 4];
   __shared__ __attribute__((aligned(16))) float rests[REST ? 2 : 1][REST ? TL_ROWS : 4];
 
@@ -122,6 +132,8 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
     const uint32_t dst = __builtin_amdgcn_readfirstlane(qtile_lds + (uint32_t)(t & 1) * (TL_ROWS * PS * 16));
     // scalar base: the first row of the tile; the others follow within 64 rows of it
     bool real;
+    int ln = lane;
+    if (OPAQUE) asm volatile("" : "+v"(ln));
     const int first = __builtin_amdgcn_readfirstlane(source_row(t * TL_ROWS, real));
     const uint64_t addr = reinterpret_cast<uint64_t>(q_head) + (uint64_t)(uint32_t)first * (uint32_t)(P * 16);
     const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(addr >> 32)) << 32) |
@@ -130,7 +142,7 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
     for (int i = 0; i < DMA; ++i) {
       const int j = i * 4 + wave;                        // wave-uniform
       if (j < PS) {
-        const int slot = j * 64 + lane;
+        const int slot = j * 64 + ln;
         const int r = slot / PS, piece = min(slot - r * PS, P - 1);
         const uint32_t off = (uint32_t)((source_row(t * TL_ROWS + r, real) - first) * P + piece) * 16u;
         lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, dst + j * 1024);
@@ -213,7 +225,7 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[kb][r] = 0.f;
-      // EMIT: -lse2 of the lane's rows, asked for before the products so that it is there after them
+      // EMIT: -lse2 of the lane's rows, read from LDS before the products so that it is there after them
       float4 nl[4];
       if (EMIT) {
 #pragma unroll
