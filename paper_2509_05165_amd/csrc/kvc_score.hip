@@ -430,13 +430,15 @@ inline int mfma_chunk(const Problem& pb, int row_chunks) {
   return wgs >= 2048 ? MF_CHUNK_BIG : MF_CHUNK;
 }
 // The K loads carry the streaming hint (which keeps a pass's partial results in L2 instead) where a
-// launch reads each key once and its K is far beyond the 256 MB memory-side cache.  Where the
-// row chunks of a head share the reads, or the emit pass can still find what the
-// statistics pass read, plain loads are better.  Whole passes in us, plain / hint: row chunks
-// shared: 80 layers x 64k (four) 21250 / 22250, 16k per head (four) 4792 / 4856, ragged 4k (two)
-// 1684 / 1708; one row chunk: 51 MB of K 108 / 111, 268 MB 294 / 304; 4.7 GB 7424 / 7353, 8.6 GB
-// 5514 / 5470; 10.7 GB with the rest of the rows in a launch of its own 13834 / 13550.
-constexpr int64_t MF_STREAM_BYTES = int64_t(1) << 30;
+// launch reads each key once and its K is well beyond the 256 MB memory-side cache: 3/8 GiB and more.
+// Below that the emit pass still finds part of what the statistics pass read, and plain loads
+// are better.  Whole passes of 32 layers in us, plain / hint, by K: 32/8 heads 0.25 GiB 243 / 252,
+// 0.31 347 / 348, 0.38 361 / 354, 0.5 444 / 439, 1 857 / 838, 2 1593 / 1562, 8 6371 / 6314; 16/8
+// heads 0.18 GiB 163 / 183, 0.31 279 / 282, 0.38 316 / 306, 0.5 383 / 365, 2 1354 / 1251; 8/8 heads
+// 0.31 GiB 258 / 262, 0.5 371 / 347.  Row chunks of a head share the reads, where plain loads
+// are better at any size: 80 layers x 64k (four) 21250 / 22250, 16k per head (four) 4792 / 4856,
+// ragged 4k (two) 1684 / 1708.
+constexpr int64_t MF_STREAM_BYTES = int64_t(3) << 27;
 constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact emit launch (two per compute unit)
 
 // The ways through the stage (see the top of the file).
