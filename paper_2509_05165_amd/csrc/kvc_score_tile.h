@@ -86,9 +86,10 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   // otherwise the emit forms whose registers are used up spill it (2 to 15 registers), and every
   // reload waits for the loads before it between two loads of a tile.  Score stage, 16 layers of
   // 4096 tokens, 32/8 heads, in us without / with: bf16 d = 80 79 / 71, 128 (M = 200) 252 / 245,
-  // 256 207 / 189, float32 d = 64 327 / 298, 128 613 / 577.  The two forms with registers to
-  // spare gain nothing (bf16 d = 64 54.0 / 54.2) or lose (float32 d = 256 1344 / 1369).
-  constexpr bool OPAQUE = EMIT && KS < 32 && (KS > 4 || sizeof(T) == 4);
+  // 256 207 / 189, float32 d = 64 327 / 298, 128 613 / 577.  The forms with registers to spare
+  // gain nothing (bf16 d = 64 54.0 / 54.2) or lose (bf16 d = 96, 4 layers of 3 x 699 tokens, 53.1 /
+  // 54.9; float32 d = 256 1344 / 1369).
+  constexpr bool OPAQUE = EMIT && (sizeof(T) == 4 ? KS < 32 : KS == 5 || KS >= 8);
   __shared__ __attribute__((aligned(16))) float nls[EMIT ? 2 : 1][EMIT ? TL_ROWS : 4];
   __shared__ __attribute__((aligned(16))) float rests[REST ? 2 : 1][REST ? TL_ROWS : 4];
 
