@@ -24,7 +24,8 @@ namespace {
 constexpr int GA_THREADS = 256;
 // Large pools: 64 rows per wave, two wave instructions of loads in flight per lane (measured: 2
 // beats 1, 3, 4 and 8).  A pool that would leave the chip with few waves is a chain of
-// latencies instead: it gets fewer rows per wave and all of them in flight.
+// latencies instead: it gets fewer rows per wave and four wave instructions of loads in flight
+// (16 rows of 256 bytes: all of them).
 // (99k rows of 256 bytes, 102 MB moved: 33 us with 64 rows per wave, 27 with 32, 24 with 16, 26
 // with 8; 524k rows: 105 us with 64 and 32, 108 with 16.)
 constexpr int GA_WAVES = 4096;   // waves that a launch should have (16 per compute unit)

@@ -1,4 +1,4 @@
-// bf16 matrix-core kernels of kvc_score (d = 128, window in {32,64,128,256}).
+// bf16 matrix-core kernels of kvc_score (d = 128, windows of 32, 64, 128 or a multiple of 256).
 // Included by kvc_score.hip only.
 //
 // One workgroup (4 waves) handles one KV head x one chunk of keys x up to 256
@@ -217,6 +217,9 @@ __device__ __forceinline__ float merge_few(const float* __restrict__ part_m, con
 //   the workgroup waits for tile t+1, meets at a barrier, starts the load of
 //   tile t+2 into the buffer of tile t and (EMIT) writes out tile t-1; the last
 //   phase already prefetches the first fragments of tile t+1.
+// In the statistics pass the compiler, which cannot see that the first wait covers the query
+// fragments, puts a vmcnt(0) of its own in front of the first product of every macro tile: there
+// tile t+2 has the last phase of tile t to arrive in, not four phases.  The emit pass has no such wait.
 //
 // causal != 0: task token m sits at position n - window + m of its sequence and
 // sees keys at positions <= that only.  Tiles that lie wholly below position

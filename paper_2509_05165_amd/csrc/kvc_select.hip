@@ -16,9 +16,9 @@
 // with device-scope atomic loads), so a call is five launches instead of eleven.
 //
 // Inside kvc_compress the rows of the pool are known to be sorted (the composite of sorted
-// scores is sorted, in floating point too), the scratch has been cleared by the rank kernel and
-// the scores are still to be aggregated over the heads: launch_composite_select then needs three
-// launches.  The first pass aggregates, stores and histograms, and the last workgroup of the
+// scores is sorted, in floating point too), the scratch is clear (the rank kernel does that on the
+// way where the workspace has room for it beside its own) and the scores are still to be aggregated
+// over the heads: launch_composite_select then needs three launches.  The first pass aggregates, stores and histograms, and the last workgroup of the
 // third pass finds the counts of a row by searching it instead of sweeping all rows.  Composite
 // and selection of 32 layers x 777 tokens: 34 -> 30 us; at 131072 tokens the pass as a
 // whole is within the noise of the separate launches.
