@@ -357,15 +357,18 @@ __global__ __launch_bounds__(SEL_THREADS) void select_hist(
 }
 
 // The composite (mean or maximum over the heads of the rank-aligned scores) and the first
-// histogram pass over it.  grid: (rank blocks, layers, batch); HKV heads (0: not known at compile
-// time), VEC consecutive ranks per thread, all loads of a thread in flight together; the
-// heads are joined in ascending order as in kvc_composite.
+// histogram pass over it.  grid: (rank blocks, layers, batch); the heads are joined in ascending
+// order as in kvc_composite.  HKV heads known at compile time: VEC consecutive ranks per thread, all
+// loads of a thread in flight together.  HKV = 0, any number: CH_RANKS ranks of CH_HEADS heads in
+// flight.  One at a time made a chain of the heads: 32 layers of 4096 ranks took 35 us with 12 heads
+// and 80 with 32 (the composite and the histogram as two launches 17 and 23); with 4 ranks 16 and
+// 26, with 8 12 and 15; 64 heads, 8 layers of 16384, 36 and 20 (two launches 30).
+constexpr int CH_RANKS = 8, CH_HEADS = 4;
 template <int HKV, int VEC>
 __global__ __launch_bounds__(SEL_THREADS) void composite_hist(
     const float* __restrict__ sorted, SeqTable seq, int hkv_arg, int total, int head_max,
     int floor_rank, int per_block, BudgetTable budget, float* __restrict__ I, SelState* state,
     uint32_t* __restrict__ hist, uint32_t* __restrict__ tickets) {
-  typedef float vec_t __attribute__((ext_vector_type(VEC)));
   __shared__ uint32_t lh[SEL_BINS];
   __shared__ uint32_t found;
   const int hkv = HKV ? HKV : hkv_arg;
@@ -378,16 +381,16 @@ __global__ __launch_bounds__(SEL_THREADS) void composite_hist(
     __syncthreads();
     const float* p0 = sorted + (size_t)l * hkv * total + tok0;
     float* out = I + (size_t)l * total + tok0;
-    for (int i0 = begin; i0 < end; i0 += SEL_THREADS * VEC) {
-      const int i = i0 + (int)threadIdx.x * VEC;
-      const bool live = i < end;                         // VEC > 1: n is a multiple of VEC (host-checked)
-      const float* p = p0 + (live ? i : begin);
-      vec_t acc;
-      if constexpr (HKV > 0) {
+    if constexpr (HKV > 0) {
+      typedef float vec_t __attribute__((ext_vector_type(VEC)));
+      for (int i0 = begin; i0 < end; i0 += SEL_THREADS * VEC) {
+        const int i = i0 + (int)threadIdx.x * VEC;
+        const bool live = i < end;                       // VEC > 1: n is a multiple of VEC (host-checked)
+        const float* p = p0 + (live ? i : begin);
         vec_t x[HKV];
 #pragma unroll
         for (int h = 0; h < HKV; ++h) x[h] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(p + (size_t)h * total));
-        acc = x[0];
+        vec_t acc = x[0];
 #pragma unroll
         for (int h = 1; h < HKV; ++h) {
           if (head_max) {
@@ -397,18 +400,47 @@ __global__ __launch_bounds__(SEL_THREADS) void composite_hist(
             acc += x[h];
           }
         }
-      } else {
-        static_assert(HKV > 0 || VEC == 1, "the general form takes one rank per thread");
-        acc[0] = p[0];
-        for (int h = 1; h < hkv; ++h) {
-          const float x = p[(size_t)h * total];
-          acc[0] = head_max ? fmaxf(acc[0], x) : acc[0] + x;
+        if (!head_max) acc = acc / float(hkv);
+        if (live) *reinterpret_cast<vec_t*>(out + i) = acc;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) hist_add(lh, live && i + j >= floor_rank, float_to_ordered(acc[j]) >> 21);
+      }
+    } else {
+      for (int i0 = begin; i0 < end; i0 += SEL_THREADS * CH_RANKS) {
+        const float* p[CH_RANKS];
+        float acc[CH_RANKS];
+#pragma unroll
+        for (int e = 0; e < CH_RANKS; ++e) {
+          p[e] = p0 + min(i0 + e * SEL_THREADS + (int)threadIdx.x, end - 1);   // clamped; dropped below
+          acc[e] = *p[e];
+        }
+        int h = 1;
+        for (; h + CH_HEADS <= hkv; h += CH_HEADS) {     // (no branch among the loads, or they go out one by one)
+          float x[CH_HEADS][CH_RANKS];
+#pragma unroll
+          for (int j = 0; j < CH_HEADS; ++j)
+#pragma unroll
+            for (int e = 0; e < CH_RANKS; ++e) x[j][e] = p[e][(size_t)(h + j) * total];
+#pragma unroll
+          for (int j = 0; j < CH_HEADS; ++j)
+#pragma unroll
+            for (int e = 0; e < CH_RANKS; ++e) acc[e] = head_max ? fmaxf(acc[e], x[j][e]) : acc[e] + x[j][e];
+        }
+        for (; h < hkv; ++h) {
+          float x[CH_RANKS];
+#pragma unroll
+          for (int e = 0; e < CH_RANKS; ++e) x[e] = p[e][(size_t)h * total];
+#pragma unroll
+          for (int e = 0; e < CH_RANKS; ++e) acc[e] = head_max ? fmaxf(acc[e], x[e]) : acc[e] + x[e];
+        }
+#pragma unroll
+        for (int e = 0; e < CH_RANKS; ++e) {
+          const int i = i0 + e * SEL_THREADS + (int)threadIdx.x;
+          if (!head_max) acc[e] = acc[e] / float(hkv);
+          if (i < end) out[i] = acc[e];
+          hist_add(lh, i < end && i >= floor_rank, float_to_ordered(acc[e]) >> 21);
         }
       }
-      if (!head_max) acc = acc / float(hkv);
-      if (live) *reinterpret_cast<vec_t*>(out + i) = acc;
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) hist_add(lh, live && i + j >= floor_rank, float_to_ordered(acc[j]) >> 21);
     }
     __syncthreads();
     uint32_t* gh = hist + (size_t)b * 3 * SEL_BINS;

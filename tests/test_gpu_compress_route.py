@@ -2,7 +2,8 @@
 (aggregation and first histogram in one launch, counts of the sorted rows by searching them).
 It must give what the stage calls give on the same scores, bit for bit: composite, threshold,
 lengths and offsets, over the borders of that route (4 and 8 heads with and without 16-byte
-aligned sequences, other head counts, pools of up to 256 rows and more, floors, ties, forced
+aligned sequences, other head counts around their batches of four, pools of up to 256 rows and more,
+floors, ties, forced
 tokens, empty sequences, budgets of nothing and of everything)."""
 import numpy as np
 import pytest
@@ -21,6 +22,10 @@ CASES = [
     (5, 8, 4, [4100, 64], 50, {}),
     (2, 8, 4, [4099], 10, dict(agg_head=kv.KVC_AGG_MAX)),
     (2, 6, 3, [300, 0, 77], 40, dict(min_per_layer=100)),
+    (2, 9, 9, [2047, 1], 30, {}),                                # heads in batches of four behind the first: 4 + 4
+    (2, 12, 12, [2049, 300], 30, dict(min_per_layer=7)),         # 4 + 4 + 3
+    (2, 6, 6, [4100], 30, dict(agg_head=kv.KVC_AGG_MAX)),        # 4 + 1
+    (3, 2, 1, [2100], 30, {}),                                   # none
     (1, 8, 8, [40], 100, {}),
     (4, 8, 8, [257], 0, {}),
     (70, 2, 2, [130], 25, {}),                                   # more rows than lanes of a wave
