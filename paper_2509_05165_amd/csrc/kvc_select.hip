@@ -27,6 +27,7 @@
 // unstructured variant.  With a per-row floor f the first f ranks of every row
 // are kept unconditionally and stay out of the histograms; the budget that is
 // searched for is what remains after them.
+#include <algorithm>
 #include <mutex>
 
 #include "kvc_internal.h"
@@ -56,11 +57,34 @@ struct SelState {
 
 struct BudgetTable { int64_t b[KVC_MAX_BATCH]; };
 
+// What the first pass on cleared scratch and the last pass over sorted rows need besides.
+struct SelectExtra {
+  int rows;
+  float* tau;
+  int32_t* lengths;
+  int64_t* offsets;
+  BudgetTable budget;
+};
+
 __device__ __forceinline__ void digit_of(int pass, uint32_t key, uint32_t* digit, uint32_t* hi) {
   // pass 0: bits 31..21, pass 1: bits 20..10, pass 2: bits 9..0
   if (pass == 0) { *digit = key >> 21; *hi = 0; }
   else if (pass == 1) { *digit = (key >> 10) & 2047u; *hi = key >> 21; }
   else { *digit = key & 1023u; *hi = key >> 10; }
+}
+
+// Scratch and state of a stage call; budget.b[] already excludes the floor entries.
+__global__ void select_init(uint32_t* words, int count, SelState* state, BudgetTable budget, SeqTable seq,
+                            int rows, int floor_rank) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < count) words[i] = 0;
+  if (i < seq.batch) {
+    const int n = seq.cu[i + 1] - seq.cu[i];
+    state[i].prefix = 0;
+    state[i].bad = 0;
+    state[i].remaining = (uint64_t)budget.b[i];
+    state[i].expect = (uint64_t)rows * (uint64_t)max(n - floor_rank, 0);   // entries that compete
+  }
 }
 
 __global__ void select_clear(uint32_t* words, int count) {
@@ -142,14 +166,15 @@ __device__ __forceinline__ uint64_t block_scan_incl(uint64_t v, uint64_t* total)
 // One workgroup: picks the digit whose bucket holds the wanted rank, walking from
 // the largest digit down.  Thread t owns bins [bins - (t+1)*per, bins - t*per) in
 // descending order; a prefix sum over the threads names the owner of the rank.
-// The first pass looks for rank `budget` among `pool` entries, the others go on from state[b]
-// (all zero before the first pass).  *found (LDS): the threshold bits fixed so far.
+// FRESH (pass 0 on state[b] that is all zero): looks for rank `budget` among `pool` entries; otherwise
+// goes on from state[b].  *found (LDS): the threshold bits fixed so far.
+template <bool FRESH>
 __device__ __forceinline__ void find_digit(int pass, int b, const uint32_t* __restrict__ hist,
                                            SelState* state, uint64_t budget, uint64_t pool,
                                            uint32_t* found) {
-  const uint64_t want = pass == 0 ? budget : state[b].remaining;    // uniform
+  const uint64_t want = FRESH ? budget : state[b].remaining;    // uniform
   if (want == 0) return;                       // budget 0: nothing to find
-  const uint64_t expect = pass == 0 ? pool : state[b].expect;       // uniform; read before anyone updates it
+  const uint64_t expect = FRESH ? pool : state[b].expect;       // uniform; read before anyone updates it
   const uint32_t prefix = state[b].prefix;
   const uint32_t* gh = hist + ((size_t)b * 3 + pass) * SEL_BINS;
   const int bins = pass == 2 ? 1024 : SEL_BINS;
@@ -298,12 +323,12 @@ __device__ __forceinline__ uint2 count_sorted(const float* row, int first, int n
 
 // grid: (token blocks, rows, batch).  SORTED (last pass, at most SEL_THREADS rows): every row is
 // descending, and the last workgroup of a sequence finds its counts, lengths and offsets.
-template <bool SORTED>
-__global__ __launch_bounds__(SEL_THREADS) void select_hist(
-    const float* __restrict__ I, SeqTable seq, int total, int rows, int pass, int floor_rank,
-    int per_block, BudgetTable budget, SelState* state,
-    uint32_t* __restrict__ hist /* [batch][3][SEL_BINS] */, uint32_t* __restrict__ tickets,
-    float* tau, int32_t* lengths, int64_t* offsets) {
+// FRESH: pass 0 on cleared state.
+template <bool SORTED, bool FRESH>
+__device__ __forceinline__ void select_hist_body(
+    const float* __restrict__ I, const SeqTable& seq, int total, int pass, int floor_rank, int per_block,
+    SelState* state, uint32_t* __restrict__ hist /* [batch][3][SEL_BINS] */, uint32_t* __restrict__ tickets,
+    const SelectExtra* extra) {
   __shared__ __attribute__((aligned(8))) uint32_t lh[SEL_BINS];
   __shared__ uint32_t found;
   const int b = blockIdx.z;
@@ -338,22 +363,44 @@ __global__ __launch_bounds__(SEL_THREADS) void select_hist(
   }
   // every workgroup of the sequence takes a ticket, the idle ones included
   if (!last_workgroup(tickets, pass, seq.batch, b)) return;
-  find_digit(pass, b, hist, state, (uint64_t)budget.b[b], (uint64_t)rows * (uint64_t)max(n - floor_rank, 0), &found);
-  if (!SORTED) return;
-  __syncthreads();                                       // found
-  const uint32_t tau_key = budget.b[b] > 0 ? found : 0u;
-  uint2* rc = reinterpret_cast<uint2*>(lh);              // counts of a row (the histogram is flushed)
-  int lanes = 64;
-  while (lanes * rows > SEL_THREADS) lanes /= 2;         // at least 1: rows <= SEL_THREADS
-  const int r = (int)threadIdx.x / lanes;
-  if (budget.b[b] > 0) {                                 // uniform
-    const uint2 c = count_sorted(I + (size_t)min(r, rows - 1) * total + tok0, min(floor_rank, n), n,
-                                 tau_key, lanes, r < rows);
-    if (r < rows && ((int)threadIdx.x & (lanes - 1)) == 0) rc[r] = c;
+  if constexpr (FRESH)
+    find_digit<true>(pass, b, hist, state, (uint64_t)extra->budget.b[b],
+                     (uint64_t)extra->rows * (uint64_t)max(n - floor_rank, 0), &found);
+  else
+    find_digit<false>(pass, b, hist, state, 0, 0, &found);
+  if constexpr (SORTED) {
+    const BudgetTable& budget = extra->budget;
+    const int rows = extra->rows;
+    __syncthreads();                                       // found
+    const uint32_t tau_key = budget.b[b] > 0 ? found : 0u;
+    uint2* rc = reinterpret_cast<uint2*>(lh);              // counts of a row (the histogram is flushed)
+    int lanes = 64;
+    while (lanes * rows > SEL_THREADS) lanes /= 2;         // at least 1: rows <= SEL_THREADS
+    const int r = (int)threadIdx.x / lanes;
+    if (budget.b[b] > 0) {                                 // uniform
+      const uint2 c = count_sorted(I + (size_t)min(r, rows - 1) * total + tok0, min(floor_rank, n), n,
+                                   tau_key, lanes, r < rows);
+      if (r < rows && ((int)threadIdx.x & (lanes - 1)) == 0) rc[r] = c;
+    }
+    __syncthreads();
+    finalize_sequence(b, seq, rows, floor_rank, budget, tau_key, state,
+                      [&](int l, int i) -> uint64_t { return i ? rc[l].y : rc[l].x; }, extra->tau, extra->lengths, extra->offsets);
   }
-  __syncthreads();
-  finalize_sequence(b, seq, rows, floor_rank, budget, tau_key, state,
-                    [&](int l, int i) -> uint64_t { return i ? rc[l].y : rc[l].x; }, tau, lengths, offsets);
+}
+
+// The plain pass keeps its argument block, with the grid's size that the system puts behind it, within
+// one cache line: the size is first asked for behind a barrier of every workgroup, and from the
+// next line three launches over 64 sequences took 60 us for 55.
+__global__ __launch_bounds__(SEL_THREADS) void select_hist(
+    const float* __restrict__ I, SeqTable seq, int total, int pass, int floor_rank, int per_block, SelState* state,
+    uint32_t* __restrict__ hist, uint32_t* __restrict__ tickets) {
+  select_hist_body<false, false>(I, seq, total, pass, floor_rank, per_block, state, hist, tickets, nullptr);
+}
+template <bool SORTED, bool FRESH>
+__global__ __launch_bounds__(SEL_THREADS) void select_hist_with(
+    const float* __restrict__ I, SeqTable seq, int total, int pass, int floor_rank, int per_block, SelState* state,
+    uint32_t* __restrict__ hist, uint32_t* __restrict__ tickets, SelectExtra extra) {
+  select_hist_body<SORTED, FRESH>(I, seq, total, pass, floor_rank, per_block, state, hist, tickets, &extra);
 }
 
 // The composite (mean or maximum over the heads of the rank-aligned scores) and the first
@@ -367,8 +414,8 @@ constexpr int CH_RANKS = 8, CH_HEADS = 4;
 template <int HKV, int VEC>
 __global__ __launch_bounds__(SEL_THREADS) void composite_hist(
     const float* __restrict__ sorted, SeqTable seq, int hkv_arg, int total, int head_max,
-    int floor_rank, int per_block, BudgetTable budget, float* __restrict__ I, SelState* state,
-    uint32_t* __restrict__ hist, uint32_t* __restrict__ tickets) {
+    int floor_rank, int per_block, float* __restrict__ I, SelState* state,
+    uint32_t* __restrict__ hist, uint32_t* __restrict__ tickets, BudgetTable budget) {
   __shared__ uint32_t lh[SEL_BINS];
   __shared__ uint32_t found;
   const int hkv = HKV ? HKV : hkv_arg;
@@ -448,7 +495,7 @@ __global__ __launch_bounds__(SEL_THREADS) void composite_hist(
       if (lh[i]) atomicAdd(&gh[i], lh[i]);
   }
   if (last_workgroup(tickets, 0, seq.batch, b))
-    find_digit(0, b, hist, state, (uint64_t)budget.b[b],
+    find_digit<true>(0, b, hist, state, (uint64_t)budget.b[b],
                (uint64_t)gridDim.y * (uint64_t)max(n - floor_rank, 0), &found);
 }
 
@@ -568,9 +615,10 @@ static BudgetTable open_budgets(const Problem& pb, const int64_t* budget) {
   return bt;
 }
 
-// Passes [first_pass, 3) and the counts, on cleared scratch.
+// Passes [first_pass, 3) and the counts.  fresh: the scratch is all zero (otherwise select_init has
+// set the state, or a first pass has).
 static kvc_status select_passes(const Problem& pb, const float* I, const BudgetTable& bt, int first_pass,
-                                bool sorted, float* tau, int32_t* lengths, int64_t* offsets, char* w,
+                                bool fresh, bool sorted, float* tau, int32_t* lengths, int64_t* offsets, char* w,
                                 hipStream_t stream) {
   const SelectLayout L = select_layout(pb);
   uint32_t* hist = reinterpret_cast<uint32_t*>(w + L.off_hist);
@@ -583,13 +631,17 @@ static kvc_status select_passes(const Problem& pb, const float* I, const BudgetT
   // more rows than threads (unstructured pools) keep the counting sweep: one workgroup
   // searching them one row per thread and round would take longer than the sweep's launch
   const bool search = sorted && rows <= SEL_THREADS;
+  const SelectExtra extra{rows, tau, lengths, offsets, bt};
   for (int pass = first_pass; pass < 3; ++pass) {
     if (pass == 2 && search)
-      KVC_LAUNCH("select_hist", stream, select_hist<true><<<grid, SEL_THREADS, 0, stream>>>(
-          I, pb.seq, total, rows, pass, floor_rank, per_block, bt, state, hist, tickets, tau, lengths, offsets));
+      KVC_LAUNCH("select_hist", stream, select_hist_with<true, false><<<grid, SEL_THREADS, 0, stream>>>(
+          I, pb.seq, total, pass, floor_rank, per_block, state, hist, tickets, extra));
+    else if (pass == 0 && fresh)
+      KVC_LAUNCH("select_hist", stream, select_hist_with<false, true><<<grid, SEL_THREADS, 0, stream>>>(
+          I, pb.seq, total, pass, floor_rank, per_block, state, hist, tickets, extra));
     else
-      KVC_LAUNCH("select_hist", stream, select_hist<false><<<grid, SEL_THREADS, 0, stream>>>(
-          I, pb.seq, total, rows, pass, floor_rank, per_block, bt, state, hist, tickets, tau, lengths, offsets));
+      KVC_LAUNCH("select_hist", stream, select_hist<<<grid, SEL_THREADS, 0, stream>>>(
+          I, pb.seq, total, pass, floor_rank, per_block, state, hist, tickets));
   }
   if (!search)
     KVC_LAUNCH("select_count", stream, select_count<<<grid, SEL_THREADS, 0, stream>>>(
@@ -610,9 +662,11 @@ kvc_status launch_global_select(const Problem& pb, const float* I, const int64_t
   const SelectLayout L = select_layout(pb);
   char* w = static_cast<char*>(ws);
   const BudgetTable bt = open_budgets(pb, budget);
-  const kvc_status st = launch_select_clear(pb, ws, stream);
-  if (st != KVC_OK) return st;
-  if (pb.max_seqlen > 0) return select_passes(pb, I, bt, 0, false, tau, lengths, offsets, w, stream);
+  const int words = int(L.off_state / 4);
+  KVC_LAUNCH("select_init", stream, select_init<<<(std::max(words, pb.batch) + 255) / 256, 256, 0, stream>>>(
+      reinterpret_cast<uint32_t*>(w), words, reinterpret_cast<SelState*>(w + L.off_state), bt, pb.seq, pb.sel_rows,
+      pb.min_per_layer));
+  if (pb.max_seqlen > 0) return select_passes(pb, I, bt, 0, false, false, tau, lengths, offsets, w, stream);
   KVC_LAUNCH("select_finalize", stream, select_finalize<<<pb.batch, SEL_THREADS, 0, stream>>>(
       pb.seq, pb.sel_rows, pb.min_per_layer, bt, reinterpret_cast<SelState*>(w + L.off_state),
       reinterpret_cast<uint32_t*>(w + L.off_counts), tau, lengths, offsets));
@@ -626,7 +680,7 @@ kvc_status launch_composite_select(const Problem& pb, const float* S_sorted, flo
   char* w = static_cast<char*>(ws);
   const BudgetTable bt = open_budgets(pb, budget);
   if (pb.unstructured)   // the pool is the rank-aligned per-head scores themselves
-    return select_passes(pb, S_sorted, bt, 0, true, tau, lengths, offsets, w, stream);
+    return select_passes(pb, S_sorted, bt, 0, true, true, tau, lengths, offsets, w, stream);
   const int total = int(pb.total), head_max = pb.agg_head == KVC_AGG_MAX;
   const int per_block = select_per_block(pb);
   dim3 grid((unsigned)((pb.max_seqlen + per_block - 1) / per_block), pb.layers, pb.batch);
@@ -635,16 +689,16 @@ kvc_status launch_composite_select(const Problem& pb, const float* S_sorted, flo
   for (int b = 0; b <= pb.batch; ++b) vec4 = vec4 && pb.seq.cu[b] % 4 == 0;
 #define KVC_COMPOSITE_HIST(HKV, VEC)                                                              \
   KVC_LAUNCH("composite_hist", stream, composite_hist<HKV, VEC><<<grid, SEL_THREADS, 0, stream>>>( \
-      S_sorted, pb.seq, pb.hkv, total, head_max, pb.min_per_layer, per_block, bt, I,               \
+      S_sorted, pb.seq, pb.hkv, total, head_max, pb.min_per_layer, per_block, I,                   \
       reinterpret_cast<SelState*>(w + L.off_state), reinterpret_cast<uint32_t*>(w + L.off_hist),   \
-      reinterpret_cast<uint32_t*>(w + L.off_tickets)))
+      reinterpret_cast<uint32_t*>(w + L.off_tickets), bt))
   if (pb.hkv == 8 && vec4) KVC_COMPOSITE_HIST(8, 4);
   else if (pb.hkv == 8) KVC_COMPOSITE_HIST(8, 1);
   else if (pb.hkv == 4 && vec4) KVC_COMPOSITE_HIST(4, 4);
   else if (pb.hkv == 4) KVC_COMPOSITE_HIST(4, 1);
   else KVC_COMPOSITE_HIST(0, 1);
 #undef KVC_COMPOSITE_HIST
-  return select_passes(pb, I, bt, 1, true, tau, lengths, offsets, w, stream);
+  return select_passes(pb, I, bt, 1, false, true, tau, lengths, offsets, w, stream);
 }
 
 }  // namespace kvc
