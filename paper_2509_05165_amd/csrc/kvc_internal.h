@@ -118,6 +118,13 @@ __device__ __forceinline__ void wait_memory() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
+// As wait_vmcnt<0>, and known to the compiler: it counts the loads that it can see, and without this
+// puts a wait of its own, for everything in flight, in front of the first use of each.
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0), the other counters at their maxima
+  asm volatile("" ::: "memory");
+}
+
 // The LDS half of it, where loads to LDS stay in flight over the barrier.
 __device__ __forceinline__ void wait_lds() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

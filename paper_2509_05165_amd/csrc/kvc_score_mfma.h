@@ -547,7 +547,7 @@ __device__ __forceinline__ void score_mfma_body(
   // Tile 0 has landed (and the query fragments); tile 1 is requested only now, so
   // that at kernel start, when every workgroup asks at once, all first tiles are
   // served before any second one.
-  wait_vmcnt<0>();
+  wait_loads();
   if (EMIT) lse_s[threadIdx.x] = my_nl;
   if (ntiles > 1) issue_tile(1);
   int issued = ntiles > 1 ? 1 : 0;            // highest tile requested so far

@@ -151,11 +151,18 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
     }
   };
   // EMIT: minus the log-sum-exp of row `lane` of tile t (and minus the rest of it)
+  // (the sign and the padding rows where the loads are used: here they would wait for them at once)
   auto load_nl = [&](int t, float& rest) -> float {
     bool real;
     const int r = source_row(t * TL_ROWS + lane, real);
-    rest = REST ? -lse2[a.rows_all + qrow0 + r] : 0.f;
-    return real ? -lse2[qrow0 + r] : NEG_BIG;
+    rest = REST ? lse2[a.rows_all + qrow0 + r] : 0.f;
+    return lse2[qrow0 + r];
+  };
+  auto store_nl = [&](int t, float lse, float rest) {
+    bool real;
+    source_row(t * TL_ROWS + lane, real);
+    nls[t & 1][lane] = real ? -lse : NEG_BIG;
+    if (REST) rests[t & 1][lane] = -rest;
   };
 
   issue_tile(t_begin);
@@ -172,8 +179,8 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   }
   float next_nl = 0.f, next_rest = 0.f;
   if (EMIT && wave == 0) {
-    nls[t_begin & 1][lane] = load_nl(t_begin, next_rest);
-    if (REST) rests[t_begin & 1][lane] = next_rest;
+    next_nl = load_nl(t_begin, next_rest);
+    store_nl(t_begin, next_nl, next_rest);
   }
 
   const bool active = wkey0 < n;                                  // wave-uniform, like the next two
@@ -211,7 +218,8 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   };
 
   for (int t = t_begin; t < t_end; ++t) {
-    wait_memory();
+    wait_loads();
+    wait_lds();
     __syncthreads();                      // tile t is complete; every wave is done with tile t-1
     if (!EMIT && t > t_begin) store_stats(t - 1);
     if (t + 1 < t_end) {
@@ -306,10 +314,7 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
         }
       }
     }
-    if (EMIT && wave == 0 && t + 1 < t_end) {
-      nls[(t + 1) & 1][lane] = next_nl;
-      if (REST) rests[(t + 1) & 1][lane] = next_rest;
-    }
+    if (EMIT && wave == 0 && t + 1 < t_end) store_nl(t + 1, next_nl, next_rest);
   }
   if constexpr (!EMIT) {
     wait_memory();
