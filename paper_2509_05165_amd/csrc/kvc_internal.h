@@ -118,10 +118,11 @@ __device__ __forceinline__ void wait_memory() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
-// As wait_vmcnt<0>, and known to the compiler: it counts the loads that it can see, and without this
+// As wait_vmcnt, and known to the compiler: it counts the loads that it can see, and without this
 // puts a wait of its own, for everything in flight, in front of the first use of each.
+template <int N = 0>
 __device__ __forceinline__ void wait_loads() {
-  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0), the other counters at their maxima
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | (N >> 4 << 14));   // the other counters at their maxima
   asm volatile("" ::: "memory");
 }
 

@@ -15,6 +15,7 @@
 //                     of the others need (K goes straight into LDS), and workspaces too small for
 //                     a layer of the key-stationary kernels
 #include <algorithm>
+#include <type_traits>
 
 #include "kvc_internal.h"
 
@@ -575,7 +576,6 @@ template <typename T, int KS>
 kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* const* q,
                        const void* const* k, int l0, int layers, float* part_m, float* part_s,
                        float* lse2, float* out, size_t out_stride, hipStream_t stream) {
-  constexpr int KB = tile_keys(KS) / 128;
   PtrTable qt{}, kt{};
   for (int l = 0; l < layers; ++l) { qt.p[l] = q[l0 + l]; kt.p[l] = k[l0 + l]; }
   constexpr int keys = tile_keys(KS);
@@ -588,17 +588,21 @@ kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* cons
   a.head_magic = uint32_t(((uint64_t(1) << 32) + a.head_rows - 1) / a.head_rows);
   a.causal = pb.causal_tail; a.group_max = pb.agg_group == KVC_AGG_MAX;
   a.c2 = pb.scale * LOG2E;
-  a.rows_all = size_t(L.rows_layer) * layers;
+  a.rows_layer = size_t(L.rows_layer);
+  a.rows_all = a.rows_layer * layers;
   a.out_layer_stride = out_stride;
   // the rows of a head are independent in the statistics pass: small launches deal them
   // to several workgroups until every compute unit has its two
   const int64_t wgs = flat * pb.hkv * layers;
   const int tiles = (pb.group * pb.window + TL_ROWS - 1) / TL_ROWS;
   a.row_split = int(std::max<int64_t>(1, std::min<int64_t>(tiles, 512 / wgs)));
+  a.linear = 1;
   KVC_LAUNCH("score_tile<stats>", stream,
-             score_tile<T, KS, KB, false, true><<<dim3(unsigned(flat), pb.hkv * a.row_split, layers), TL_THREADS, 0, stream>>>(
+             score_tile<T, KS, false, true><<<dim3(unsigned(flat), pb.hkv * a.row_split, layers), TL_THREADS, 0, stream>>>(
                  qt, kt, pb.seq, a, part_m, part_s, nullptr, nullptr));
   a.row_split = 1;
+  a.linear = pb.window % 8 == 0;
+  const dim3 grid(unsigned(flat), pb.hkv, layers);
   const int rows_all = int(a.rows_all), chunks = int((pb.max_seqlen + keys - 1) / keys);
   if (chunks <= 4)
     KVC_LAUNCH("score_merge", stream, score_merge_few<<<(rows_all + 255) / 256, 256, 0, stream>>>(
@@ -606,12 +610,11 @@ kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* cons
   else
     KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
         pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4)));
-  const dim3 grid(unsigned(flat), pb.hkv, layers);
   if (pb.agg_task == KVC_AGG_MAX)
-    KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, KB, true, true><<<grid, TL_THREADS, 0, stream>>>(
+    KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, true, true><<<grid, TL_THREADS, 0, stream>>>(
         qt, kt, pb.seq, a, nullptr, nullptr, lse2, out));
   else
-    KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, KB, true, false><<<grid, TL_THREADS, 0, stream>>>(
+    KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, true, false><<<grid, TL_THREADS, 0, stream>>>(
         qt, kt, pb.seq, a, nullptr, nullptr, lse2, out));
   return KVC_OK;
 }

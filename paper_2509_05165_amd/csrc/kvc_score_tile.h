@@ -16,9 +16,9 @@
 // feed four v_mfma_f32_32x32x2_f32 (any order of the products is as good as another, as
 // long as both operands agree).  float32 products and sums stay float32 throughout.
 //
-// LDS tile: row r at slot r * PS (PS = 2 KS + 1 slots of 16 bytes: an odd stride, so that the
-// reads of 16 consecutive rows cover all banks).  The direct global->LDS loads write
-// consecutive slots; 64 rows of PS slots are exactly PS wave instructions.
+// LDS tile: row r at slot r * SP (SP slots of 16 bytes, a power of two, so that a direct global->LDS
+// load brings whole rows), its piece p at slot p ^ f(r) of the row, so that the reads of 16 consecutive
+// rows cover all banks.  Slots of pieces past the row (head sizes of 80, 96, ...) are zero.
 #pragma once
 
 namespace kvc {
@@ -33,10 +33,41 @@ struct TileArgs {
   int head_rows;                     // EMIT: window rounded up to 8 (rows of a head in tile order)
   uint32_t head_magic;               // EMIT: ceil(2^32 / head_rows)
   int causal, group_max;
+  int linear;                        // rows in tile order follow one another in memory
   float c2;
-  size_t rows_all;                   // query rows of the launch: layers * batch * Hq * window
+  size_t rows_all, rows_layer;       // query rows of the launch, of a layer: batch * Hq * window
   size_t out_layer_stride;
 };
+
+// 16-byte slots of a row in LDS: a power of two, so that a load instruction brings whole rows.
+constexpr int tile_slots(int ksteps) { return ksteps <= 4 ? 8 : ksteps <= 8 ? 16 : 2 * ksteps; }
+
+// Per kernel: waves per SIMD, 32-key blocks per wave, tiles of query rows in LDS, k-steps by which the
+// fragments run ahead of their products.  Score stage in us, 200 task tokens x 8192 tokens x 32 layers of
+// 32 heads of 128 / 14k tokens in heads of 64: the emit pass with 3 and 4 waves and two key blocks
+// takes 373 / 65, with 2 and 3 waves 424 / 72, with three key blocks and 2 waves 402, with four 435.  A third
+// tile lets the emit pass read across the tile border; the statistics pass gains nothing from it (461 / 92
+// with two and with three).  Heads of 80 have no room for it beside four waves: 263 us against 273 (3 waves,
+// three tiles) and 277 before at M = 200, 16 layers of 2 x 4096 tokens.  (light: max pooling; the mean holds more
+// and would spill.)
+constexpr int tile_waves(int ks, bool emit, bool light) {
+  return ks > 16 ? 1 : ks > 8 ? 2 : (ks > 5 ? 3 : 4) - (emit && !light);
+}
+constexpr int tile_kb(int ks) { return ks > 16 ? 1 : 2; }
+constexpr int tile_ring(int ks, bool emit) { return emit && ks <= 8 && ks != 5 ? 3 : 2; }
+constexpr int tile_ahead(int ks) { return ks % 4 == 0 ? 4 : ks; }
+
+// As lds_dma16_s, 4 bytes per lane.
+__device__ __forceinline__ void lds_dma4_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
+               : "memory");
+}
+
+__device__ __forceinline__ uint4 load16(const __attribute__((address_space(1))) char* base, uint32_t off) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(base + off);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
 
 // One k-step (16 bytes of every row of both operands) of a 32x32 tile.
 template <typename T>
@@ -58,42 +89,45 @@ __device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
 // sum of 2^(t - max) over the wave's keys, then over the workgroup's, to part_m / part_s.
 // EMIT: queries on the rows, a lane owns one key.  In tile order every query head is
 // padded to a multiple of 8 rows, so each group of four accumulator registers (8 rows) belongs to
-// one head; the padding rows carry lse = +1e30 and contribute nothing.
+// one head; the padding rows are copies of the last one (the mean leaves them out).
 //
-// What bounds it is latency inside a wave (fragment reads, products, the vector work on their
-// result, one after the other) and the vector port, so registers are held to what four waves per
-// SIMD (rows of up to 160 bytes), three (256) or two (512) leave, masks stay out of the common
-// path and the tile loads take 32-bit offsets from a scalar base.  The emit pass also waits for
-// what it has only just asked for: the compiler cannot see that wait_memory covers the key
-// fragments and puts its own vmcnt(0) in front of the first product of every tile, behind the loads
-// of the next one, and load_nl negates what it loads at once; the tile loads run ahead in the
-// statistics pass only.  200 task tokens, 32 heads of 128 and 8192 tokens x 32 layers, both passes:
-// 1126 us with two waves and the mask looked at per element, 1062 with three, 989 without the
-// mask, 972 now (0.88 PFLOP/s); heads of 64 in a ragged batch of 14k tokens 206, 202, 187, 186.  A
-// form with two accumulator sets and prefetched fragments, one wave less, took 1075 and 262.
-template <typename T, int KS, int KB, bool EMIT, bool TASK_MAX>
-__global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 : 4) void score_tile(
+// What bounds it is the vector port and the issue of one wave (fragment reads, products, the vector work
+// on their result, one after the other), so a wave issues little else: the tile loads start from scalar
+// addresses and keep their lane offsets, the log-sum-exps of a tile come the same way, masks stay
+// out of the common path, the buffers of the ring are constants, and the statistics of four tiles
+// are joined by all threads at once.  With an address computed per lane and load the address code
+// was half of what a wave issued in the emit pass.  Score stage, 200 task tokens, 32 heads of 128 and 8192
+// tokens x 32 layers, statistics + emit in us: 493 + 449 then, 461 + 373 now (0.98 PFLOP/s over both);
+// heads of 64 in a ragged batch of 14k tokens 97 + 77, 92 + 65.  Measured and left: the keys of the next
+// chunk prefetched into registers while a workgroup walks over chunks (543 + 436), fixed wave priorities (537 +
+// 436), two accumulator sets and one wave less (5 % slower at heads of 64).
+template <typename T, int KS, bool EMIT, bool TASK_MAX>
+__global__ __launch_bounds__(TL_THREADS, tile_waves(KS, EMIT, TASK_MAX)) void score_tile(
     PtrTable q_tab, PtrTable k_tab, SeqTable seq, TileArgs a, float* __restrict__ part_m,
     float* __restrict__ part_s, const float* __restrict__ lse2, float* __restrict__ out) {
-  constexpr int PS = 2 * KS + 1;
-  constexpr int KEYS = 4 * 32 * KB;
-  constexpr int DMA = (PS + 3) / 4;             // load instructions per wave and tile, at most
-  __shared__ __attribute__((aligned(16))) uint4 qtile[2][TL_ROWS * PS];
-  __shared__ float2 stat[EMIT ? 1 : 2][4][EMIT ? 1 : TL_ROWS];
-  // EMIT: minus the log-sum-exps of a tile's rows; float32 keeps what rounding took from them, too
+  constexpr int SP = tile_slots(KS);            // 16-byte slots per row in LDS
+  constexpr int RPD = 64 / SP;                  // rows that one load instruction brings
+  constexpr int DMA = TL_ROWS / RPD / 4;        // load instructions per wave and tile
+  constexpr int KB = tile_kb(KS), KEYS = 4 * 32 * KB;
+  constexpr int RING = tile_ring(KS, EMIT);
+  constexpr int AHEAD = tile_ahead(KS);
+  // EMIT, float32: the log-sum-exps carry what rounding took from them, too
   constexpr bool REST = EMIT && sizeof(T) == 4;
-  // An opaque copy of the lane keeps what a tile load's offsets are made of out of the live set:
-  // otherwise the emit forms whose registers are used up spill it (2 to 15 registers), and every
-  // reload waits for the loads before it between two loads of a tile.  Score stage, 16 layers of
-  // 4096 tokens, 32/8 heads, in us without / with: bf16 d = 80 79 / 71, 128 (M = 200) 252 / 245,
-  // 256 207 / 189, float32 d = 64 327 / 298, 128 613 / 577.  The forms with registers to spare
-  // gain nothing (bf16 d = 64 54.0 / 54.2) or lose (bf16 d = 96, 4 layers of 3 x 699 tokens, 53.1 /
-  // 54.9; float32 d = 256 1344 / 1369).
-  constexpr bool OPAQUE = EMIT && (sizeof(T) == 4 ? KS < 32 : KS == 5 || KS >= 8);
-  __shared__ __attribute__((aligned(16))) float nls[EMIT ? 2 : 1][EMIT ? TL_ROWS : 4];
-  __shared__ __attribute__((aligned(16))) float rests[REST ? 2 : 1][REST ? TL_ROWS : 4];
+  __shared__ __attribute__((aligned(1024))) uint4 qtile[RING][TL_ROWS * SP];
+  constexpr int GROUP = KS == 5 ? 2 : 4;        // STATS: tiles whose statistics are joined at a time
+  __shared__ float2 stat[EMIT ? 1 : 2 * GROUP][4][EMIT ? 1 : TL_ROWS];
+  // EMIT: the log-sum-exps of a tile's rows
+  __shared__ __attribute__((aligned(256))) float lses[EMIT ? RING : 1][EMIT ? TL_ROWS : 4];
+  __shared__ __attribute__((aligned(256))) float rests[REST ? RING : 1][REST ? TL_ROWS : 4];
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int col = lane & 31, half = lane >> 5;
+  const int P = a.pieces;
+  const int R = EMIT ? a.group * a.head_rows : a.group * a.window;
+  const int all_tiles = (R + TL_ROWS - 1) / TL_ROWS;
 
   const int layer = blockIdx.z;
+  const int h = blockIdx.y / a.row_split, split = blockIdx.y - h * a.row_split;
   int b = 0, chunk = blockIdx.x;
   for (; b < a.batch - 1; ++b) {
     const int nc = (seq.cu[b + 1] - seq.cu[b] + KEYS - 1) / KEYS;
@@ -102,168 +136,226 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
   }
   const int tok0 = seq.cu[b], n = seq.cu[b + 1] - tok0;
   if (chunk * KEYS >= n) return;
-  const int h = blockIdx.y / a.row_split, split = blockIdx.y - h * a.row_split;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int col = lane & 31, half = lane >> 5;
-  const int wkey0 = chunk * KEYS + wave * 32 * KB;       // first key of the wave
-  const int P = a.pieces;
-  const uint4* q_head = static_cast<const uint4*>(q_tab.p[layer]) +
-                        ((size_t)b * a.hkv + h) * a.group * a.window * P;
-  const uint4* k_head = static_cast<const uint4*>(k_tab.p[layer]) + ((size_t)h * a.total + tok0) * P;
-  // first query row of this (layer, sequence, KV head) among the rows of the launch
-  const size_t qrow0 = (((size_t)layer * a.batch + b) * a.hkv + h) * a.group * a.window;
-  const int R = EMIT ? a.group * a.head_rows : a.group * a.window;
-  const int all_tiles = (R + TL_ROWS - 1) / TL_ROWS;
-  const int t_begin = EMIT ? 0 : (int)((int64_t)all_tiles * split / a.row_split);
-  const int t_end = EMIT ? all_tiles : (int)((int64_t)all_tiles * (split + 1) / a.row_split);
+  const int t_begin = EMIT ? 0 : (int)((uint32_t)all_tiles * (uint32_t)split / (uint32_t)a.row_split);
+  const int t_end = EMIT ? all_tiles : (int)((uint32_t)all_tiles * (uint32_t)(split + 1) / (uint32_t)a.row_split);
   if (t_begin >= t_end) return;
+  // first query row of the (sequence, KV head) in its layer, among the rows of the launch
+  const size_t head_row = ((size_t)b * a.hkv + h) * (uint32_t)(a.group * a.window);
+  const size_t qrow0 = (size_t)layer * a.rows_layer + head_row;
+  const uint4* q_head = static_cast<const uint4*>(q_tab.p[layer]) + head_row * P;
 
-  // query row (among the head's group * window) that row `pr` in tile order stands for, and
-  // whether it is a real one; never falling with pr
-  auto source_row = [&](int pr, bool& real) -> int {
-    if (!EMIT) { real = pr < R; return min(pr, R - 1); }
-    uint32_t g = __umulhi((uint32_t)pr, a.head_magic);   // exact or one too large
-    if (g * (uint32_t)a.head_rows > (uint32_t)pr) --g;
-    const int m = pr - (int)g * a.head_rows;
-    real = (int)g < a.group && m < a.window;
-    return (int)g < a.group ? (int)g * a.window + min(m, a.window - 1) : a.group * a.window - 1;
-  };
+  // ---- query tiles to LDS ----
+  // Load j of a tile (j = 4 i + wave) brings the RPD rows from j RPD on, in tile order; they lie in one
+  // group of 8, hence in one query head, and follow one another in memory.  The row they start from is
+  // scalar, and a lane's offset from it is the same for every tile unless the head ends before the
+  // group does (then its last row is read again).
+  const int rr = lane / SP, slot = lane % SP;
   const uint32_t qtile_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint4*)(&qtile[0][0]);
-  auto issue_tile = [&](int t) {
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(qtile_lds + (uint32_t)(t & 1) * (TL_ROWS * PS * 16));
-    // scalar base: the first row of the tile; the others follow within 64 rows of it
-    bool real;
-    int ln = lane;
-    if (OPAQUE) asm volatile("" : "+v"(ln));
-    const int first = __builtin_amdgcn_readfirstlane(source_row(t * TL_ROWS, real));
-    const uint64_t addr = reinterpret_cast<uint64_t>(q_head) + (uint64_t)(uint32_t)first * (uint32_t)(P * 16);
-    const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(addr >> 32)) << 32) |
-                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)addr);
+  const uint32_t lses_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)(&lses[0][0]);
+  const uint32_t rests_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)(&rests[0][0]);
+  auto lane_piece = [&](int i) {        // piece of the row that lands in the lane's slot
+    const int swz = KS == 4 ? (wave * 4 + (rr >> 1)) & 7 : ((i * 4 * RPD) & 15) ^ ((wave * RPD + rr) & 15);
+    return slot ^ swz;
+  };
+  // slots of pieces past the row are zero and stay so
+  if (P < SP) {
+    for (int i = threadIdx.x; i < RING * TL_ROWS * SP; i += TL_THREADS) (&qtile[0][0])[i] = make_uint4(0, 0, 0, 0);
+    wait_lds();
+    __syncthreads();
+  }
+  const uint32_t qoff = (uint32_t)((wave * RPD + rr) * P + lane_piece(0)) * 16u;
+  // query row (among the head's group * window) behind row `pr` in tile order, and how many of its head follow
+  auto source_row = [&](uint32_t pr, int& behind) -> int {
+    if (!EMIT) {
+      const int row = min((int)pr, R - 1);
+      behind = R - 1 - row;
+      return row;
+    }
+    uint32_t g = __umulhi(pr, a.head_magic);           // exact or one too large
+    if (g * (uint32_t)a.head_rows > pr) --g;
+    int m = (int)(pr - g * (uint32_t)a.head_rows);
+    if ((int)g >= a.group) { g = (uint32_t)a.group - 1; m = 0; }
+    m = min(m, a.window - 1);
+    behind = a.window - 1 - m;
+    return (int)g * a.window + m;
+  };
+  auto scalar64 = [](uint64_t x) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  };
+  int ahead_t = t_begin, ahead_buf = 0;   // the next tile to be asked for, and its buffer
+  auto issue_tile = [&]() {
+    const int t = ahead_t;
+    if (EMIT && wave == (t & 3)) {      // a row per lane
+      int behind;
+      const uint32_t off = (uint32_t)source_row((uint32_t)(t * TL_ROWS + lane), behind) * 4u;
+      lds_dma4_s(reinterpret_cast<const void*>(scalar64(reinterpret_cast<uint64_t>(lse2 + qrow0))), off,
+                 __builtin_amdgcn_readfirstlane(lses_lds + ahead_buf * (TL_ROWS * 4)));
+      if (REST)
+        lds_dma4_s(reinterpret_cast<const void*>(scalar64(reinterpret_cast<uint64_t>(lse2 + a.rows_all + qrow0))), off,
+                   __builtin_amdgcn_readfirstlane(rests_lds + ahead_buf * (TL_ROWS * 4)));
+    }
+    const uint32_t dst = qtile_lds + (uint32_t)ahead_buf * (TL_ROWS * SP * 16) + wave * 1024;
+    const uint64_t tile = reinterpret_cast<uint64_t>(q_head) + (uint64_t)(uint32_t)t * (uint32_t)(TL_ROWS * 16 * P);
+    if (a.linear && (t + 1) * TL_ROWS <= R) {
 #pragma unroll
-    for (int i = 0; i < DMA; ++i) {
-      const int j = i * 4 + wave;                        // wave-uniform
-      if (j < PS) {
-        const int slot = j * 64 + ln;
-        const int r = slot / PS, piece = min(slot - r * PS, P - 1);
-        const uint32_t off = (uint32_t)((source_row(t * TL_ROWS + r, real) - first) * P + piece) * 16u;
-        lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, dst + j * 1024);
+      for (int i = 0; i < DMA; ++i) {
+        const uint64_t base = scalar64(tile + (uint32_t)(i * 4 * RPD * 16) * (uint32_t)P);
+        const uint32_t off = RPD >= 4 ? qoff : (uint32_t)((wave * RPD + rr) * P + lane_piece(i)) * 16u;
+        if (lane_piece(i) < P)
+          lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, __builtin_amdgcn_readfirstlane(dst + i * 4096));
+      }
+    } else {
+      // (opaque: the products of the offsets are not worth registers across the tile loop)
+      int rrow = rr;
+      asm volatile("" : "+v"(rrow));
+#pragma unroll
+      for (int i = 0; i < DMA; ++i) {
+        const uint32_t pr = (uint32_t)__builtin_amdgcn_readfirstlane(t * TL_ROWS + (4 * i + wave) * RPD);
+        int behind;
+        const int row = source_row(pr, behind);
+        const uint64_t base = scalar64(reinterpret_cast<uint64_t>(q_head) + (uint64_t)(uint32_t)row * (uint32_t)(P * 16));
+        const uint32_t off = (uint32_t)(min(rrow, behind) * P + lane_piece(i)) * 16u;
+        if (lane_piece(i) < P)
+          lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, __builtin_amdgcn_readfirstlane(dst + i * 4096));
       }
     }
-  };
-  // EMIT: minus the log-sum-exp of row `lane` of tile t (and minus the rest of it)
-  // (the sign and the padding rows where the loads are used: here they would wait for them at once)
-  auto load_nl = [&](int t, float& rest) -> float {
-    bool real;
-    const int r = source_row(t * TL_ROWS + lane, real);
-    rest = REST ? lse2[a.rows_all + qrow0 + r] : 0.f;
-    return lse2[qrow0 + r];
-  };
-  auto store_nl = [&](int t, float lse, float rest) {
-    bool real;
-    source_row(t * TL_ROWS + lane, real);
-    nls[t & 1][lane] = real ? -lse : NEG_BIG;
-    if (REST) rests[t & 1][lane] = -rest;
+    ahead_buf = ahead_buf + 1 == RING ? 0 : ahead_buf + 1;
+    ++ahead_t;
   };
 
-  issue_tile(t_begin);
-  // ---- keys: registers for the whole kernel; pieces past the row are zero ----
+  for (int i = 0; i < RING - 1; ++i)
+    if (ahead_t < t_end) issue_tile();
+  // ---- keys: registers for the whole kernel ----
   uint4 kf[KB][KS];
-#pragma unroll
-  for (int kb = 0; kb < KB; ++kb) {
-    const uint4* krow = k_head + (size_t)min(wkey0 + kb * 32 + col, n - 1) * P;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int piece = 2 * ks + half;
-      kf[kb][ks] = piece < P ? krow[piece] : make_uint4(0, 0, 0, 0);
-    }
-  }
-  float next_nl = 0.f, next_rest = 0.f;
-  if (EMIT && wave == 0) {
-    next_nl = load_nl(t_begin, next_rest);
-    store_nl(t_begin, next_nl, next_rest);
-  }
-
-  const bool active = wkey0 < n;                                  // wave-uniform, like the next two
-  const bool ragged = wkey0 + 32 * KB > n;
-  const bool masked = a.causal && wkey0 + 32 * KB - 1 > n - a.window;
-  const int subs = a.head_rows >> 3;                              // EMIT: groups of 8 rows per query head
-  int sub = 0;                                                    // EMIT: of them, done of the current head
-  float tacc[KB], gacc[KB];                                       // EMIT: current head's aggregate, group's
-#pragma unroll
-  for (int kb = 0; kb < KB; ++kb) { tacc[kb] = TASK_MAX ? NEG_BIG : 0.f; gacc[kb] = 0.f; }
-  const float inv_window = 1.f / float(a.window);
-  auto finish_head = [&]() {
+  {
+    // scalar address of the wave's first key (or of the last one there is), keys behind it
+    const int row = min(chunk * KEYS + wave * 32 * KB, n - 1), behind = n - 1 - row;
+    // (rebuilt as a global-memory pointer: through the integers the compiler would lose that)
+    typedef const __attribute__((address_space(1))) char* global_ptr;
+    const global_ptr base = (global_ptr)scalar64(reinterpret_cast<uint64_t>(k_tab.p[layer]) +
+        (((uint64_t)(uint32_t)h * (uint32_t)a.total + (uint32_t)(tok0 + row)) * (uint32_t)(P * 16)));
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
-      const float tv = cross_half<TASK_MAX>(tacc[kb]);
-      const float sv = TASK_MAX ? fast_exp2(tv) : tv * inv_window;
-      gacc[kb] = a.group_max ? fmaxf(gacc[kb], sv) : gacc[kb] + sv;
-      tacc[kb] = TASK_MAX ? NEG_BIG : 0.f;
+      const uint32_t off = (uint32_t)(min(kb * 32 + col, behind) * P) * 16u;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)   // (pieces past the row: any will do, they meet zeros)
+        kf[kb][ks] = load16(base, off + min(2 * ks + half, P - 1) * 16);
+    }
+  }
+  const int subs = a.head_rows >> 3;                              // EMIT: groups of 8 rows per query head
+  const float inv_window = 1.f / float(a.window);
+  // STATS: up to GROUP tiles wait in LDS for the four waves' statistics of a row to be joined, a row per
+  // thread; their rows start at st_row of part_m / part_s
+  size_t st_row = 0;
+  int st_tiles = 0, st_rows = 0, st_group = 0;
+  auto store_stats = [&]() {
+    if ((int)threadIdx.x < st_rows) {
+      float2 x[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) x[w] = stat[st_group * GROUP + wave][w][lane];
+      const float mm = fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x));
+      float ss = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) ss += x[w].y * fast_exp2(x[w].x - mm);
+      part_m[st_row + threadIdx.x] = mm;
+      part_s[st_row + threadIdx.x] = ss;
+    }
+    st_tiles = st_rows = 0;
+    st_group ^= 1;
+  };
+
+  // fragments of block `blk` of the tile in buffer `buf`
+  const int swz = KS == 4 ? (col >> 1) & 7 : col & 15;
+  const int fbase = col * SP * 16 + ((half ^ swz) << 4);
+  auto frag = [&](int buf, int blk, int ks) {
+    int at = fbase;
+    // (opaque where registers are short: no address per k-step is kept)
+    if (REST || (EMIT && KS == 5)) asm volatile("" : "+v"(at));
+    const unsigned char* p = reinterpret_cast<const unsigned char*>(&qtile[buf][blk * 32 * SP]);
+    return *reinterpret_cast<const uint4*>(p + (at ^ (32 * ks)));
+  };
+  uint4 qf[AHEAD];
+  const int wkey0 = chunk * KEYS + wave * 32 * KB;           // first key of the wave
+  const bool active = wkey0 < n;                              // wave-uniform, like the next two
+  const bool ragged = wkey0 + 32 * KB > n;
+  const bool masked = a.causal && wkey0 + 32 * KB - 1 > n - a.window;
+  int sub = 0, heads = a.group;       // EMIT: groups of 8 rows done of the current head; heads left
+  float tacc[KB], gacc[KB];           // EMIT: current head's aggregate, group's
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) { tacc[kb] = TASK_MAX ? NEG_BIG : 0.f; gacc[kb] = 0.f; }
+  auto finish_head = [&]() {
+    // (rows behind the last head are copies of rows before them)
+    if (heads > 0) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const float tv = cross_half<TASK_MAX>(tacc[kb]);
+        const float sv = TASK_MAX ? fast_exp2(tv) : tv * inv_window;
+        gacc[kb] = a.group_max ? fmaxf(gacc[kb], sv) : gacc[kb] + sv;
+        tacc[kb] = TASK_MAX ? NEG_BIG : 0.f;
+      }
+      --heads;
     }
     sub = 0;
   };
-  // STATS: one wave joins the four waves' statistics of tile t (a row per lane)
-  auto store_stats = [&](int t) {
-    const int row = t * TL_ROWS + lane;
-    if (wave != (t & 3) || row >= R) return;
-    float2 x[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) x[w] = stat[t & 1][w][lane];
-    const float mm = fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x));
-    float ss = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) ss += x[w].y * fast_exp2(x[w].x - mm);
-    part_m[(size_t)chunk * a.rows_all + qrow0 + row] = mm;
-    part_s[(size_t)chunk * a.rows_all + qrow0 + row] = ss;
-  };
-
-  for (int t = t_begin; t < t_end; ++t) {
+  auto tile = [&](const int t, auto buffer) __attribute__((always_inline)) {
+    const int buf = buffer;
+    // this tile (RING 3: and the next, which the fragments run into) is complete, and every wave is done
+    // with the tile before, whose buffer the next load takes
     wait_loads();
     wait_lds();
-    __syncthreads();                      // tile t is complete; every wave is done with tile t-1
-    if (!EMIT && t > t_begin) store_stats(t - 1);
-    if (t + 1 < t_end) {
-      issue_tile(t + 1);
-      if (EMIT && wave == 0) next_nl = load_nl(t + 1, next_rest);
+    __syncthreads();
+    if (!EMIT && st_tiles == GROUP) store_stats();
+    if (ahead_t < t_end) issue_tile();
+    const int next_buf = buf + 1 == RING ? 0 : buf + 1;
+    if (RING == 2 || t == t_begin) {
+#pragma unroll
+      for (int ks = 0; ks < AHEAD; ++ks) qf[ks] = frag(buf, 0, ks);
     }
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
-      if (EMIT && !active) break;
       f32x16 acc[KB];
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[kb][r] = 0.f;
-      // EMIT: -lse2 of the lane's rows, read from LDS before the products so that it is there after them
-      float4 nl[4];
-      if (EMIT) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          nl[i] = *reinterpret_cast<const float4*>(&nls[t & 1][blk * 32 + 8 * i + 4 * half]);
-      }
-      const uint4* qrow = &qtile[t & 1][(blk * 32 + col) * PS + half];
+      float4 nl[4];                     // EMIT: lse2 of the lane's rows
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        const uint4 qf = qrow[2 * ks];
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
-          acc[kb] = EMIT ? tile_mma<T>(qf, kf[kb][ks], acc[kb]) : tile_mma<T>(kf[kb][ks], qf, acc[kb]);
+          acc[kb] = EMIT ? tile_mma<T>(qf[ks % AHEAD], kf[kb][ks], acc[kb])
+                         : tile_mma<T>(kf[kb][ks], qf[ks % AHEAD], acc[kb]);
+        // (behind the last tile they are read and not used)
+        if (ks + AHEAD < KS) qf[ks % AHEAD] = frag(buf, blk, ks + AHEAD);
+        else if (blk == 0) qf[ks % AHEAD] = frag(buf, 1, ks + AHEAD - KS);
+        else if (RING > 2) qf[ks % AHEAD] = frag(next_buf, 0, ks + AHEAD - KS);
+        if (EMIT && ks == KS / 2) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            nl[i] = *reinterpret_cast<const float4*>(&lses[buf][blk * 32 + 8 * i + 4 * half]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (!EMIT) {
         if (ragged) {                     // keys past the sequence drop out
+          int mine = wkey0 + 4 * half;    // (opaque, or 32 key positions are formed outside the branch)
+          asm volatile("" : "+v"(mine));
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if (wkey0 + kb * 32 + acc_row(r, half) >= n) acc[kb][r] = -__builtin_inff();
+              if (mine + kb * 32 + acc_row(r, 0) >= n) acc[kb][r] = -__builtin_inff();
         }
         if (masked) {                     // task token m sees keys up to n - window + m
           const int seen = n - a.window + (t * TL_ROWS + blk * 32 + col) % a.window;
+          int mine = wkey0 + 4 * half;
+          asm volatile("" : "+v"(mine));
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if (wkey0 + kb * 32 + acc_row(r, half) > seen) acc[kb][r] = -__builtin_inff();
+              if (mine + kb * 32 + acc_row(r, 0) > seen) acc[kb][r] = -__builtin_inff();
         }
         float amax = acc[0][0];
 #pragma unroll
@@ -278,8 +370,8 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
 #pragma unroll
           for (int r = 0; r < 16; ++r) s += fast_exp2(fmaf(acc[kb][r], a.c2, -mx));
         s = cross_half<false>(s);
-        if (half == 0) stat[t & 1][wave][blk * 32 + col] = make_float2(mx, s);
-      } else {
+        if (half == 0) stat[st_group * GROUP + st_tiles][wave][blk * 32 + col] = make_float2(mx, s);
+      } else if (active) {
         // registers 4 i .. 4 i + 3 hold rows 8 i + 4 half .. + 3 of the block
         if (masked) {                     // on its own, so that the common case has no mask to look at
           int m8 = sub;
@@ -290,43 +382,73 @@ __global__ __launch_bounds__(TL_THREADS, KS > 16 ? 1 : KS > 8 ? 2 : KS > 5 ? 3 :
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
               for (int r = 0; r < 4; ++r)
-                if (wkey0 + kb * 32 + col > seen + r) acc[kb][4 * i + r] = -__builtin_inff();
+                // (a row behind the window is a copy of its last one, which sees every key)
+                if (wkey0 + kb * 32 + col > min(seen + r, n - 1)) acc[kb][4 * i + r] = -__builtin_inff();
             if (++m8 == subs) m8 = 0;
           }
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        auto fold = [&](int i) {
           float4 rest = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (REST) rest = *reinterpret_cast<const float4*>(&rests[t & 1][blk * 32 + 8 * i + 4 * half]);
+          if (REST) rest = *reinterpret_cast<const float4*>(&rests[buf][blk * 32 + 8 * i + 4 * half]);
+          const int rows = a.window - 8 * sub - 4 * half;      // of the four, those in the window
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb) {
-            float x0 = fmaf(acc[kb][4 * i], a.c2, nl[i].x), x1 = fmaf(acc[kb][4 * i + 1], a.c2, nl[i].y);
-            float x2 = fmaf(acc[kb][4 * i + 2], a.c2, nl[i].z), x3 = fmaf(acc[kb][4 * i + 3], a.c2, nl[i].w);
-            if (REST) { x0 += rest.x; x1 += rest.y; x2 += rest.z; x3 += rest.w; }
+            float x0 = fmaf(acc[kb][4 * i], a.c2, -nl[i].x), x1 = fmaf(acc[kb][4 * i + 1], a.c2, -nl[i].y);
+            float x2 = fmaf(acc[kb][4 * i + 2], a.c2, -nl[i].z), x3 = fmaf(acc[kb][4 * i + 3], a.c2, -nl[i].w);
+            if (REST) { x0 -= rest.x; x1 -= rest.y; x2 -= rest.z; x3 -= rest.w; }
             if (TASK_MAX) {
               tacc[kb] = fmaxf(fmaxf(tacc[kb], x0), x1);
               tacc[kb] = fmaxf(fmaxf(tacc[kb], x2), x3);
             } else {
-              tacc[kb] += (fast_exp2(x0) + fast_exp2(x1)) + (fast_exp2(x2) + fast_exp2(x3));
+              tacc[kb] += ((rows > 0 ? fast_exp2(x0) : 0.f) + (rows > 1 ? fast_exp2(x1) : 0.f)) +
+                          ((rows > 2 ? fast_exp2(x2) : 0.f) + (rows > 3 ? fast_exp2(x3) : 0.f));
             }
           }
-          if (++sub == subs) finish_head();
+          ++sub;
+        };
+        if (sub + 4 <= subs) {            // the block ends within the query head
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fold(i);
+          if (sub == subs) finish_head();
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            fold(i);
+            if (sub == subs) finish_head();
+          }
         }
       }
     }
-    if (EMIT && wave == 0 && t + 1 < t_end) store_nl(t + 1, next_nl, next_rest);
-  }
-  if constexpr (!EMIT) {
-    wait_memory();
-    __syncthreads();
-    store_stats(t_end - 1);
+    if (!EMIT) {
+      if (st_tiles++ == 0) st_row = (size_t)chunk * a.rows_all + qrow0 + t * TL_ROWS;
+      st_rows += min(R - t * TL_ROWS, TL_ROWS);
+    }
+  };
+  if constexpr (KS <= 8) {            // the buffers of the ring are constants of the addresses
+    for (int t = t_begin; t < t_end; t += RING) {
+      tile(t, std::integral_constant<int, 0>{});
+      if (t + 1 < t_end) tile(t + 1, std::integral_constant<int, 1>{});
+      if (RING == 3 && t + 2 < t_end) tile(t + 2, std::integral_constant<int, RING - 1>{});
+    }
   } else {
+    int buf = 0;
+    for (int t = t_begin; t < t_end; ++t) {
+      tile(t, buf);
+      buf = buf + 1 == RING ? 0 : buf + 1;
+    }
+  }
+  if constexpr (EMIT) {
     float* out_head = out + (size_t)layer * a.out_layer_stride + (size_t)h * a.total + tok0;
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
       const int key = wkey0 + kb * 32 + col;
       if (half == 0 && key < n) out_head[key] = gacc[kb];
     }
+  }
+  if constexpr (!EMIT) {
+    wait_memory();
+    __syncthreads();
+    store_stats();
   }
 }
 
@@ -337,8 +459,8 @@ inline int tile_ksteps(int dtype, int pieces) {
   if (dtype == KVC_BF16) return ks <= 4 ? 4 : ks <= 5 ? 5 : ks <= 6 ? 6 : ks <= 8 ? 8 : 16;
   return ks <= 4 ? 4 : ks <= 8 ? 8 : ks <= 16 ? 16 : 32;
 }
-// keys per workgroup: two 32-key blocks per wave; one where a row takes 128 registers
-constexpr int tile_keys(int ksteps) { return ksteps > 16 ? 128 : 256; }
+// keys per workgroup of the statistics pass
+constexpr int tile_keys(int ksteps) { return 128 * tile_kb(ksteps); }
 
 }  // namespace
 }  // namespace kvc

@@ -1,0 +1,25 @@
+"""kvc_score where the tiles of query rows of the key-stationary kernels wrap: one to ten tiles of 64
+rows (the emit pass has three in LDS, the statistics pass two and joins the statistics of four at a
+time), the last of them full or not, heads padded to 8 rows or not, rows whose pieces do not fill their slots.
+
+The oracle is float64; the bound is that of tests/test_gpu_score_shapes.py."""
+import pytest
+
+import paper_2509_05165_amd as kv
+from kvc_testlib import DeviceWorkload
+from test_gpu_score_shapes import _check, _scores, _workload
+
+pytestmark = pytest.mark.gpu
+
+CASES = [("bf16", 64, 2, 1, w, [70]) for w in (32, 33, 64, 95, 128, 129, 160, 250, 289, 320)]
+CASES += [("bf16", d, 3, 1, w, [257, 5]) for d in (80, 96, 136, 192) for w in (21, 64, 107)]
+CASES += [("f32", d, 2, 1, w, [200]) for d in (36, 64, 132) for w in (31, 96, 161)]
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,window,lens", CASES)
+@pytest.mark.parametrize("agg", [kv.KVC_AGG_MAX, kv.KVC_AGG_MEAN])
+def test_tiles(dtype, d, hq, hkv, window, lens, agg):
+    print(f"[case] {dtype} d={d} hq={hq} M={window} {lens} agg={agg}", flush=True)
+    w = _workload(dtype, d, hq, hkv, window, lens, layers=1)
+    dw = DeviceWorkload(w)
+    _check(w, _scores(w, dw, dw.ptrs(dw.q), dw.ptrs(dw.k), agg_task=agg), agg_task=agg)
