@@ -38,6 +38,7 @@ __device__ __forceinline__ float load_as_float(const uint16_t* p) {
 
 #include "kvc_score_mfma.h"
 #include "kvc_score_tile.h"
+#include "kvc_score_keys.h"
 
 namespace kvc {
 namespace {
@@ -186,20 +187,38 @@ __global__ __launch_bounds__(256) void score_emit_generic(
 }
 
 // ---------------------------------------------------------------------------
-// lse merge: 16 query rows per workgroup, 16 threads per row stride over the
+// lse merge: 32 query rows per workgroup, 16 threads per row stride over the
 // key chunks (partials are stored [chunk][row], so reads are coalesced).
 // ---------------------------------------------------------------------------
-constexpr int MERGE_ROWS = 16;
+constexpr int MERGE_ROWS = 32;
 // with_rest: lse2 holds a second array behind the first, what rounding took from each entry
 // (float32 callers: at a log-sum-exp of 50 the rounding is 2e-6, more than the rest of the path).
+//
+// START: also what the key-stationary emit pass starts the accumulators of a row from, relative to the first
+// row of its 32-row block, and a flag per row chunk with a row too far from that (the flags are clear).
+// The start values take the place of the first chunk's part_m.
+struct StartArgs {
+  float* start;
+  uint32_t* far;
+  float c2;
+  int head_rows, row_chunks;     // query rows of a KV head
+};
+__device__ __forceinline__ void store_start(const StartArgs& s, int row, float lse, float first) {
+  const float diff = first - lse;                    // (-lse2) - (-lse2 of the first row)
+  s.start[row] = diff * (1.f / s.c2);
+  if (fabsf(diff) > EMIT_SPREAD_LIMIT) {
+    const int head = row / s.head_rows;
+    atomicOr(&s.far[(size_t)head * s.row_chunks + (row - head * s.head_rows) / MF_RCHUNK], 1u);
+  }
+}
 
-__global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_seq, int layers,
-                                                   int chunk_keys,
-                                                   const float* __restrict__ part_m,
+template <bool START>
+__global__ __launch_bounds__(512) void score_merge(SeqTable seq, int rows_per_seq, int layers,
+                                                   int chunk_keys, const float* part_m,
                                                    const float* __restrict__ part_s,
-                                                   float* __restrict__ lse2, int with_rest) {
+                                                   float* __restrict__ lse2, int with_rest, StartArgs st) {
   __shared__ float sm[16][MERGE_ROWS], ss[16][MERGE_ROWS];
-  const int r = threadIdx.x & (MERGE_ROWS - 1), cg = threadIdx.x >> 4;
+  const int r = threadIdx.x & (MERGE_ROWS - 1), cg = threadIdx.x / MERGE_ROWS;
   // rows of every layer of the launch: row = (layer * batch + sequence) * rows_per_seq + ...
   const int rows = rows_per_seq * seq.batch * layers;
   const int row = blockIdx.x * MERGE_ROWS + r;
@@ -219,6 +238,7 @@ __global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_se
   sm[cg][r] = mm;
   ss[cg][r] = acc;
   __syncthreads();
+  float lse = 0.f;
   if (cg == 0 && row < rows && chunks > 0) {
     float top = NEG_BIG;
 #pragma unroll
@@ -226,29 +246,40 @@ __global__ __launch_bounds__(256) void score_merge(SeqTable seq, int rows_per_se
     float tot = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) tot += ss[i][r] * fast_exp2(sm[i][r] - top);
-    const float lg = __log2f(tot), lse = top + lg;
+    const float lg = __log2f(tot);
+    lse = top + lg;
     lse2[row] = lse;
     if (with_rest) lse2[rows + row] = (top - lse) + lg;
+  }
+  // (the rows of a workgroup are one block of a query head: START has windows of whole blocks)
+  if (START && cg == 0) {
+    const float first = __shfl(lse, 0);
+    if (row < rows && chunks > 0) store_start(st, row, lse, first);
   }
 }
 
 // Same merge, one thread per row: for sequences of a few chunks (the 4096-token
 // regime has one), where sixteen lanes per row would mostly idle.
+template <bool START>
 __global__ __launch_bounds__(256) void score_merge_few(SeqTable seq, int rows_per_seq, int layers,
-                                                       int chunk_keys,
-                                                       const float* __restrict__ part_m,
+                                                       int chunk_keys, const float* part_m,
                                                        const float* __restrict__ part_s,
-                                                       float* __restrict__ lse2, int with_rest) {
+                                                       float* __restrict__ lse2, int with_rest, StartArgs st) {
   const int rows = rows_per_seq * seq.batch * layers;
   const int row = blockIdx.x * 256 + threadIdx.x;
-  if (row >= rows) return;
-  const int b = (row / rows_per_seq) % seq.batch;
+  const int b = row < rows ? (row / rows_per_seq) % seq.batch : 0;
   const int n = seq.cu[b + 1] - seq.cu[b];
-  const int chunks = (n + chunk_keys - 1) / chunk_keys;
-  if (chunks == 0) return;
-  float rest;
-  lse2[row] = merge_few(part_m, part_s, row, rows, chunks, rest);
-  if (with_rest) lse2[rows + row] = rest;
+  const int chunks = row < rows ? (n + chunk_keys - 1) / chunk_keys : 0;
+  float lse = 0.f, rest;
+  if (chunks > 0) {
+    lse = merge_few(part_m, part_s, row, rows, chunks, rest);
+    lse2[row] = lse;
+    if (with_rest) lse2[rows + row] = rest;
+  }
+  if (START) {
+    const float first = __shfl(lse, threadIdx.x & 32);         // first row of the block of 32
+    if (chunks > 0) store_start(st, row, lse, first);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -344,8 +375,10 @@ __global__ void score_finish(const float* part, FinishArgs a, SeqTable seq, floa
 
 // The common case of the finish (one row chunk per KV head, no value norms, no
 // forced retention, HKV heads known at compile time): all loads of a thread are
-// independent and in flight together; VEC consecutive tokens per thread.
-template <int HKV, int VEC>
+// independent and in flight together; VEC consecutive tokens per thread.  ROUNDED: every product is
+// rounded before it is summed, as in the general kernel; otherwise the compiler contracts them.  (Both
+// exist because scores decide on ranks: a shape keeps the roundings it always had.)
+template <int HKV, int VEC, bool ROUNDED>
 __global__ __launch_bounds__(256) void score_finish_plain(const float* part, float* S, int total,
                                                           float group_norm, int add_head_mean,
                                                           size_t part_layer_stride,
@@ -356,16 +389,30 @@ __global__ __launch_bounds__(256) void score_finish_plain(const float* part, flo
   part += blockIdx.y * part_layer_stride;
   S += blockIdx.y * layer_stride;
   vec_t v[HKV];
+  if constexpr (ROUNDED) {
+#pragma clang fp contract(off)
 #pragma unroll
-  for (int h = 0; h < HKV; ++h)
-    v[h] = *reinterpret_cast<const vec_t*>(part + (size_t)h * total + c) * group_norm;
-  vec_t sum = v[0];
+    for (int h = 0; h < HKV; ++h)
+      v[h] = *reinterpret_cast<const vec_t*>(part + (size_t)h * total + c) * group_norm;
+    vec_t sum = v[0];
 #pragma unroll
-  for (int h = 1; h < HKV; ++h) sum += v[h];    // same order as the general kernel
-  const vec_t mean = add_head_mean ? sum / float(HKV) : (vec_t)(0.f);
+    for (int h = 1; h < HKV; ++h) sum += v[h];    // same order as the general kernel
+    const vec_t mean = add_head_mean ? sum / float(HKV) : (vec_t)(0.f);
 #pragma unroll
-  for (int h = 0; h < HKV; ++h)
-    *reinterpret_cast<vec_t*>(S + (size_t)h * total + c) = v[h] + mean;
+    for (int h = 0; h < HKV; ++h)
+      *reinterpret_cast<vec_t*>(S + (size_t)h * total + c) = v[h] + mean;
+  } else {
+#pragma unroll
+    for (int h = 0; h < HKV; ++h)
+      v[h] = *reinterpret_cast<const vec_t*>(part + (size_t)h * total + c) * group_norm;
+    vec_t sum = v[0];
+#pragma unroll
+    for (int h = 1; h < HKV; ++h) sum += v[h];
+    const vec_t mean = add_head_mean ? sum / float(HKV) : (vec_t)(0.f);
+#pragma unroll
+    for (int h = 0; h < HKV; ++h)
+      *reinterpret_cast<vec_t*>(S + (size_t)h * total + c) = v[h] + mean;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -532,7 +579,7 @@ ScoreLayout choose_layout(const Problem& pb, const void* const* q, const void* c
 // holds the group partials of the first of them.
 kvc_status finish_scores(const Problem& pb, const FinishArgs& fa, const void* const* v, float* vnorm,
                          const float* part, size_t part_stride, float* S_all, int l0, int layers,
-                         hipStream_t stream) {
+                         hipStream_t stream, bool rounded = false) {
   const int total = int(pb.total);
   const size_t s_stride = size_t(pb.hkv) * total;
   float* S = S_all + size_t(l0) * s_stride;
@@ -558,7 +605,8 @@ kvc_status finish_scores(const Problem& pb, const FinishArgs& fa, const void* co
                     (reinterpret_cast<uintptr_t>(part) | reinterpret_cast<uintptr_t>(S)) % 16 == 0;
 #define KVC_FINISH_PLAIN(HKV, VEC)                                                              \
   KVC_LAUNCH("score_finish", stream,                                                            \
-             score_finish_plain<HKV, VEC><<<dim3((total / VEC + 255) / 256, layers), 256, 0, stream>>>( \
+             (rounded ? score_finish_plain<HKV, VEC, true> : score_finish_plain<HKV, VEC, false>) \
+             <<<dim3((total / VEC + 255) / 256, layers), 256, 0, stream>>>(                     \
                  part, S, total, fa.group_norm, pb.add_head_mean, part_stride, s_stride))
   if (plain && pb.hkv == 8 && vec4) KVC_FINISH_PLAIN(8, 4);
   else if (plain && pb.hkv == 8) KVC_FINISH_PLAIN(8, 1);
@@ -605,11 +653,11 @@ kvc_status score_tiles(const Problem& pb, const ScoreLayout& L, const void* cons
   const dim3 grid(unsigned(flat), pb.hkv, layers);
   const int rows_all = int(a.rows_all), chunks = int((pb.max_seqlen + keys - 1) / keys);
   if (chunks <= 4)
-    KVC_LAUNCH("score_merge", stream, score_merge_few<<<(rows_all + 255) / 256, 256, 0, stream>>>(
-        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4)));
+    KVC_LAUNCH("score_merge", stream, score_merge_few<false><<<(rows_all + 255) / 256, 256, 0, stream>>>(
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4), StartArgs{}));
   else
-    KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4)));
+    KVC_LAUNCH("score_merge", stream, score_merge<false><<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 512, 0, stream>>>(
+        pb.seq, pb.hq * pb.window, layers, keys, part_m, part_s, lse2, int(sizeof(T) == 4), StartArgs{}));
   if (pb.agg_task == KVC_AGG_MAX)
     KVC_LAUNCH("score_tile<emit>", stream, score_tile<T, KS, true, true><<<grid, TL_THREADS, 0, stream>>>(
         qt, kt, pb.seq, a, nullptr, nullptr, lse2, out));
@@ -726,11 +774,34 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     // themselves (two loads a chunk and row), which is a launch of 5 us less (one prompt of 777
     // tokens 107.0 -> 103.5 us, one of 4096 301 -> 294)
     const bool merge = chunks > 4;
+    static const char* ek_env = getenv("KVC_EK");
+    const bool by_keys = !(ek_env && !atoi(ek_env)) && task_max && L.row_chunks > 1 && L.row_chunks <= EK_MAX_CHUNKS;
+    if (chunks > 0 && by_keys) {
+      KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);
+      const StartArgs st{part_m, reinterpret_cast<uint32_t*>(defer.entries), c2, rows_head, L.row_chunks};
+      if (merge)
+        KVC_LAUNCH("score_merge", stream, score_merge<true><<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 512, 0, stream>>>(
+            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0, st));
+      else
+        KVC_LAUNCH("score_merge", stream, score_merge_few<true><<<(rows_all + 255) / 256, 256, 0, stream>>>(
+            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0, st));
+      EmitKeysArgs ea{};
+      ea.batch = pb.batch; ea.hkv = pb.hkv; ea.group = pb.group; ea.window = pb.window; ea.total = total;
+      ea.row_chunks = L.row_chunks; ea.c2 = c2; ea.causal = pb.causal_tail; ea.group_max = group_max;
+      ea.rows_layer = size_t(L.rows_layer); ea.out_layer_stride = size_t(pb.hkv) * total;
+      int64_t pairs = 0;
+      for (int b = 0; b < pb.batch; ++b) pairs += (pb.seq.cu[b + 1] - pb.seq.cu[b] + EK_KEYS - 1) / EK_KEYS;
+      float* dst = pb.hkv > 8 ? reinterpret_cast<float*>(w + L.off_part) : S;
+      KVC_LAUNCH("score_emit_keys", stream, score_emit_keys<<<dim3(unsigned(pairs), pb.hkv, pb.layers), TL_THREADS, 0, stream>>>(
+          qt, kt, pb.seq, ea, st.start, lse2, st.far, dst));
+      fa.row_chunks = 1; fa.chunks_per_head = 1;
+      return finish_scores(pb, fa, v, vnorm, dst, ea.out_layer_stride, S, 0, pb.layers, stream, true);
+    }
     if (chunks > 0) {
       KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);
       if (merge)
-        KVC_LAUNCH("score_merge", stream, score_merge<<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0));
+        KVC_LAUNCH("score_merge", stream, score_merge<false><<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 512, 0, stream>>>(
+            pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0, StartArgs{}));
       float *few_m = merge ? nullptr : part_m, *few_s = merge ? nullptr : part_s;
       if (task_max) {
         KVC_SCORE_MFMA_WQ("score_mfma<emit>", true, true, few_m, few_s, lse2, part_all);
@@ -791,8 +862,8 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
         KVC_LAUNCH("score_stats_generic", stream, score_stats_generic<uint16_t><<<gs, 256, lds_s, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, L.max_chunks,
             pb.causal_tail, part_m, part_s));
-        KVC_LAUNCH("score_merge", stream, score_merge<<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, 0));
+        KVC_LAUNCH("score_merge", stream, score_merge<false><<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 512, 0, stream>>>(
+            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, 0, StartArgs{}));
         KVC_LAUNCH("score_emit_generic", stream, score_emit_generic<uint16_t><<<ge, 256, lds_e, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, lse2, task_max,
             group_max, pb.causal_tail, part));
@@ -802,8 +873,8 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
         KVC_LAUNCH("score_stats_generic", stream, score_stats_generic<float><<<gs, 256, lds_s, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, L.max_chunks,
             pb.causal_tail, part_m, part_s));
-        KVC_LAUNCH("score_merge", stream, score_merge<<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 256, 0, stream>>>(
-            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, 0));
+        KVC_LAUNCH("score_merge", stream, score_merge<false><<<(L.rows_layer + MERGE_ROWS - 1) / MERGE_ROWS, 512, 0, stream>>>(
+            pb.seq, rows_per_seq, 1, chunk, part_m, part_s, lse2, 0, StartArgs{}));
         KVC_LAUNCH("score_emit_generic", stream, score_emit_generic<float><<<ge, 256, lds_e, stream>>>(
             ql, kl, pb.seq, pb.hq, pb.group, pb.window, pb.d, total, c2, chunk, lse2, task_max,
             group_max, pb.causal_tail, part));

@@ -291,6 +291,8 @@ __device__ __forceinline__ void score_mfma_body(
     chunk -= nc;
   }
   const int zid = layer * batch + b;
+  // no row chunk is far from its first rows yet (score_merge may set this)
+  if (!EMIT && chunk == 0 && threadIdx.x == 0) reinterpret_cast<uint32_t*>(defer.entries)[(size_t)zid * gy + by] = 0;
   const uint16_t* __restrict__ q_layer = static_cast<const uint16_t*>(q_tab.p[layer]);
   const uint16_t* __restrict__ k_layer = static_cast<const uint16_t*>(k_tab.p[layer]);
   if (EMIT) out += (size_t)layer * out_layer_stride;
