@@ -10,6 +10,7 @@
 // Three implementations of stats/emit, chosen by type, shape and alignment:
 //   kvc_score_mfma.h  query-stationary matrix-core kernels: bf16, d = 128, windows of 32, 64,
 //                     128 or a multiple of 256
+//   kvc_score_keys.h  the max-pooling emit pass of those shapes, key-stationary: heads of more than 256 rows
 //   kvc_score_tile.h  key-stationary matrix-core kernels: every other shape, both types
 //   the plain kernels below: q or k that do not start at 16-byte addresses, which the 16-byte loads
 //                     of the others need (K goes straight into LDS), and workspaces too small for
@@ -489,6 +490,23 @@ inline int mfma_chunk(const Problem& pb, int row_chunks) {
 constexpr int64_t MF_STREAM_BYTES = int64_t(3) << 27;
 constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact emit launch (two per compute unit)
 
+// Heads of more than one row chunk take the key-stationary emit pass (bit for bit the same scores): K is
+// read once, no wave works on rows that are not there, and the row chunks need no partials.  Score stage
+// in us, query- / key-stationary: 28 layers 28/4 heads M = 64 (448 rows) 1 x 300 tokens 44 / 33, 1 x 8192
+// 282 / 262, 8 x 4096 946 / 919; 40/8 heads M = 128 (640) 1 x 8192 954 / 897, 8 x 4096 3662 / 3421; 80
+// layers 64/8 M = 128 (1024) 8192 2551 / 2465; 32/8 M = 1024 (4096) 8192 3715 / 3586.  Two full row chunks
+// have nothing to gain but the partials, and lose where K comes from memory, because a workgroup waits
+// for its keys before it works on them: 32/8 M = 128 4 x 1500 500 / 486, 1 x 8192 (0.5 GiB of K) 631 / 608,
+// 8 x 4096 (2 GiB) 2070 / 2142; 64/8 M = 64 80 layers 8192 (1.25 GiB) 1376 / 1370, 8 x 4096 5108 / 5292.
+// A few workgroups with very many rows each leave compute units idle: 28/4 heads x 300 tokens (224
+// workgroups) M = 256 (1792 rows) 82 / 80, M = 512 127 / 139, M = 1024 226 / 245.  One row chunk: 32/8 heads
+// 128k tokens 2124 / 2371 (emit pass alone), 8 x 4096 M = 64 1177 / 1269.
+inline bool emit_by_keys(int rows_head, int64_t k_bytes, int64_t workgroups) {
+  if (rows_head <= MF_RCHUNK || rows_head > MF_RCHUNK * EK_MAX_CHUNKS) return false;
+  if (rows_head == 2 * MF_RCHUNK) return k_bytes < int64_t(5) << 27;
+  return workgroups >= 512 || rows_head <= 2048;
+}
+
 // The ways through the stage (see the top of the file).
 enum ScoreRoute { SCORE_QUERY_STATIONARY, SCORE_KEY_STATIONARY, SCORE_PLAIN };
 
@@ -774,8 +792,9 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     // themselves (two loads a chunk and row), which is a launch of 5 us less (one prompt of 777
     // tokens 107.0 -> 103.5 us, one of 4096 301 -> 294)
     const bool merge = chunks > 4;
-    static const char* ek_env = getenv("KVC_EK");
-    const bool by_keys = !(ek_env && !atoi(ek_env)) && task_max && L.row_chunks > 1 && L.row_chunks <= EK_MAX_CHUNKS;
+    int64_t key_pairs = 0;     // (sequence, chunk) pairs of the key-stationary emit pass
+    for (int b = 0; b < pb.batch; ++b) key_pairs += (pb.seq.cu[b + 1] - pb.seq.cu[b] + EK_KEYS - 1) / EK_KEYS;
+    const bool by_keys = task_max && emit_by_keys(rows_head, k_bytes, key_pairs * pb.hkv * pb.layers);
     if (chunks > 0 && by_keys) {
       KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);
       const StartArgs st{part_m, reinterpret_cast<uint32_t*>(defer.entries), c2, rows_head, L.row_chunks};
@@ -789,10 +808,8 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
       ea.batch = pb.batch; ea.hkv = pb.hkv; ea.group = pb.group; ea.window = pb.window; ea.total = total;
       ea.row_chunks = L.row_chunks; ea.c2 = c2; ea.causal = pb.causal_tail; ea.group_max = group_max;
       ea.rows_layer = size_t(L.rows_layer); ea.out_layer_stride = size_t(pb.hkv) * total;
-      int64_t pairs = 0;
-      for (int b = 0; b < pb.batch; ++b) pairs += (pb.seq.cu[b + 1] - pb.seq.cu[b] + EK_KEYS - 1) / EK_KEYS;
       float* dst = pb.hkv > 8 ? reinterpret_cast<float*>(w + L.off_part) : S;
-      KVC_LAUNCH("score_emit_keys", stream, score_emit_keys<<<dim3(unsigned(pairs), pb.hkv, pb.layers), TL_THREADS, 0, stream>>>(
+      KVC_LAUNCH("score_emit_keys", stream, score_emit_keys<<<dim3(unsigned(key_pairs), pb.hkv, pb.layers), TL_THREADS, 0, stream>>>(
           qt, kt, pb.seq, ea, st.start, lse2, st.far, dst));
       fa.row_chunks = 1; fa.chunks_per_head = 1;
       return finish_scores(pb, fa, v, vnorm, dst, ea.out_layer_stride, S, 0, pb.layers, stream, true);
