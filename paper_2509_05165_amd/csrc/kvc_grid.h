@@ -37,4 +37,17 @@ constexpr GridBlock row_chunk_block(uint32_t p, uint32_t gx, uint32_t hkv, uint3
   return {slice - lh * gx, (lh - bz * hkv) * row_chunks + rc, bz};
 }
 
+// The same for batches of unequal sequences: the stretches of K of a sequence's (layer, head) pairs together,
+// bx slowest, so that what bx counts last (the short ones) is worked last and the workgroups that
+// are still running when no others are left are short.
+constexpr GridBlock pair_major_block(uint32_t p, uint32_t gx, uint32_t hkv, uint32_t row_chunks, uint32_t gz) {
+  const uint32_t slices = gx * hkv * gz;
+  const uint32_t first = p / (GRID_GROUP * row_chunks) * GRID_GROUP;      // of the group
+  const uint32_t left = slices - first, here = left < GRID_GROUP ? left : GRID_GROUP;
+  const uint32_t q = p - first * row_chunks, rc = q / here;
+  const uint32_t slice = first + q - rc * here;
+  const uint32_t bx = slice / (hkv * gz), lh = slice - bx * (hkv * gz), bz = lh / hkv;
+  return {bx, (lh - bz * hkv) * row_chunks + rc, bz};
+}
+
 }  // namespace kvc

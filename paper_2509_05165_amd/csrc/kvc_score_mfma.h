@@ -241,6 +241,12 @@ struct DeferList {
   uint64_t* entries;      // device: bx | by << 32 | bz << 56
   uint32_t capacity;
 };
+// Order of the (sequence, chunk) pairs of a batch of unequal sequences: whole chunks, then the last chunks
+// of the sequences that end in a shorter one, longest first.
+struct PairOrder {
+  int32_t whole;                       // whole chunks of the batch; -1: sequence by sequence
+  uint8_t last[KVC_MAX_BATCH];         // sequences with a shorter last chunk
+};
 // A workgroup's LDS: declared in the kernels, so that two forms of the body can share it.
 template <bool EMIT>
 struct MfmaShared {
@@ -261,7 +267,7 @@ __device__ __forceinline__ void score_mfma_body(
     const SeqTable& seq, int hq, int group, int window, int total, float c2, int chunk_keys,
     int row_chunks, float* __restrict__ part_m, float* __restrict__ part_s,
     const float* __restrict__ lse2, int group_max, int causal, float* __restrict__ out,
-    const DeferList& defer, const int bx, const int by, const int bz, const int gy, const int gz) {
+    const DeferList& defer, const PairOrder& order, const int bx, const int by, const int bz, const int gy, const int gz) {
   static_assert(MODE == 0 || (EMIT && TASK_MAX), "modes 1 and 2 are forms of the max-pooling emit pass");
   constexpr bool RECENTRE = MODE == 1;
   constexpr int WK = 4 / WQ;        // waves along the keys
@@ -285,10 +291,16 @@ __device__ __forceinline__ void score_mfma_body(
   if (!EMIT && bx == 0 && by == 0 && bz == 0 && threadIdx.x == 0) *defer.count = 0;
   const int chunk_shift = __builtin_ctz(chunk_keys);   // chunk_keys is a power of two (host-checked)
   int b = 0, chunk = bx;
-  for (; b < batch - 1; ++b) {
-    const int nc = (seq.cu[b + 1] - seq.cu[b] + chunk_keys - 1) >> chunk_shift;
-    if (chunk < nc) break;
-    chunk -= nc;
+  if (order.whole >= 0 && bx >= order.whole) {
+    b = order.last[bx - order.whole];
+    chunk = (seq.cu[b + 1] - seq.cu[b]) >> chunk_shift;
+  } else {
+    const int part = order.whole >= 0 ? 0 : chunk_keys - 1;   // (whole chunks only, or all)
+    for (; b < batch - 1; ++b) {
+      const int nc = (seq.cu[b + 1] - seq.cu[b] + part) >> chunk_shift;
+      if (chunk < nc) break;
+      chunk -= nc;
+    }
   }
   const int zid = layer * batch + b;
   // no row chunk is far from its first rows yet (score_merge may set this)
@@ -756,25 +768,28 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
     float* __restrict__ part_m, float* __restrict__ part_s, const float* __restrict__ lse2,
-    int group_max, int causal, float* __restrict__ out, DeferList defer) {
+    int group_max, int causal, float* __restrict__ out, DeferList defer, PairOrder order) {
   KVC_MFMA_SHARED(EMIT);
   constexpr int MODE = (EMIT && TASK_MAX) ? 1 : 0;
   int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-  if constexpr (REM > 0) {
-    const GridBlock at = row_chunk_block(bx + gridDim.x * (by + gridDim.y * bz), gridDim.x,
-                                         gridDim.y / row_chunks, row_chunks, gridDim.z);
+  if (REM > 0 || order.whole >= 0) {
+    const uint32_t p = bx + gridDim.x * (by + gridDim.y * bz), hkv = gridDim.y / row_chunks;
+    const GridBlock at = order.whole >= 0 ? pair_major_block(p, gridDim.x, hkv, row_chunks, gridDim.z)
+                                          : row_chunk_block(p, gridDim.x, hkv, row_chunks, gridDim.z);
     bx = at.bx; by = at.by; bz = at.bz;
+  }
+  if constexpr (REM > 0) {
     if (by % row_chunks == row_chunks - 1) {
       score_mfma_body<EMIT, TASK_MAX, REM, MODE, STREAM, LSE>(
           sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-          row_chunks, part_m, part_s, lse2, group_max, causal, out, defer,
+          row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order,
           bx, by, bz, (int)gridDim.y, (int)gridDim.z);
       return;
     }
   }
   score_mfma_body<EMIT, TASK_MAX, WQ, MODE, STREAM, LSE>(
       sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-      row_chunks, part_m, part_s, lse2, group_max, causal, out, defer,
+      row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order,
       bx, by, bz, (int)gridDim.y, (int)gridDim.z);
 }
 
@@ -787,7 +802,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
     int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
     float* __restrict__ part_m, float* __restrict__ part_s,
     const float* __restrict__ lse2, int group_max, int causal,
-    float* __restrict__ out, DeferList defer, int gx, int gy, int gz) {
+    float* __restrict__ out, DeferList defer, PairOrder order, int gx, int gy, int gz) {
   KVC_MFMA_SHARED(true);
   const uint32_t listed = min(*defer.count, defer.capacity);     // appended by the launch before this one
   for (uint32_t i = blockIdx.x; i < listed; i += gridDim.x) {
@@ -800,12 +815,12 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
         if (rem)
           score_mfma_body<true, true, REM, 2, false, LSE_EITHER>(
               sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-              row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
+              row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order, bx, by, bz, gy, gz);
       }
       if (!rem)
         score_mfma_body<true, true, WQ, 2, false, LSE_EITHER>(
             sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-            row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, bx, by, bz, gy, gz);
+            row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order, bx, by, bz, gy, gz);
     }
     __syncthreads();   // the next entry reuses the LDS
   }
