@@ -501,8 +501,19 @@ constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact e
 // A few workgroups with very many rows each leave compute units idle: 28/4 heads x 300 tokens (224
 // workgroups) M = 256 (1792 rows) 82 / 80, M = 512 127 / 139, M = 1024 226 / 245.  One row chunk: 32/8 heads
 // 128k tokens 2124 / 2371 (emit pass alone), 8 x 4096 M = 64 1177 / 1269.
-inline bool emit_by_keys(int rows_head, int64_t k_bytes, int64_t workgroups) {
-  if (rows_head <= MF_RCHUNK || rows_head > MF_RCHUNK * EK_MAX_CHUNKS) return false;
+//
+// Heads of one row chunk take it where sequences are short, so that the workgroups of the other have next to
+// nothing to do (32 layers 32/8 heads M = 32 1 x 200 tokens 28.5 / 24.0, 64 x 100 701 / 562, 1 x 512 34.8 / 32.4; but
+// 16 x 300 at M = 64 309 / 335), and where their rows leave waves without work (5 to 7 blocks of 32) as long as K
+// comes out of the cache (28/4 heads M = 32 1 x 1500 66 / 54, 1 x 9000 179 / 165, 4 x 20000 1158 / 1197; 40/8 1 x 2500
+// 182 / 148).
+inline bool emit_by_keys(int rows_head, int64_t k_bytes, int64_t workgroups, int64_t max_seqlen) {
+  if (rows_head <= MF_RCHUNK) {
+    const int blocks = rows_head / 32;
+    return max_seqlen <= EK_KEYS || (max_seqlen <= 2 * EK_KEYS && workgroups <= 1536) ||
+           (blocks > 4 && blocks < 8 && k_bytes < MF_STREAM_BYTES);
+  }
+  if (rows_head > MF_RCHUNK * EK_MAX_CHUNKS) return false;
   if (rows_head == 2 * MF_RCHUNK) return k_bytes < int64_t(5) << 27;
   return workgroups >= 512 || rows_head <= 2048;
 }
@@ -818,25 +829,31 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const bool merge = chunks > 4;
     int64_t key_pairs = 0;     // (sequence, chunk) pairs of the key-stationary emit pass
     for (int b = 0; b < pb.batch; ++b) key_pairs += (pb.seq.cu[b + 1] - pb.seq.cu[b] + EK_KEYS - 1) / EK_KEYS;
-    const bool by_keys = task_max && emit_by_keys(rows_head, k_bytes, key_pairs * pb.hkv * pb.layers);
+    const bool by_keys = task_max && emit_by_keys(rows_head, k_bytes, key_pairs * pb.hkv * pb.layers, pb.max_seqlen);
+    // (heads of one row chunk: the workgroups merge the statistics of a few chunks themselves)
+    const bool own_merge = !merge && L.row_chunks == 1;
     if (chunks > 0 && by_keys) {
       KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);
       const StartArgs st{part_m, reinterpret_cast<uint32_t*>(defer.entries), c2, rows_head, L.row_chunks};
       if (merge)
         KVC_LAUNCH("score_merge", stream, score_merge<true><<<(rows_all + MERGE_ROWS - 1) / MERGE_ROWS, 512, 0, stream>>>(
             pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0, st));
-      else
+      else if (!own_merge)
         KVC_LAUNCH("score_merge", stream, score_merge_few<true><<<(rows_all + 255) / 256, 256, 0, stream>>>(
             pb.seq, rows_per_seq, pb.layers, chunk, part_m, part_s, lse2, 0, st));
       EmitKeysArgs ea{};
       ea.batch = pb.batch; ea.hkv = pb.hkv; ea.group = pb.group; ea.window = pb.window; ea.total = total;
       ea.row_chunks = L.row_chunks; ea.c2 = c2; ea.causal = pb.causal_tail; ea.group_max = group_max;
-      ea.rows_layer = size_t(L.rows_layer); ea.out_layer_stride = size_t(pb.hkv) * total;
+      ea.rows_layer = size_t(L.rows_layer); ea.rows_all = ea.rows_layer * pb.layers;
+      ea.chunk_shift = __builtin_ctz(chunk);
+      ea.out_layer_stride = size_t(pb.hkv) * total;
       float* dst = pb.hkv > 8 ? reinterpret_cast<float*>(w + L.off_part) : S;
-      KVC_LAUNCH("score_emit_keys", stream, score_emit_keys<<<dim3(unsigned(key_pairs), pb.hkv, pb.layers), TL_THREADS, 0, stream>>>(
-          qt, kt, pb.seq, ea, st.start, lse2, st.far, dst));
+      KVC_LAUNCH("score_emit_keys", stream, (own_merge ? score_emit_keys<true> : score_emit_keys<false>)
+          <<<dim3(unsigned(key_pairs), pb.hkv, pb.layers), TL_THREADS, 0, stream>>>(
+          qt, kt, pb.seq, ea, part_m, part_s, st.start, lse2, st.far, dst));
       fa.row_chunks = 1; fa.chunks_per_head = 1;
-      return finish_scores(pb, fa, v, vnorm, dst, ea.out_layer_stride, S, 0, pb.layers, stream, true);
+      // (a head of several row chunks has always been finished with every product rounded)
+      return finish_scores(pb, fa, v, vnorm, dst, ea.out_layer_stride, S, 0, pb.layers, stream, L.row_chunks > 1);
     }
     if (chunks > 0) {
       KVC_SCORE_MFMA_WQ("score_mfma<stats>", false, true, part_m, part_s, nullptr, nullptr);

@@ -25,16 +25,23 @@ struct EmitKeysArgs {
   int batch, hkv, group, window, total, row_chunks;
   float c2;
   int causal, group_max;
-  size_t rows_layer;                           // query rows of a layer: batch * Hq * window
+  size_t rows_layer, rows_all;                 // query rows of a layer (batch * Hq * window), of the launch
+  int chunk_shift;                             // MERGES: log2 of the keys of a statistics chunk
   size_t out_layer_stride;
 };
 
 // grid: ((sequence, chunk) pairs, Hkv, layers)
+//
+// MERGES: heads of one row chunk, statistics of a few chunks: a workgroup merges them for its rows
+// itself (as score_merge_few, bit for bit), and start, lse2 and far are not used.
+template <bool MERGES>
 __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
-    PtrTable q_tab, PtrTable k_tab, SeqTable seq, EmitKeysArgs a, const float* __restrict__ start,
-    const float* __restrict__ lse2, const uint32_t* __restrict__ far, float* __restrict__ out) {
+    PtrTable q_tab, PtrTable k_tab, SeqTable seq, EmitKeysArgs a, const float* __restrict__ part_m,
+    const float* __restrict__ part_s, const float* __restrict__ start, const float* __restrict__ lse2,
+    const uint32_t* __restrict__ far, float* __restrict__ out) {
+  constexpr int ROWBUF = MERGES ? MF_RCHUNK / TL_ROWS : EK_RING;    // tiles whose start values are in LDS
   __shared__ __attribute__((aligned(1024))) unsigned char qtile[EK_RING][EK_TILE];
-  __shared__ __attribute__((aligned(256))) float starts[EK_RING][TL_ROWS], lses[EK_RING][TL_ROWS];
+  __shared__ __attribute__((aligned(256))) float starts[ROWBUF][TL_ROWS], lses[ROWBUF][TL_ROWS];
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 31, half = lane >> 5;
@@ -65,7 +72,7 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
   int ahead_t = 0, ahead_buf = 0;       // the next tile to be asked for, and its buffer
   auto issue_tile = [&]() {
     const int t = ahead_t;
-    if (wave == (t & 3)) {              // a row per lane
+    if (!MERGES && wave == (t & 3)) {   // a row per lane
       const uint32_t off = (uint32_t)min(t * TL_ROWS + lane, R - 1) * 4u;
       lds_dma4_s(reinterpret_cast<const void*>(scalar64(reinterpret_cast<uint64_t>(start + qrow0))), off,
                  __builtin_amdgcn_readfirstlane(starts_lds + ahead_buf * (TL_ROWS * 4)));
@@ -103,7 +110,16 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
   }
   // row chunks that take the exact form
   uint32_t exact_chunks = 0;
-  for (int rc = 0; rc < a.row_chunks; ++rc)
+  if constexpr (MERGES) {
+    const int row = threadIdx.x;
+    float lse = 0.f, rest;
+    if (row < R) lse = merge_few(part_m, part_s, qrow0 + row, a.rows_all, (n + (1 << a.chunk_shift) - 1) >> a.chunk_shift, rest);
+    const float diff = __shfl(lse, lane & 32) - lse;   // (-lse2) - (-lse2 of the first row of the block)
+    starts[0][row] = diff * (1.f / a.c2);
+    lses[0][row] = lse;
+    exact_chunks = __syncthreads_or(row < R && fabsf(diff) > EMIT_SPREAD_LIMIT) ? 1u : 0u;
+  }
+  for (int rc = MERGES ? a.row_chunks : 0; rc < a.row_chunks; ++rc)
     exact_chunks |= (far[(((size_t)layer * a.batch + b) * a.hkv + h) * a.row_chunks + rc] & 1u) << rc;
   exact_chunks = __builtin_amdgcn_readfirstlane(exact_chunks);
 
@@ -125,16 +141,18 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
   };
   uint4 qf[4];                          // fragments run four k-steps ahead of their products
   f32x16 sv;                            // start values of the next block
-  auto load_starts = [&](int buf, int blk) {
+  auto load_starts = [&](int rows, int blk) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float4 v = *reinterpret_cast<const float4*>(&starts[buf][blk * 32 + 8 * i + 4 * half]);
+      const float4 v = *reinterpret_cast<const float4*>(&starts[rows][blk * 32 + 8 * i + 4 * half]);
       sv[4 * i] = v.x; sv[4 * i + 1] = v.y; sv[4 * i + 2] = v.z; sv[4 * i + 3] = v.w;
     }
   };
 
   auto tile = [&](const int t, auto buffer) __attribute__((always_inline)) {
     constexpr int buf = decltype(buffer)::value, next_buf = buf + 1 == EK_RING ? 0 : buf + 1;
+    // (behind the last tile its values are read again and not used)
+    const int rows = MERGES ? t : buf, next_rows = MERGES ? min(t + 1, ROWBUF - 1) : next_buf;
     // this tile and the next, which the fragments run into, are complete, and every wave is done with the
     // tile before, whose buffer the next load takes
     wait_loads();
@@ -144,7 +162,7 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
     if (t == 0) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) qf[ks] = frag(buf, 0, ks);
-      load_starts(buf, 0);
+      load_starts(rows, 0);
     }
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
@@ -152,7 +170,7 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
       if (blk == 1 && block >= blocks) break;
       const bool exact = exact_chunks >> (block >> 3) & 1;
       f32x16 acc[EK_KB];
-      const float base = -lses[buf][blk * 32];
+      const float base = -lses[rows][blk * 32];
       if (exact) {
         asm volatile("");               // (a branch, not 16 selects)
 #pragma unroll
@@ -168,7 +186,7 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
         if (ks < 4) qf[ks] = frag(buf, blk, ks + 4);
         else if (blk == 0) qf[ks & 3] = frag(buf, 1, ks - 4);
         else qf[ks & 3] = frag(next_buf, 0, ks - 4);
-        if (ks == 1) load_starts(blk ? next_buf : buf, blk ^ 1);
+        if (ks == 1) load_starts(blk ? next_rows : rows, blk ^ 1);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (masked) {                     // task token m sees keys up to n - window + m
@@ -185,7 +203,7 @@ __global__ __launch_bounds__(TL_THREADS, 3) void score_emit_keys(
         for (int kb = 0; kb < EK_KB; ++kb) v[kb] = NEG_BIG;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float4 l = *reinterpret_cast<const float4*>(&lses[buf][blk * 32 + 8 * i + 4 * half]);
+          const float4 l = *reinterpret_cast<const float4*>(&lses[rows][blk * 32 + 8 * i + 4 * half]);
 #pragma unroll
           for (int kb = 0; kb < EK_KB; ++kb) {
             v[kb] = fmaxf(fmaxf(v[kb], fmaf(acc[kb][4 * i], c2, -l.x)), fmaf(acc[kb][4 * i + 1], c2, -l.y));

@@ -47,6 +47,26 @@ def test_group_maximum_and_forced_tokens(hq, hkv, window):
         np.testing.assert_allclose(got[0][:, int(w.cu[b]):int(w.cu[b + 1])], ref, rtol=1e-4)
 
 
+@pytest.mark.parametrize("lens", [[200, 3, 256], [400], [3000], [9000]])   # the last: more than four chunks
+@pytest.mark.parametrize("hq,hkv,window", [(1, 1, 32), (5, 1, 32), (7, 1, 32), (2, 1, 64), (3, 1, 64), (2, 1, 128), (1, 1, 256)])
+def test_heads_of_one_row_chunk(hq, hkv, window, lens):
+    print(f"[case] {hq}/{hkv} M={window} {lens}", flush=True)
+    w = _workload(hq, hkv, window, lens)
+    _check(w, _scores(w))
+
+
+def test_one_row_chunk_in_the_exact_form_merging_for_itself():
+    w = _workload(7, 1, 32, [300, 40])
+    for b in range(2):
+        q, k, v = w.seq[b][0]
+        qf = (q.astype(np.uint32) << 16).view(np.float32).copy()
+        qf[:, 1::2] *= 20
+        q = wl.f32_to_bf16_bits(qf)
+        w.seq[b][0] = (q, k, v)
+        w.q[0][b] = q
+    _check(w, _scores(w), dust=1e-30)
+
+
 def test_ten_heads():
     w = _workload(50, 10, 64, [300, 65], layers=2)
     _check(w, _scores(w))
