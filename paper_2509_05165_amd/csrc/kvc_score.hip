@@ -785,7 +785,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     // 2752 / 2854, 40/8 4238 / 4302; with one row chunk there is nothing to lose (M = 64 1499 / 1448, 8 x 4096..
     // 32768 5288 / 5243).
     PairOrder order{};
-    order.whole = -1;
+    int whole_first = -1;
     if (pb.batch > 1 && workgroups < (int64_t(1) << 31)) {
       int last[KVC_MAX_BATCH], whole = 0, count = 0;
       for (int b = 0; b < pb.batch; ++b) {
@@ -796,7 +796,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
       auto rest = [&](int b) { return (pb.seq.cu[b + 1] - pb.seq.cu[b]) % chunk; };
       std::sort(last, last + count, [&](int x, int y) { return rest(x) != rest(y) ? rest(x) > rest(y) : x < y; });
       if (count > 0 && (whole > 0 ? L.row_chunks == 1 || whole <= count : rest(last[0]) > rest(last[count - 1]))) {
-        order.whole = whole;
+        whole_first = whole;
         for (int i = 0; i < count; ++i) order.last[i] = uint8_t(last[i]);
       }
     }
@@ -809,11 +809,11 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
                : (hint_ ? score_mfma<EMIT, TMAX, WQ, REM, (REM) == 0, few_> : score_mfma<EMIT, TMAX, WQ, REM, false, few_>)) \
         <<<dim3(gx, pb.hkv * L.row_chunks, pb.layers), MF_THREADS, 0, stream>>>(                 \
         qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,      \
-        L.row_chunks, PM, PS, LSE, group_max, pb.causal_tail, OUT, defer, order));               \
+        L.row_chunks, whole_first, PM, PS, LSE, group_max, pb.causal_tail, OUT, defer, order));               \
     if (EMIT && TMAX)                                                                            \
       KVC_LAUNCH(NAME ",exact", stream, score_mfma_listed<WQ, REM><<<MF_LISTED_BLOCKS, MF_THREADS, 0, stream>>>( \
           qt, kt, pb.batch, out_stride, pb.seq, pb.hq, pb.group, pb.window, total, c2, chunk,    \
-          L.row_chunks, PM, PS, LSE, group_max, pb.causal_tail, OUT, defer, order, (int)gx, pb.hkv * L.row_chunks, pb.layers)); \
+          L.row_chunks, whole_first, PM, PS, LSE, group_max, pb.causal_tail, OUT, defer, order, (int)gx, pb.hkv * L.row_chunks, pb.layers)); \
   } while (0)
 #define KVC_SCORE_MFMA_WQ(NAME, EMIT, TMAX, PM, PS, LSE, OUT)                                        \
   do {                                                                                             \

@@ -243,8 +243,9 @@ struct DeferList {
 };
 // Order of the (sequence, chunk) pairs of a batch of unequal sequences: whole chunks, then the last chunks
 // of the sequences that end in a shorter one, longest first.
+// (`whole`, the whole chunks of the batch, or -1: sequence by sequence, is an argument among the other
+// numbers, so that a launch in the plain order touches no further line of its arguments.)
 struct PairOrder {
-  int32_t whole;                       // whole chunks of the batch; -1: sequence by sequence
   uint8_t last[KVC_MAX_BATCH];         // sequences with a shorter last chunk
 };
 // A workgroup's LDS: declared in the kernels, so that two forms of the body can share it.
@@ -267,7 +268,7 @@ __device__ __forceinline__ void score_mfma_body(
     const SeqTable& seq, int hq, int group, int window, int total, float c2, int chunk_keys,
     int row_chunks, float* __restrict__ part_m, float* __restrict__ part_s,
     const float* __restrict__ lse2, int group_max, int causal, float* __restrict__ out,
-    const DeferList& defer, const PairOrder& order, const int bx, const int by, const int bz, const int gy, const int gz) {
+    const DeferList& defer, const int whole, const PairOrder& order, const int bx, const int by, const int bz, const int gy, const int gz) {
   static_assert(MODE == 0 || (EMIT && TASK_MAX), "modes 1 and 2 are forms of the max-pooling emit pass");
   constexpr bool RECENTRE = MODE == 1;
   constexpr int WK = 4 / WQ;        // waves along the keys
@@ -291,11 +292,11 @@ __device__ __forceinline__ void score_mfma_body(
   if (!EMIT && bx == 0 && by == 0 && bz == 0 && threadIdx.x == 0) *defer.count = 0;
   const int chunk_shift = __builtin_ctz(chunk_keys);   // chunk_keys is a power of two (host-checked)
   int b = 0, chunk = bx;
-  if (order.whole >= 0 && bx >= order.whole) {
-    b = order.last[bx - order.whole];
+  if (whole >= 0 && bx >= whole) {
+    b = order.last[bx - whole];
     chunk = (seq.cu[b + 1] - seq.cu[b]) >> chunk_shift;
   } else {
-    const int part = order.whole >= 0 ? 0 : chunk_keys - 1;   // (whole chunks only, or all)
+    const int part = whole >= 0 ? 0 : chunk_keys - 1;   // (whole chunks only, or all)
     for (; b < batch - 1; ++b) {
       const int nc = (seq.cu[b + 1] - seq.cu[b] + part) >> chunk_shift;
       if (chunk < nc) break;
@@ -766,15 +767,15 @@ __device__ __forceinline__ void score_mfma_body(
 template <bool EMIT, bool TASK_MAX, int WQ, int REM, bool STREAM, int LSE>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
-    int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
+    int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks, int whole,
     float* __restrict__ part_m, float* __restrict__ part_s, const float* __restrict__ lse2,
     int group_max, int causal, float* __restrict__ out, DeferList defer, PairOrder order) {
   KVC_MFMA_SHARED(EMIT);
   constexpr int MODE = (EMIT && TASK_MAX) ? 1 : 0;
   int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-  if (REM > 0 || order.whole >= 0) {
+  if (REM > 0 || whole >= 0) {
     const uint32_t p = bx + gridDim.x * (by + gridDim.y * bz), hkv = gridDim.y / row_chunks;
-    const GridBlock at = order.whole >= 0 ? pair_major_block(p, gridDim.x, hkv, row_chunks, gridDim.z)
+    const GridBlock at = whole >= 0 ? pair_major_block(p, gridDim.x, hkv, row_chunks, gridDim.z)
                                           : row_chunk_block(p, gridDim.x, hkv, row_chunks, gridDim.z);
     bx = at.bx; by = at.by; bz = at.bz;
   }
@@ -782,14 +783,14 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
     if (by % row_chunks == row_chunks - 1) {
       score_mfma_body<EMIT, TASK_MAX, REM, MODE, STREAM, LSE>(
           sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-          row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order,
+          row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, whole, order,
           bx, by, bz, (int)gridDim.y, (int)gridDim.z);
       return;
     }
   }
   score_mfma_body<EMIT, TASK_MAX, WQ, MODE, STREAM, LSE>(
       sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-      row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order,
+      row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, whole, order,
       bx, by, bz, (int)gridDim.y, (int)gridDim.z);
 }
 
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
 template <int WQ, int REM>
 __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
     PtrTable q_tab, PtrTable k_tab, int batch, size_t out_layer_stride, SeqTable seq,
-    int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks,
+    int hq, int group, int window, int total, float c2, int chunk_keys, int row_chunks, int whole,
     float* __restrict__ part_m, float* __restrict__ part_s,
     const float* __restrict__ lse2, int group_max, int causal,
     float* __restrict__ out, DeferList defer, PairOrder order, int gx, int gy, int gz) {
@@ -815,12 +816,12 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma_listed(
         if (rem)
           score_mfma_body<true, true, REM, 2, false, LSE_EITHER>(
               sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-              row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order, bx, by, bz, gy, gz);
+              row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, whole, order, bx, by, bz, gy, gz);
       }
       if (!rem)
         score_mfma_body<true, true, WQ, 2, false, LSE_EITHER>(
             sh, q_tab, k_tab, batch, out_layer_stride, seq, hq, group, window, total, c2, chunk_keys,
-            row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, order, bx, by, bz, gy, gz);
+            row_chunks, part_m, part_s, lse2, group_max, causal, out, defer, whole, order, bx, by, bz, gy, gz);
     }
     __syncthreads();   // the next entry reuses the LDS
   }

@@ -308,6 +308,14 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS, EMIT, TASK_MAX)) void sc
     if (!EMIT && st_tiles == GROUP) store_stats();
     if (ahead_t < t_end) issue_tile();
     const int next_buf = buf + 1 == RING ? 0 : buf + 1;
+    if (!active) {                      // a wave without keys only keeps the others company
+      if (!EMIT) {
+        stat[st_group * GROUP + st_tiles][wave][lane] = make_float2(NEG_BIG, 0.f);
+        if (st_tiles++ == 0) st_row = (size_t)chunk * a.rows_all + qrow0 + t * TL_ROWS;
+        st_rows += min(R - t * TL_ROWS, TL_ROWS);
+      }
+      return;
+    }
     if (RING == 2 || t == t_begin) {
 #pragma unroll
       for (int ks = 0; ks < AHEAD; ++ks) qf[ks] = frag(buf, 0, ks);
@@ -371,7 +379,7 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS, EMIT, TASK_MAX)) void sc
           for (int r = 0; r < 16; ++r) s += fast_exp2(fmaf(acc[kb][r], a.c2, -mx));
         s = cross_half<false>(s);
         if (half == 0) stat[st_group * GROUP + st_tiles][wave][blk * 32 + col] = make_float2(mx, s);
-      } else if (active) {
+      } else {
         // registers 4 i .. 4 i + 3 hold rows 8 i + 4 half .. + 3 of the block
         if (masked) {                     // on its own, so that the common case has no mask to look at
           int m8 = sub;
