@@ -7,10 +7,11 @@
 //   merge : lse2[row] = log2 sum_c 2^t over all chunks of the row's sequence
 //   emit  : logits again; p = 2^(t - lse2); Agg_task over m, Agg_group over g
 //   finish: combine row-chunk partials, add the mean over KV heads
-// Three implementations of stats/emit, chosen by type, shape and alignment:
+// The implementations of stats/emit, chosen by type, shape and alignment:
 //   kvc_score_mfma.h  query-stationary matrix-core kernels: bf16, d = 128, windows of 32, 64,
 //                     128 or a multiple of 256
-//   kvc_score_keys.h  the max-pooling emit pass of those shapes, key-stationary: heads of more than 256 rows
+//   kvc_score_keys.h  the max-pooling emit pass of those shapes, key-stationary: heads of more than 256 rows,
+//                     and of fewer where those kernels leave waves idle (emit_by_keys)
 //   kvc_score_tile.h  key-stationary matrix-core kernels: every other shape, both types
 //   the plain kernels below: q or k that do not start at 16-byte addresses, which the 16-byte loads
 //                     of the others need (K goes straight into LDS), and workspaces too small for

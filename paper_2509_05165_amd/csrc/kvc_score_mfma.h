@@ -217,9 +217,10 @@ __device__ __forceinline__ float merge_few(const float* __restrict__ part_m, con
 //   the workgroup waits for tile t+1, meets at a barrier, starts the load of
 //   tile t+2 into the buffer of tile t and (EMIT) writes out tile t-1; the last
 //   phase already prefetches the first fragments of tile t+1.
-// In the statistics pass the compiler, which cannot see that the first wait covers the query
-// fragments, puts a vmcnt(0) of its own in front of the first product of every macro tile: there
-// tile t+2 has the last phase of tile t to arrive in, not four phases.  The emit pass has no such wait.
+// The waits are wait_loads, which the compiler sees: behind plain ones it put a vmcnt(0) of its own, for
+// the query fragments, in front of the first product of every macro tile of the statistics pass, and
+// tile t+2 had the last phase of tile t to arrive in, not four phases (whole passes: 32 sequences
+// of 4096 tokens at 40/8 heads 0.9 % shorter without it, 128k tokens in one within noise).
 //
 // causal != 0: task token m sits at position n - window + m of its sequence and
 // sees keys at positions <= that only.  Tiles that lie wholly below position
