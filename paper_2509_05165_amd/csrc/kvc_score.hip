@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "kvc_internal.h"
+#include "kvc_rules.h"
 
 namespace kvc {
 
@@ -479,45 +480,7 @@ inline int mfma_chunk(const Problem& pb, int row_chunks) {
   const int64_t wgs = big_chunks * pb.hkv * row_chunks * pb.batch * pb.layers;
   return wgs >= 2048 ? MF_CHUNK_BIG : MF_CHUNK;
 }
-// The K loads carry the streaming hint (which keeps a pass's partial results in L2 instead) where a
-// launch reads each key once and its K is well beyond the 256 MB memory-side cache: 3/8 GiB and more.
-// Below that the emit pass still finds part of what the statistics pass read, and plain loads
-// are better.  Whole passes of 32 layers in us, plain / hint, by K: 32/8 heads 0.25 GiB 243 / 252,
-// 0.31 347 / 348, 0.38 361 / 354, 0.5 444 / 439, 1 857 / 838, 2 1593 / 1562, 8 6371 / 6314; 16/8
-// heads 0.18 GiB 163 / 183, 0.31 279 / 282, 0.38 316 / 306, 0.5 383 / 365, 2 1354 / 1251; 8/8 heads
-// 0.31 GiB 258 / 262, 0.5 371 / 347.  Row chunks of a head share the reads, where plain loads
-// are better at any size: 80 layers x 64k (four) 21250 / 22250, 16k per head (four) 4792 / 4856,
-// ragged 4k (two) 1684 / 1708.
-constexpr int64_t MF_STREAM_BYTES = int64_t(3) << 27;
 constexpr int MF_LISTED_BLOCKS = 512;   // workgroups of the list-driven exact emit launch (two per compute unit)
-
-// Heads of more than one row chunk take the key-stationary emit pass (bit for bit the same scores): K is
-// read once, no wave works on rows that are not there, and the row chunks need no partials.  Score stage
-// in us, query- / key-stationary: 28 layers 28/4 heads M = 64 (448 rows) 1 x 300 tokens 44 / 33, 1 x 8192
-// 282 / 262, 8 x 4096 946 / 919; 40/8 heads M = 128 (640) 1 x 8192 954 / 897, 8 x 4096 3662 / 3421; 80
-// layers 64/8 M = 128 (1024) 8192 2551 / 2465; 32/8 M = 1024 (4096) 8192 3715 / 3586.  Two full row chunks
-// have nothing to gain but the partials, and lose where K comes from memory, because a workgroup waits
-// for its keys before it works on them: 32/8 M = 128 4 x 1500 500 / 486, 1 x 8192 (0.5 GiB of K) 631 / 608,
-// 8 x 4096 (2 GiB) 2070 / 2142; 64/8 M = 64 80 layers 8192 (1.25 GiB) 1376 / 1370, 8 x 4096 5108 / 5292.
-// A few workgroups with very many rows each leave compute units idle: 28/4 heads x 300 tokens (224
-// workgroups) M = 256 (1792 rows) 82 / 80, M = 512 127 / 139, M = 1024 226 / 245.  One row chunk: 32/8 heads
-// 128k tokens 2124 / 2371 (emit pass alone), 8 x 4096 M = 64 1177 / 1269.
-//
-// Heads of one row chunk take it where sequences are short, so that the workgroups of the other have next to
-// nothing to do (32 layers 32/8 heads M = 32 1 x 200 tokens 28.5 / 24.0, 64 x 100 701 / 562, 1 x 512 34.8 / 32.4; but
-// 16 x 300 at M = 64 309 / 335), and where their rows leave waves without work (5 to 7 blocks of 32) as long as K
-// comes out of the cache (28/4 heads M = 32 1 x 1500 66 / 54, 1 x 9000 179 / 165, 4 x 20000 1158 / 1197; 40/8 1 x 2500
-// 182 / 148).
-inline bool emit_by_keys(int rows_head, int64_t k_bytes, int64_t workgroups, int64_t max_seqlen) {
-  if (rows_head <= MF_RCHUNK) {
-    const int blocks = rows_head / 32;
-    return max_seqlen <= EK_KEYS || (max_seqlen <= 2 * EK_KEYS && workgroups <= 1536) ||
-           (blocks > 4 && blocks < 8 && k_bytes < MF_STREAM_BYTES);
-  }
-  if (rows_head > MF_RCHUNK * EK_MAX_CHUNKS) return false;
-  if (rows_head == 2 * MF_RCHUNK) return k_bytes < int64_t(5) << 27;
-  return workgroups >= 512 || rows_head <= 2048;
-}
 
 // The ways through the stage (see the top of the file).
 enum ScoreRoute { SCORE_QUERY_STATIONARY, SCORE_KEY_STATIONARY, SCORE_PLAIN };
@@ -830,7 +793,7 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const bool merge = chunks > 4;
     int64_t key_pairs = 0;     // (sequence, chunk) pairs of the key-stationary emit pass
     for (int b = 0; b < pb.batch; ++b) key_pairs += (pb.seq.cu[b + 1] - pb.seq.cu[b] + EK_KEYS - 1) / EK_KEYS;
-    const bool by_keys = task_max && emit_by_keys(rows_head, k_bytes, key_pairs * pb.hkv * pb.layers, pb.max_seqlen);
+    const bool by_keys = task_max && emit_by_keys(rows_head, pb.hkv, k_bytes, key_pairs * pb.hkv * pb.layers, pb.max_seqlen);
     // (heads of one row chunk: the workgroups merge the statistics of a few chunks themselves)
     const bool own_merge = !merge && L.row_chunks == 1;
     if (chunks > 0 && by_keys) {

@@ -16,10 +16,9 @@ namespace kvc {
 namespace {
 
 constexpr int EK_KB = 2;                       // 32-key blocks of a wave
-constexpr int EK_KEYS = 4 * 32 * EK_KB;        // keys of a workgroup
+static_assert(EK_KEYS == 4 * 32 * EK_KB, "a block of keys per wave");
 constexpr int EK_RING = 3;
 constexpr int EK_TILE = TL_ROWS * MF_D * 2;    // bytes of a tile of query rows
-constexpr int EK_MAX_CHUNKS = 32;              // row chunks of a head at most (a bit each)
 
 struct EmitKeysArgs {
   int batch, hkv, group, window, total, row_chunks;

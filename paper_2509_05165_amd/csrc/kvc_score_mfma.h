@@ -30,7 +30,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int MF_D = 128;
 constexpr int MF_THREADS = 256;
 constexpr int MF_TILE = 128;                 // keys per LDS macro tile
-constexpr int MF_RCHUNK = 256;               // query rows per workgroup
 constexpr int MF_KBUF = MF_TILE * 256;       // bytes per K buffer
 constexpr int MF_NBUF = 2;
 constexpr int MF_DMA = MF_KBUF / 16 / MF_THREADS;   // direct loads per thread per tile (8)
