@@ -48,14 +48,21 @@ constexpr int tile_slots(int ksteps) { return ksteps <= 4 ? 8 : ksteps <= 8 ? 16
 // takes 373 / 65, with 2 and 3 waves 424 / 72, with three key blocks and 2 waves 402, with four 435.  A third
 // tile lets the emit pass read across the tile border; the statistics pass gains nothing from it (461 / 92
 // with two and with three).  Heads of 80 have no room for it beside four waves: 263 us against 273 (3 waves,
-// three tiles) and 277 before at M = 200, 16 layers of 2 x 4096 tokens.  (light: max pooling; the mean holds more
-// and would spill.)
-constexpr int tile_waves(int ks, bool emit, bool light) {
-  return ks > 16 ? 1 : ks > 8 ? 2 : (ks > 5 ? 3 : 4) - (emit && !light);
-}
+// three tiles) and 277 before at M = 200, 16 layers of 2 x 4096 tokens.
+//
+// The fragments run ahead only as far as the registers of these waves reach without spills.  A
+// float32 step is eight products of 64 cycles, so two steps are plenty; for bf16 heads of 128 two, of
+// 80 one.  With four steps (five at heads of 80) the max pooling forms of heads of 128 and float32 heads of 32 and 64 spilled
+// 4 to 6 registers, and mean pooling had a wave less.  Score stage in us, 16 layers of 32/8 heads, 2 x 1365..4096 tokens (float32
+// 2 x 341..1024), further ahead / now: mean of heads of 128 M = 8 77.8 / 71.5, M = 50 of 28 layers of 28/4 heads 192 / 177,
+// of 80 146 / 141; of float32 64 M = 100 329 / 322; max of heads of 128 M = 8 73.9 / 70.9.
+constexpr int tile_waves(int ks) { return ks > 16 ? 1 : ks > 8 ? 2 : ks > 5 ? 3 : 4; }
 constexpr int tile_kb(int ks) { return ks > 16 ? 1 : 2; }
 constexpr int tile_ring(int ks, bool emit) { return emit && ks <= 8 && ks != 5 ? 3 : 2; }
-constexpr int tile_ahead(int ks) { return ks % 4 == 0 ? 4 : ks; }
+constexpr int tile_ahead(int ks, bool emit, bool f32) {
+  if (emit && (f32 || ks == 8)) return 2;
+  return emit && ks == 5 ? 1 : ks % 4 == 0 ? 4 : ks;      // (divides ks)
+}
 
 // As lds_dma16_s, 4 bytes per lane.
 __device__ __forceinline__ void lds_dma4_s(const void* sbase, uint32_t voff, uint32_t lds_base) {
@@ -102,7 +109,7 @@ __device__ __forceinline__ f32x16 tile_mma(uint4 rows, uint4 cols, f32x16 acc) {
 // chunk prefetched into registers while a workgroup walks over chunks (543 + 436), fixed wave priorities (537 +
 // 436), two accumulator sets and one wave less (5 % slower at heads of 64).
 template <typename T, int KS, bool EMIT, bool TASK_MAX>
-__global__ __launch_bounds__(TL_THREADS, tile_waves(KS, EMIT, TASK_MAX)) void score_tile(
+__global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
     PtrTable q_tab, PtrTable k_tab, SeqTable seq, TileArgs a, float* __restrict__ part_m,
     float* __restrict__ part_s, const float* __restrict__ lse2, float* __restrict__ out) {
   constexpr int SP = tile_slots(KS);            // 16-byte slots per row in LDS
@@ -110,7 +117,7 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS, EMIT, TASK_MAX)) void sc
   constexpr int DMA = TL_ROWS / RPD / 4;        // load instructions per wave and tile
   constexpr int KB = tile_kb(KS), KEYS = 4 * 32 * KB;
   constexpr int RING = tile_ring(KS, EMIT);
-  constexpr int AHEAD = tile_ahead(KS);
+  constexpr int AHEAD = tile_ahead(KS, EMIT, sizeof(T) == 4);
   // EMIT, float32: the log-sum-exps carry what rounding took from them, too
   constexpr bool REST = EMIT && sizeof(T) == 4;
   __shared__ __attribute__((aligned(1024))) uint4 qtile[RING][TL_ROWS * SP];
