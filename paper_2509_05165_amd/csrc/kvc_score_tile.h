@@ -51,16 +51,16 @@ constexpr int tile_slots(int ksteps) { return ksteps <= 4 ? 8 : ksteps <= 8 ? 16
 // three tiles) and 277 before at M = 200, 16 layers of 2 x 4096 tokens.
 //
 // The fragments run ahead only as far as the registers of these waves reach without spills.  A
-// float32 step is eight products of 64 cycles, so two steps are plenty; for bf16 heads of 128 two, of
-// 80 one.  With four steps (five at heads of 80) the max pooling forms of heads of 128 and float32 heads of 32 and 64 spilled
+// float32 step is eight products of 64 cycles, so two steps are plenty; for bf16 heads of 128 two (and for
+// the mean of heads of 64), of 80 one.  With four steps (five at heads of 80) the max pooling forms of heads of 128 and float32 heads of 32 and 64 spilled
 // 4 to 6 registers, and mean pooling had a wave less.  Score stage in us, 16 layers of 32/8 heads, 2 x 1365..4096 tokens (float32
 // 2 x 341..1024), further ahead / now: mean of heads of 128 M = 8 77.8 / 71.5, M = 50 of 28 layers of 28/4 heads 192 / 177,
 // of 80 146 / 141; of float32 64 M = 100 329 / 322; max of heads of 128 M = 8 73.9 / 70.9.
 constexpr int tile_waves(int ks) { return ks > 16 ? 1 : ks > 8 ? 2 : ks > 5 ? 3 : 4; }
 constexpr int tile_kb(int ks) { return ks > 16 ? 1 : 2; }
 constexpr int tile_ring(int ks, bool emit) { return emit && ks <= 8 && ks != 5 ? 3 : 2; }
-constexpr int tile_ahead(int ks, bool emit, bool f32) {
-  if (emit && (f32 || ks == 8)) return 2;
+constexpr int tile_ahead(int ks, bool emit, bool mean, bool f32) {
+  if (emit && (f32 || ks == 8 || (ks == 4 && mean))) return 2;
   return emit && ks == 5 ? 1 : ks % 4 == 0 ? 4 : ks;      // (divides ks)
 }
 
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
   constexpr int DMA = TL_ROWS / RPD / 4;        // load instructions per wave and tile
   constexpr int KB = tile_kb(KS), KEYS = 4 * 32 * KB;
   constexpr int RING = tile_ring(KS, EMIT);
-  constexpr int AHEAD = tile_ahead(KS, EMIT, sizeof(T) == 4);
+  constexpr int AHEAD = tile_ahead(KS, EMIT, !TASK_MAX, sizeof(T) == 4);
   // EMIT, float32: the log-sum-exps carry what rounding took from them, too
   constexpr bool REST = EMIT && sizeof(T) == 4;
   __shared__ __attribute__((aligned(1024))) uint4 qtile[RING][TL_ROWS * SP];
@@ -402,10 +402,13 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
             if (++m8 == subs) m8 = 0;
           }
         }
-        auto fold = [&](int i) {
+        // whole: all rows lie in the window (or don't matter, being copies: the maximum), and the mean looks at
+        // none of them.  Mean pooling, score stage in us, each row looked at / not: 16 layers of 32/8 heads, 2 x 1365..4096
+        // tokens, heads of 128 M = 200 357 / 341, of 80 M = 100 163 / 157; float32 heads of 32, 2 x 341..1024, M = 100 125.8 / 123.4.
+        auto fold = [&](int i, auto whole) {
           float4 rest = make_float4(0.f, 0.f, 0.f, 0.f);
           if (REST) rest = *reinterpret_cast<const float4*>(&rests[buf][blk * 32 + 8 * i + 4 * half]);
-          const int rows = a.window - 8 * sub - 4 * half;      // of the four, those in the window
+          const int rows = decltype(whole)::value ? 4 : a.window - 8 * sub - 4 * half;
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb) {
             float x0 = fmaf(acc[kb][4 * i], a.c2, -nl[i].x), x1 = fmaf(acc[kb][4 * i + 1], a.c2, -nl[i].y);
@@ -421,14 +424,14 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
           }
           ++sub;
         };
-        if (sub + 4 <= subs) {            // the block ends within the query head
+        if (TASK_MAX ? sub + 4 <= subs : 8 * sub + 32 <= a.window) {   // the block ends within the query head
 #pragma unroll
-          for (int i = 0; i < 4; ++i) fold(i);
+          for (int i = 0; i < 4; ++i) fold(i, std::true_type{});
           if (sub == subs) finish_head();
         } else {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            fold(i);
+            fold(i, std::integral_constant<bool, TASK_MAX>{});
             if (sub == subs) finish_head();
           }
         }
