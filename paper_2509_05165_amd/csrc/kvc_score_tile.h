@@ -246,8 +246,18 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
     for (int kb = 0; kb < KB; ++kb) {
       const uint32_t off = (uint32_t)(min(kb * 32 + col, behind) * P) * 16u;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)   // (pieces past the row: any will do, they meet zeros)
+      for (int ks = 0; ks < KS; ++ks)
         kf[kb][ks] = load16(base, off + min(2 * ks + half, P - 1) * 16);
+    }
+    // pieces past the row are zero, like those of the queries that they meet: a copy of the last piece would
+    // make a logit of minus infinity NaN
+    if (P < 2 * KS) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        if (2 * ks + half >= P) {
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) kf[kb][ks] = make_uint4(0, 0, 0, 0);
+        }
     }
   }
   const int subs = a.head_rows >> 3;                              // EMIT: groups of 8 rows per query head
