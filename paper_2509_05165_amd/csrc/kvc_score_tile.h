@@ -18,7 +18,11 @@
 //
 // LDS tile: row r at slot r * SP (SP slots of 16 bytes, a power of two, so that a direct global->LDS
 // load brings whole rows), its piece p at slot p ^ f(r) of the row, so that the reads of 16 consecutive
-// rows cover all banks.  Slots of pieces past the row (head sizes of 80, 96, ...) are zero.
+// rows cover all banks.  Rows that don't fill their k-steps (head sizes of 72, 192, ...) end in copies of their
+// last piece, which meet zeros of the keys; slots past the k-steps (80, 96, ...) are never read.  Clearing the tiles
+// instead cost every workgroup up to 64 KB of LDS writes and a barrier: score stage in us, cleared / now, 28 layers of
+// 16/8 heads, M = 14, heads of 192 5662 tokens 236.9 / 209.0, of 104 10662 tokens 222.1 / 209.1, float32 heads of 48
+// 3000 tokens 120.5 / 114.7.
 #pragma once
 
 namespace kvc {
@@ -57,6 +61,7 @@ constexpr int tile_slots(int ksteps) { return ksteps <= 4 ? 8 : ksteps <= 8 ? 16
 // 2 x 341..1024), further ahead / now: mean of heads of 128 M = 8 77.8 / 71.5, M = 50 of 28 layers of 28/4 heads 192 / 177,
 // of 80 146 / 141; of float32 64 M = 100 329 / 322; max of heads of 128 M = 8 73.9 / 70.9.
 constexpr int tile_waves(int ks) { return ks > 16 ? 1 : ks > 8 ? 2 : ks > 5 ? 3 : 4; }
+constexpr int tile_least(int ks) { return ks <= 4 ? 1 : ks <= 5 ? 9 : ks <= 6 ? 11 : ks <= 8 ? 9 : ks + 1; }   // pieces of a row
 constexpr int tile_kb(int ks) { return ks > 16 ? 1 : 2; }
 constexpr int tile_ring(int ks, bool emit) { return emit && ks <= 8 && ks != 5 ? 3 : 2; }
 constexpr int tile_ahead(int ks, bool emit, bool mean, bool f32) {
@@ -160,16 +165,11 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
   const uint32_t qtile_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint4*)(&qtile[0][0]);
   const uint32_t lses_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)(&lses[0][0]);
   const uint32_t rests_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)(&rests[0][0]);
-  auto lane_piece = [&](int i) {        // piece of the row that lands in the lane's slot
+  auto lane_slot = [&](int i) {         // what the k-steps read in the lane's slot: piece of a padded row
     const int swz = KS == 4 ? (wave * 4 + (rr >> 1)) & 7 : ((i * 4 * RPD) & 15) ^ ((wave * RPD + rr) & 15);
     return slot ^ swz;
   };
-  // slots of pieces past the row are zero and stay so
-  if (P < SP) {
-    for (int i = threadIdx.x; i < RING * TL_ROWS * SP; i += TL_THREADS) (&qtile[0][0])[i] = make_uint4(0, 0, 0, 0);
-    wait_lds();
-    __syncthreads();
-  }
+  auto lane_piece = [&](int i) { return min(lane_slot(i), P - 1); };    // (past the row its last one: they meet zeros)
   const uint32_t qoff = (uint32_t)((wave * RPD + rr) * P + lane_piece(0)) * 16u;
   // query row (among the head's group * window) behind row `pr` in tile order, and how many of its head follow
   auto source_row = [&](uint32_t pr, int& behind) -> int {
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
       for (int i = 0; i < DMA; ++i) {
         const uint64_t base = scalar64(tile + (uint32_t)(i * 4 * RPD * 16) * (uint32_t)P);
         const uint32_t off = RPD >= 4 ? qoff : (uint32_t)((wave * RPD + rr) * P + lane_piece(i)) * 16u;
-        if (lane_piece(i) < P)
+        if (SP == 2 * KS || lane_slot(i) < 2 * KS)
           lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, __builtin_amdgcn_readfirstlane(dst + i * 4096));
       }
     } else {
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
         const int row = source_row(pr, behind);
         const uint64_t base = scalar64(reinterpret_cast<uint64_t>(q_head) + (uint64_t)(uint32_t)row * (uint32_t)(P * 16));
         const uint32_t off = (uint32_t)(min(rrow, behind) * P + lane_piece(i)) * 16u;
-        if (lane_piece(i) < P)
+        if (SP == 2 * KS || lane_slot(i) < 2 * KS)
           lds_dma16_s<false>(reinterpret_cast<const void*>(base), off, __builtin_amdgcn_readfirstlane(dst + i * 4096));
       }
     }
@@ -242,23 +242,27 @@ __global__ __launch_bounds__(TL_THREADS, tile_waves(KS)) void score_tile(
     typedef const __attribute__((address_space(1))) char* global_ptr;
     const global_ptr base = (global_ptr)scalar64(reinterpret_cast<uint64_t>(k_tab.p[layer]) +
         (((uint64_t)(uint32_t)h * (uint32_t)a.total + (uint32_t)(tok0 + row)) * (uint32_t)(P * 16)));
+    // (a row piece by piece: with the two rows of a lane in turn the parts of a 128-byte line are asked for too
+    // far apart, 75 -> 94 us for 66k tokens in heads of 104)
+    auto load_keys = [&](auto full) {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      const uint32_t off = (uint32_t)(min(kb * 32 + col, behind) * P) * 16u;
+      for (int kb = 0; kb < KB; ++kb) {
+        const uint32_t off = (uint32_t)(min(kb * 32 + col, behind) * P) * 16u + half * 16u;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        kf[kb][ks] = load16(base, off + min(2 * ks + half, P - 1) * 16);
-    }
-    // pieces past the row are zero, like those of the queries that they meet: a copy of the last piece would
-    // make a logit of minus infinity NaN
-    if (P < 2 * KS) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        if (2 * ks + half >= P) {
-#pragma unroll
-          for (int kb = 0; kb < KB; ++kb) kf[kb][ks] = make_uint4(0, 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks) {
+          kf[kb][ks] = make_uint4(0, 0, 0, 0);
+          if (decltype(full)::value || 2 * ks + 1 < tile_least(KS) || 2 * ks + half < P)
+            kf[kb][ks] = load16(base, off + ks * 32);
         }
-    }
+      }
+    };
+    // Rows that don't fill their k-steps: pieces past the row are zero (times a copy of the last piece, which the
+    // queries have there, a key of minus infinity would make the logit NaN).  Full rows have a path without the
+    // branches between the loads, which cost them up to 11 % (heads of 64, M = 6, 32 layers of 16788 tokens); where
+    // only the last piece may be past the row one masked load is the faster form (heads of 80, M = 14, 28 layers of
+    // 16/8 heads, 10662 tokens, 157.8 us against 170.5 with two paths).
+    if ((KS != 5 && KS != 6) && P == 2 * KS) load_keys(std::true_type{});
+    else load_keys(std::false_type{});
   }
   const int subs = a.head_rows >> 3;                              // EMIT: groups of 8 rows per query head
   const float inv_window = 1.f / float(a.window);
