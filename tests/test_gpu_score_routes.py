@@ -1,7 +1,9 @@
-"""kvc_score at the forms of the query-stationary kernels: one, two and four waves along the rows, a
+"""kvc_score at the shapes of the query-stationary kernels: one, two and four waves along the rows, a
 short last row chunk worked by one or two of them (1 to 4 blocks of 32 rows left over 256), up to
 four chunks of keys (the emit pass merges the statistics itself) and more (a launch of its own), the two
-aggregators, the causal mask, and workgroups that hand themselves to the exact form.
+aggregators, the causal mask, and workgroups that hand themselves to the exact form.  The max-pooling emit
+pass of most heads of more than 256 rows is the key-stationary one: EMIT_SHAPES lists heads whose emit pass
+is query-stationary, and the tests over it look at the kernels that ran.
 
 The oracle is float64.  A logit is a float32 sum of 128 products: about sqrt(128) 2^-24 |q| |k| scale
 <= 11 * 6e-8 * 60 = 4e-5 with these inputs' sinks, and a score is relative to exp(logit): 1e-4."""
@@ -16,6 +18,7 @@ from kvc_testlib import DeviceWorkload, Workload, stream
 
 pytestmark = pytest.mark.gpu
 
+EMIT, EMIT_KEYS = "score_mfma<emit>", "score_emit_keys"
 MEAN = dict(agg_task=kv.KVC_AGG_MEAN)
 CAUSAL = dict(causal_tail=1)
 SHAPES = [   # hq, hkv, window: rows of a KV head
@@ -29,6 +32,15 @@ SHAPES = [   # hq, hkv, window: rows of a KV head
     (6, 2, 128),     # 256 + 128
     (7, 1, 128),     # 3 x 256 + 128
 ]
+# few keys for the rows of a head, or few workgroups of very many rows: the emit pass of max pooling is the
+# query-stationary one.  hq, hkv, window, tokens
+EMIT_SHAPES = [
+    (2, 2, 64, 700), (4, 2, 64, 700), (4, 1, 64, 700),
+    (7, 1, 64, 130),                                    # 256 + 192
+    (9, 1, 32, 130), (10, 2, 64, 140), (33, 1, 64, 300),      # a short form of one wave along the rows
+    (11, 1, 32, 200), (6, 2, 128, 200), (7, 1, 128, 700), (67, 1, 32, 300),   # of two
+    (33, 1, 64, 8300), (67, 1, 32, 8300),               # the same and a merge of more than four chunks
+]
 
 
 def _workload(hq, hkv, window, lens, layers=1, **over):
@@ -36,13 +48,61 @@ def _workload(hq, hkv, window, lens, layers=1, **over):
     return Workload(cfg, seed=6, lens=lens)
 
 
-def _scores(w, **pkw):
+def _scores(w, ran=None, **pkw):
+    """ran: a set that the names of the kernels are added to."""
     dw = DeviceWorkload(w)
     S = torch.full((w.cfg.layers, w.cfg.hkv, w.total), -1.0, device="cuda")
-    kv.kvc_score(w.params(**pkw), dw.ptrs(dw.q), dw.ptrs(dw.k), w.cu, S.data_ptr(), dw.ws.data_ptr(), dw.ws_bytes,
-                 stream())
+    if ran is not None:
+        kv.kvc_profile_collect()
+        kv.kvc_profile_enable(True)
+    try:
+        kv.kvc_score(w.params(**pkw), dw.ptrs(dw.q), dw.ptrs(dw.k), w.cu, S.data_ptr(), dw.ws.data_ptr(), dw.ws_bytes,
+                     stream())
+    finally:
+        if ran is not None:
+            kv.kvc_profile_enable(False)
+            ran.update(kv.kvc_profile_collect())
     torch.cuda.synchronize()
     return S.cpu().numpy()
+
+
+def _many_layers(w, layers, ran, **pkw):
+    """Scores of a launch of `layers` layers that all have the queries and keys of layer 0.  ran: as in _scores."""
+    dw, c = DeviceWorkload(w), w.cfg
+    p = kv.KvcParams(c.batch, layers, c.hq, c.hkv, c.head_dim, c.window, w.dtype, **pkw)
+    size = kv.kvc_workspace_size(p, w.total, int(w.lens.max()))
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    S = torch.full((layers, c.hkv, w.total), -1.0, device="cuda")
+    kv.kvc_profile_collect()
+    kv.kvc_profile_enable(True)
+    try:
+        kv.kvc_score(p, dw.ptrs(dw.q) * layers, dw.ptrs(dw.k) * layers, w.cu, S.data_ptr(), ws.data_ptr(), size, stream())
+    finally:
+        kv.kvc_profile_enable(False)
+        ran.update(kv.kvc_profile_collect())
+    torch.cuda.synchronize()
+    return S
+
+
+def _sharpen(w, heads=slice(None), rows=slice(1, None, 2)):
+    """Layer 0: queries of these heads and rows 20 times sharper.  The log-sum-exps of a block of 32 rows then lie
+    more than 64 log2 units apart, which the cheap form of the max-pooling emit pass does not take."""
+    for b in range(w.cfg.batch):
+        q, k, v = w.seq[b][0]
+        qf = (q.astype(np.uint32) << 16).view(np.float32).copy()
+        qf[heads, rows] *= 20
+        q = wl.f32_to_bf16_bits(qf)
+        w.seq[b][0] = (q, k, v)
+        w.q[0][b] = q
+
+
+def _spread(w, b=0):
+    """Distance of the log-sum-exps from the first of their block of 32 rows, [blocks, 32]."""
+    q, k, _ = w.seq[b][0]
+    logits = np.einsum("hmd,hnd->hmn", orc.widen(q), np.repeat(orc.widen(k), w.cfg.hq // w.cfg.hkv, axis=0)) / np.sqrt(128.0)
+    top = logits.max(axis=2, keepdims=True)
+    lse2 = ((np.log(np.exp(logits - top).sum(axis=2, keepdims=True)) + top)[..., 0] / np.log(2.0)).reshape(-1, 32)
+    return np.abs(lse2 - lse2[:, :1])
 
 
 def _check(w, got, dust=0.0, **pkw):
@@ -50,6 +110,7 @@ def _check(w, got, dust=0.0, **pkw):
         for l in range(w.cfg.layers):
             ref = orc.score_layer(orc.widen(w.seq[b][l][0]), orc.widen(w.seq[b][l][1]),
                                   agg_task=pkw.get("agg_task", kv.KVC_AGG_MAX),
+                                  agg_group=pkw.get("agg_group", kv.KVC_AGG_MEAN),
                                   causal_tail=bool(pkw.get("causal_tail", 0)))
             mine = got[l][:, int(w.cu[b]):int(w.cu[b + 1])]
             big = ref > dust
@@ -77,21 +138,35 @@ def test_short_row_chunk_in_a_ragged_batch(pkw):
 @pytest.mark.parametrize("n", [700, 8300])
 @pytest.mark.parametrize("hq,hkv,window", SHAPES)
 def test_rows_too_far_apart_for_the_cheap_form(hq, hkv, window, n):
-    """Every second query is 20 times sharper: the log-sum-exps of a block lie more than 64 log2 units
-    apart, in the long row chunks and in the short one, and the exact kernel redoes all workgroups."""
+    """In the query-stationary emit pass the exact kernel redoes all workgroups, in the key-stationary one
+    every row chunk takes the exact form."""
     print(f"[case] exact form {hq}/{hkv} M={window} n={n}", flush=True)
     w = _workload(hq, hkv, window, [n])
-    q, k, v = w.seq[0][0]
-    qf = (q.astype(np.uint32) << 16).view(np.float32).copy()
-    qf[:, 1::2] *= 20
-    q = wl.f32_to_bf16_bits(qf)
-    w.seq[0][0] = (q, k, v)
-    w.q[0][0] = q
-    logits = np.einsum("hmd,hnd->hmn", orc.widen(q), np.repeat(orc.widen(k), hq // hkv, axis=0)) / np.sqrt(128.0)
-    top = logits.max(axis=2, keepdims=True)
-    lse2 = ((np.log(np.exp(logits - top).sum(axis=2, keepdims=True)) + top)[..., 0] / np.log(2.0)).reshape(-1, 32)
-    assert np.all(np.abs(lse2 - lse2[:, :1]).max(axis=1) > 64)
+    _sharpen(w)
+    assert np.all(_spread(w).max(axis=1) > 64)
     _check(w, _scores(w), dust=1e-30)
+
+
+@pytest.mark.parametrize("pkw", [{}, CAUSAL, dict(agg_group=kv.KVC_AGG_MAX)])
+@pytest.mark.parametrize("hq,hkv,window,n", EMIT_SHAPES)
+def test_forms_of_the_emit_pass(hq, hkv, window, n, pkw):
+    print(f"[case] emit {hq}/{hkv} M={window} n={n} {pkw}", flush=True)
+    w, ran = _workload(hq, hkv, window, [n]), set()
+    got = _scores(w, ran, **pkw)
+    assert EMIT in ran and EMIT_KEYS not in ran
+    _check(w, got, **pkw)
+
+
+@pytest.mark.parametrize("hq,hkv,window,n", EMIT_SHAPES)
+def test_the_exact_form_of_the_emit_pass(hq, hkv, window, n):
+    """In the long row chunks and in the short one, all of whose workgroups are on the list."""
+    print(f"[case] emit, exact form {hq}/{hkv} M={window} n={n}", flush=True)
+    w, ran = _workload(hq, hkv, window, [n]), set()
+    _sharpen(w)
+    assert np.all(_spread(w).max(axis=1) > 64)
+    got = _scores(w, ran)
+    assert EMIT in ran and EMIT_KEYS not in ran
+    _check(w, got, dust=1e-30)
 
 
 @pytest.mark.parametrize("lens", [[900, 300], [2000, 1300]])      # up to four chunks, and more
