@@ -65,4 +65,28 @@ inline bool emit_by_keys(int rows_head, int hkv, int64_t k_bytes, int64_t workgr
          workgroups >= (max_seqlen > EK_KEYS / 2 && max_seqlen <= EK_KEYS ? 128 : 192);
 }
 
+// Sequences of unequal lengths: the longest workgroups first, whatever their sequence, so that
+// long ones are neither left over at the end nor paired with short ones.  Score stage in us, sequence by
+// sequence / longest first: 16 x 150..4096 tokens 32/8 heads M = 32 1055 / 900, M = 64 1553 / 1303, M = 128
+// 2856 / 2469, 28/4 heads M = 64 1152 / 1041, 40/8 heads 2491 / 2194; 32 x 100..1500 M = 64 1299 / 1054;
+// 2 x 1000..3000 191 / 153.  Where most workgroups have a whole chunk the row chunks of a slice of
+// K no longer run side by side, which costs more than the order gives: 3 x 5000..20000 M = 128 32/8 heads
+// 2752 / 2854, 40/8 4238 / 4302; with one row chunk there is nothing to lose (M = 64 1499 / 1448, 8 x 4096..
+// 32768 5288 / 5243).
+//
+// The order costs a workgroup some 0.5 us before its first load.  That is lost where every workgroup has a
+// compute unit to itself, and where they are equally long: 6/2 heads M = 32 130 + 597 tokens 25.5 / 27.5, 16 layers of
+// 16/8 42 + 136 14.4 / 15.4, 8/8 M = 256 46..70 (one tile each) 22.7 / 25.2, 28 layers of 28/4 M = 512 26..66 169 / 181.
+// Equally long ones still gain in batches of many sequences, because no workgroup looks for its own: 16 short
+// sequences, 8/1 heads M = 512 32768 workgroups 1250 / 1161, M = 64 1024 45.5 / 42.3.  Over 924 ragged batches of 2..16
+// sequences the choice costs 0.3 % on average against the better order of each, where the order always costs 2.0 %, never 5.6 %.
+//
+// whole: whole chunks of the batch, last: sequences that end in a shorter one; longest, shortest: workgroups in
+// tiles of keys.
+inline bool longest_first(int64_t workgroups, int row_chunks, int whole, int last, int longest, int shortest) {
+  if (last == 0 || workgroups <= 256 || workgroups >= int64_t(1) << 31) return false;
+  if (longest == shortest && last < 12) return false;
+  return whole == 0 || row_chunks == 1 || whole <= last;
+}
+
 }  // namespace kvc

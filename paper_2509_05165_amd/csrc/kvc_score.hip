@@ -740,17 +740,10 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
     const DeferList defer{reinterpret_cast<uint32_t*>(w + L.off_defer),
                           reinterpret_cast<uint64_t*>(w + L.off_defer + align_up(4)),
                           uint32_t(std::min<size_t>(L.defer_capacity, 0xffffffffu))};
-    // Sequences of unequal lengths: the longest workgroups first, whatever their sequence, so that
-    // long ones are neither left over at the end nor paired with short ones.  Score stage in us, sequence by
-    // sequence / longest first: 16 x 150..4096 tokens 32/8 heads M = 32 1055 / 900, M = 64 1553 / 1303, M = 128
-    // 2856 / 2469, 28/4 heads M = 64 1152 / 1041, 40/8 heads 2491 / 2194; 32 x 100..1500 M = 64 1299 / 1054;
-    // 2 x 1000..3000 191 / 153.  Where most workgroups have a whole chunk the row chunks of a slice of
-    // K no longer run side by side, which costs more than the order gives: 3 x 5000..20000 M = 128 32/8 heads
-    // 2752 / 2854, 40/8 4238 / 4302; with one row chunk there is nothing to lose (M = 64 1499 / 1448, 8 x 4096..
-    // 32768 5288 / 5243).
+    // Order of the workgroups of a ragged batch
     PairOrder order{};
     int whole_first = -1;
-    if (pb.batch > 1 && workgroups < (int64_t(1) << 31)) {
+    if (pb.batch > 1) {
       int last[KVC_MAX_BATCH], whole = 0, count = 0;
       for (int b = 0; b < pb.batch; ++b) {
         const int n = pb.seq.cu[b + 1] - pb.seq.cu[b];
@@ -759,7 +752,10 @@ kvc_status launch_score(const Problem& pb, const void* const* q, const void* con
       }
       auto rest = [&](int b) { return (pb.seq.cu[b + 1] - pb.seq.cu[b]) % chunk; };
       std::sort(last, last + count, [&](int x, int y) { return rest(x) != rest(y) ? rest(x) > rest(y) : x < y; });
-      if (count > 0 && (whole > 0 ? L.row_chunks == 1 || whole <= count : rest(last[0]) > rest(last[count - 1]))) {
+      auto tiles = [](int keys) { return (keys + MF_TILE - 1) / MF_TILE; };
+      const int longest = tiles(whole > 0 || count == 0 ? chunk : rest(last[0]));
+      const int shortest = tiles(count > 0 ? rest(last[count - 1]) : chunk);
+      if (longest_first(workgroups, L.row_chunks, whole, count, longest, shortest)) {
         whole_first = whole;
         for (int i = 0; i < count; ++i) order.last[i] = uint8_t(last[i]);
       }
