@@ -216,10 +216,11 @@ __device__ __forceinline__ float merge_few(const float* __restrict__ part_m, con
 //   the workgroup waits for tile t+1, meets at a barrier, starts the load of
 //   tile t+2 into the buffer of tile t and (EMIT) writes out tile t-1; the last
 //   phase already prefetches the first fragments of tile t+1.
-// The waits are wait_loads, which the compiler sees: behind plain ones it put a vmcnt(0) of its own, for
-// the query fragments, in front of the first product of every macro tile of the statistics pass, and
-// tile t+2 had the last phase of tile t to arrive in, not four phases (whole passes: 32 sequences
-// of 4096 tokens at 40/8 heads 0.9 % shorter without it, 128k tokens in one within noise).
+// The wait in front of the first tile, which covers the query fragments too, is wait_loads, which the compiler
+// sees: behind a plain one it put a vmcnt(0) of its own, for these fragments, in front of the first product of every
+// macro tile of the statistics pass, and tile t+2 had the last phase of tile t to arrive in, not four phases (whole
+// passes: 32 sequences of 4096 tokens at 40/8 heads 0.9 % shorter without it, 128k tokens in one within noise).  The
+// waits of the later tiles are plain ones: their loads are inline asm, which the compiler does not count.
 //
 // causal != 0: task token m sits at position n - window + m of its sequence and
 // sees keys at positions <= that only.  Tiles that lie wholly below position
@@ -292,7 +293,7 @@ __device__ __forceinline__ void score_mfma_body(
   if (!EMIT && bx == 0 && by == 0 && bz == 0 && threadIdx.x == 0) *defer.count = 0;
   const int chunk_shift = __builtin_ctz(chunk_keys);   // chunk_keys is a power of two (host-checked)
   int b = 0, chunk = bx;
-  if (whole >= 0 && bx >= whole) {
+  if (__builtin_expect(whole >= 0 && bx >= whole, 0)) {
     b = order.last[bx - whole];
     chunk = (seq.cu[b + 1] - seq.cu[b]) >> chunk_shift;
   } else {
@@ -773,7 +774,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void score_mfma(
   KVC_MFMA_SHARED(EMIT);
   constexpr int MODE = (EMIT && TASK_MAX) ? 1 : 0;
   int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-  if (REM > 0 || whole >= 0) {
+  if (REM > 0 || __builtin_expect(whole >= 0, 0)) {   // (out of the way of a launch in plain order)
     const uint32_t p = bx + gridDim.x * (by + gridDim.y * bz), hkv = gridDim.y / row_chunks;
     const GridBlock at = whole >= 0 ? pair_major_block(p, gridDim.x, hkv, row_chunks, gridDim.z)
                                           : row_chunk_block(p, gridDim.x, hkv, row_chunks, gridDim.z);
